@@ -65,7 +65,7 @@ AttnPlan plan_attn(const aurora_attn_desc* d) {
   p.part_o_off = pb_bytes;
   if (p.mfma) {
     p.row_tiles = (p.rows_per_group + 31) / 32;
-    // the wide-row kernel (more than one row tile) writes two partials per segment
+    // (the wide-row kernel writes one partial per segment; its share of slots keeps the size that callers plan with)
     p.slots = (kAttnWorkgroups + d->batch * d->num_kv_heads) * (p.row_tiles > 1 ? 2 : 1);
     const size_t nrows = (size_t)p.slots * p.row_tiles * 32;
     p.part_ml_off = p.part_o_off + align_up(nrows * d->head_dim * sizeof(float));

@@ -58,8 +58,13 @@ hipError_t launch_attn_plan(const int32_t* seq_lens, int B, int Hkv, int32_t* PB
   return hipGetLastError();
 }
 
-// kFp8KV: kp_ / vp_ hold E4M3 codes and k_scale / v_scale [Hkv] their per-head scales (see Tile8 above);
-// otherwise bf16 pools, loaded straight into LDS.
+constexpr int kNarrowPar = 4;  // tiles of a run that the narrow kernel's wavefronts take at a time
+constexpr int kWidePar = 2;    // ... the wide kernel's two tile-parity groups
+
+// kFp8KV: kp_ / vp_ hold E4M3 codes and k_scale / v_scale [Hkv] their per-head scales ; they too go straight into LDS and are
+// widened between the LDS read and the matrix instruction (see attn_tile.hpp).  Staged through registers and widened into
+// LDS the sweep of 32 requests of 1K-4K tokens took 53 us (the loads in flight, the accumulators and the conversions did not
+// fit into 256 registers: every tile waited for spill traffic behind its loads); with codes in LDS 37 us, 4.2 TB/s.
 template <bool kLocalPlan, bool kFp8KV>
 __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
     const bf16_t* __restrict__ q, const void* __restrict__ kp_, const void* __restrict__ vp_,
@@ -79,6 +84,7 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
 
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
   __shared__ int s_wsum[4];
+  __shared__ int s_par[kMaxNq];  // the request's tree: the ancestor walk is a chain of dependent reads
   if (kLocalPlan) {
     // every workgroup builds the prefix itself; workgroup (0,0) also publishes it for the merge kernel
     build_prefix(seq_lens, B, Hkv, s_pb, s_wsum);
@@ -89,8 +95,10 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
 
   const int rt = blockIdx.y, row_tiles = gridDim.y;
   const int U = pbv(B);
-  int u = unit_begin(U, gridDim.x, blockIdx.x);
-  const int u_end = unit_begin(U, gridDim.x, blockIdx.x + 1);
+  const int wgs = active_wgs(U, gridDim.x, kNarrowPar);
+  if ((int)blockIdx.x >= wgs) return;
+  int u = unit_begin(U, wgs, blockIdx.x);
+  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv;
@@ -138,25 +146,13 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const float scale_log2 = kFp8KV ? scale_log2_q * k_scale[hk] : scale_log2_q;
-    {
-      // 32 query rows -> LDS, 16-byte chunks swizzled like the K rows (they are read the same way)
-      const u32x4_t* qp = (const u32x4_t*)(q + (((size_t)b * Nq + qs_node) * Hq + hk * G + qs_g) * kAtD);
-      const int c0 = (tid & 7) * 2;
-      u32x4_t z = {0u, 0u, 0u, 0u};
-      const u32x4_t v0 = qs_ok ? qp[c0] : z;
-      const u32x4_t v1 = qs_ok ? qp[c0 + 1] : z;
-      *(u32x4_t*)(qbuf + qs_row * kAtRowBytes + ((c0 ^ (qs_row & 15)) * 16)) = v0;
-      *(u32x4_t*)(qbuf + qs_row * kAtRowBytes + (((c0 + 1) ^ (qs_row & 15)) * 16)) = v1;
-    }
-    // chunk slots this node may see: itself and its ancestors (chain: every slot up to its own)
-    unsigned long long anc;
-    if (parents) {
-      anc = 0;
-      for (int a = node, hops = 0; a >= 0 && hops <= Nq; a = parents[(size_t)b * Nq + a], ++hops) anc |= 1ull << a;
-    } else {
-      anc = node == 63 ? ~0ull : ((1ull << (node + 1)) - 1);
-    }
-
+    // the segment's 32 query rows: on their way while the first tiles are requested
+    const u32x4_t* qp = (const u32x4_t*)(q + (((size_t)b * Nq + qs_node) * Hq + hk * G + qs_g) * kAtD);
+    const int c0 = (tid & 7) * 2;
+    const u32x4_t qz = {0u, 0u, 0u, 0u};
+    const u32x4_t q0 = qs_ok ? qp[c0] : qz;
+    const u32x4_t q1 = qs_ok ? qp[c0 + 1] : qz;
+    const int par_n = parents && tid < Nq ? parents[(size_t)b * Nq + tid] : -1;
     const int ntile = t1 - t0;
     const int32_t* bt = block_table + (size_t)b * max_pages;
 
@@ -183,40 +179,57 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
     SoftmaxState st;
     softmax_state_reset(st);
 
-    __syncthreads();  // query rows staged (nothing is in flight yet, so the fence costs nothing)
+    // query rows -> LDS, 16-byte chunks swizzled like the K rows (they are read the same way)
+    auto stage_query = [&]() {
+      *(u32x4_t*)(qbuf + qs_row * kAtRowBytes + ((c0 ^ (qs_row & 15)) * 16)) = q0;
+      *(u32x4_t*)(qbuf + qs_row * kAtRowBytes + (((c0 + 1) ^ (qs_row & 15)) * 16)) = q1;
+      if (tid < Nq) s_par[tid] = par_n;
+      __syncthreads();
+    };
     if constexpr (kFp8KV) {
-      // This wavefront's tiles are wv, wv + 4, ...; two of them are always on their way into registers.
-      // Loads past the wavefront's last tile re-read that tile (cache hits), so the loop body is straight
-      // code and the compiler's wait counts leave the younger tile in flight.
+      // This wavefront's tiles are wv, wv + 4, ...; K and V of two of them are on their way into the two halves of its
+      // buffers, and tile i + 2 takes the place of tile i as soon as the products have read it.
       const int n_my = ntile > wv ? (ntile - wv + 3) >> 2 : 0;
-      if (n_my > 0) {
-        const uint8_t* kp8 = (const uint8_t*)kp_;
-        const uint8_t* vp8 = (const uint8_t*)vp_;
-        auto fetch = [&](Tile8& t, int i) {
-          const int tile = wv + 4 * min(i, n_my - 1);
+      const uint8_t* kp8 = (const uint8_t*)kp_;
+      const uint8_t* vp8 = (const uint8_t*)vp_;
+      auto issue_k8 = [&](int i, int pid_a, int pid_b) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          issue_rows8<false>(kp8, kbuf + (i & 1) * kAtTile8, j, start + (wv + 4 * i) * kAtTile, L, page_shift, Hkv, hk, pid_a,
+                             pid_b, lane);
+      };
+      auto issue_v8 = [&](int i, int pid_a, int pid_b) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          issue_rows8<true>(vp8, vbuf + (i & 1) * kAtTile8, j, start + (wv + 4 * i) * kAtTile, L, page_shift, Hkv, hk, pid_a,
+                            pid_b, lane);
+      };
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (i < n_my) {
           int pa, pb;
-          tile_pages(tile, pa, pb);
-          load_tile8(t, kp8, vp8, start + tile * kAtTile, L, page_shift, Hkv, hk, pa, pb, lane);
-        };
-        // `live` is wave-uniform; a dead turn (odd tile count) still spills and fetches, so that the order
-        // of loads and waits is the same on every path
-        auto consume = [&](Tile8& t, int i, bool live) {
-          spill_tile8(t, kbuf, vbuf, lane);
-          fetch(t, i + 2);
-          if (live) {
-            const f32x16_t s_acc = tile_scores(kbuf, qbuf, li, lh);
-            bf16x8_t pb2[2];
-            tile_softmax(s_acc, st, pb2, scale_log2, start + (wv + 4 * i) * kAtTile, prefix, L, anc, lh);
-            tile_pv(vbuf, pb2, st, lane);
-          }
-        };
-        Tile8 ta, tb;
-        fetch(ta, 0);
-        fetch(tb, 1);
-        for (int i = 0; i < n_my; i += 2) {
-          consume(ta, i, true);
-          consume(tb, i + 1, i + 1 < n_my);
+          tile_pages(wv + 4 * i, pa, pb);
+          issue_k8(i, pa, pb);
+          issue_v8(i, pa, pb);
         }
+      stage_query();
+      const unsigned long long anc = ancestor_mask(parents ? s_par : nullptr, node, Nq);
+      QFrags qf;
+      load_q_frags8(qf, qbuf, li, lh);
+      for (int i = 0; i < n_my; ++i) {
+        const bool next = i + 1 < n_my, more = i + 2 < n_my;
+        int pa = 0, pb = 0;  // page ids of tile i + 2: scalar loads issued a tile ahead of their use
+        if (more) tile_pages(wv + 4 * (i + 2), pa, pb);
+        if (next) WAIT_VMCNT(12); else WAIT_VMCNT(4);  // K(i) landed; V(i), K(i+1), V(i+1) may be in flight
+        const f32x16_t s_acc = tile_scores8(kbuf + (i & 1) * kAtTile8, qf, li, lh);
+        asm volatile("" ::: "memory");  // the LDS reads above stay above the overwrite
+        if (more) issue_k8(i + 2, pa, pb);
+        bf16x8_t pb2[2];
+        tile_softmax(s_acc, st, pb2, scale_log2, start + (wv + 4 * i) * kAtTile, prefix, L, anc, lh);
+        if (more) WAIT_VMCNT(12); else if (next) WAIT_VMCNT(8); else WAIT_VMCNT(0);  // V(i) landed
+        tile_pv8(vbuf + (i & 1) * kAtTile8, pb2, st, lane);
+        asm volatile("" ::: "memory");
+        if (more) issue_v8(i + 2, pa, pb);
       }
     } else {
     int tt = wv;
@@ -226,6 +239,9 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
       issue_k(tt, pa0, pb0);
       issue_v(tt, pa0, pb0);
     }
+    stage_query();
+    // chunk slots this node may see: itself and its ancestors (chain: every slot up to its own)
+    const unsigned long long anc = ancestor_mask(parents ? s_par : nullptr, node, Nq);
     for (; tt < ntile; tt += 4) {
       const bool more = tt + 4 < ntile;
       // page ids of the next tile: scalar loads issued a whole tile ahead of their use
@@ -304,14 +320,14 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
 // byte is still read once per pair while two wavefronts per SIMD hide each other's latencies.  K/V
 // tiles go through a ring of LDS stages of two tiles each (every wavefront loads an eighth of both),
 // one workgroup barrier per step; one workgroup per compute unit.  Work is dealt out exactly as in the
-// narrow kernel; each wavefront writes its own partial, two per segment and query tile.
+// narrow kernel; a segment ends with a merge of the two parities through LDS.
 constexpr int kWideThreads = 512;
 constexpr int kWideStages = 3;
 constexpr int kWideStageBytes = 2 * 2 * kAtTileBytes;                // two tiles, K and V
 constexpr int kWideQBytes = 4 * 32 * kAtRowBytes;                    // four query tiles
 constexpr int kWideLdsBytes = kWideQBytes + kWideStages * kWideStageBytes;
 
-// kFp8KV: the cache holds E4M3 codes (see Tile8 above).  A wavefront then fetches its eighth of a step - four
+// kFp8KV: the cache holds E4M3 codes.  A wavefront then fetches its eighth of a step - four
 // token rows of K in lanes 0..31, of V in lanes 32..63, for each of the step's two tiles - into registers
 // two steps ahead, and widens it into the ring stage right before the step's barrier.
 template <bool kLocalPlan, bool kFp8KV>
@@ -329,6 +345,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
   char* ring = wlds + kWideQBytes;
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
   __shared__ int s_wsum[kWideThreads / kWave];
+  __shared__ int s_par[kMaxNq];
+  __shared__ float s_ml[2][4][2][32];  // (m, l) of the rows of each parity group's query tiles
   if (kLocalPlan) {
     // as build_prefix, for 512 threads (threads 256.. own requests beyond 1024: none)
     {
@@ -363,8 +381,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
   const int U = pbv(B);
-  int u = unit_begin(U, gridDim.x, blockIdx.x);
-  const int u_end = unit_begin(U, gridDim.x, blockIdx.x + 1);
+  const int wgs = active_wgs(U, gridDim.x, kWidePar);
+  if ((int)blockIdx.x >= wgs) return;
+  int u = unit_begin(U, wgs, blockIdx.x);
+  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv;
@@ -410,29 +430,20 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
     const int32_t* bt = block_table + (size_t)b * max_pages;
     const float scale_log2 = kFp8KV ? scale_log2_q * k_scale[hk] : scale_log2_q;
 
-    // the four query tiles -> LDS
+    // the four query tiles: on their way while the first steps are requested
+    const int c0 = (tid & 7) * 2;
+    u32x4_t q0[2], q1[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int ti = qs_half * 2 + i;
-      const int m = (blockIdx.y * 4 + ti) * 32 + qs_row;
+      const int m = (blockIdx.y * 4 + qs_half * 2 + i) * 32 + qs_row;
       const bool ok = m < R;
       const int nd = ok ? m / G : 0, g = ok ? m % G : 0;
       const u32x4_t* qp = (const u32x4_t*)(q + (((size_t)b * Nq + nd) * Hq + hk * G + g) * kAtD);
-      const int c0 = (tid & 7) * 2;
-      u32x4_t z = {0u, 0u, 0u, 0u};
-      const u32x4_t v0 = ok ? qp[c0] : z;
-      const u32x4_t v1 = ok ? qp[c0 + 1] : z;
-      char* dst = qall + ti * (32 * kAtRowBytes) + qs_row * kAtRowBytes;
-      *(u32x4_t*)(dst + ((c0 ^ (qs_row & 15)) * 16)) = v0;
-      *(u32x4_t*)(dst + (((c0 + 1) ^ (qs_row & 15)) * 16)) = v1;
+      const u32x4_t z = {0u, 0u, 0u, 0u};
+      q0[i] = ok ? qp[c0] : z;
+      q1[i] = ok ? qp[c0 + 1] : z;
     }
-    unsigned long long anc;
-    if (parents) {
-      anc = 0;
-      for (int a = node, hops = 0; a >= 0 && hops <= Nq; a = parents[(size_t)b * Nq + a], ++hops) anc |= 1ull << a;
-    } else {
-      anc = node == 63 ? ~0ull : ((1ull << (node + 1)) - 1);
-    }
+    const int par_n = parents && tid < Nq ? parents[(size_t)b * Nq + tid] : -1;
 
     // this wavefront's eighth of a step: load instruction `wave` of K and of V, for both tiles of the step
     // (a tile past the end of the sequence re-reads the last one; it is never multiplied)
@@ -451,9 +462,20 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
 
     SoftmaxState st;
     softmax_state_reset(st);
-    __syncthreads();  // query tiles staged; the ring is idle
     QFrags qf;  // this wavefront's query tile as MFMA operand fragments, for the whole run
-    load_q_frags(qf, qtile, li, lh);
+    unsigned long long anc;
+    auto stage_query = [&]() {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        char* dst = qall + (qs_half * 2 + i) * (32 * kAtRowBytes) + qs_row * kAtRowBytes;
+        *(u32x4_t*)(dst + ((c0 ^ (qs_row & 15)) * 16)) = q0[i];
+        *(u32x4_t*)(dst + (((c0 + 1) ^ (qs_row & 15)) * 16)) = q1[i];
+      }
+      if (tid < Nq) s_par[tid] = par_n;
+      __syncthreads();
+      load_q_frags(qf, qtile, li, lh);
+      anc = ancestor_mask(parents ? s_par : nullptr, node, Nq);
+    };
     auto compute_step = [&](int sidx) {
       const int tt = 2 * sidx + grp;
       if (rt_ok && tt < ntile) {
@@ -510,12 +532,14 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
       fetch(ra, 0);
       __builtin_amdgcn_sched_barrier(0);  // issue order = use order, or the first wait covers both steps
       fetch(rb, 1);
+      stage_query();
       for (int sidx = 0; sidx < nstep; sidx += 2) {
         turn(ra, sidx, true);
         turn(rb, sidx + 1, sidx + 1 < nstep);  // nstep is the same for the whole workgroup
       }
     } else {
       for (int i = 0; i < kWideStages - 1 && i < nstep; ++i) issue_step(i);
+      stage_query();
       for (int sidx = 0; sidx < nstep; ++sidx) {
         // steps sidx+1 .. sidx+kWideStages-2 may stay in flight; near the end of the segment fewer were issued
         if (nstep - 1 - sidx >= kWideStages - 2) WAIT_VMCNT(4 * (kWideStages - 2)); else WAIT_VMCNT(0);
@@ -528,21 +552,40 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
     }
 
     pin_accumulators(st);
-    // each wavefront writes the partial of its own query tile and tile parity
+    // The two parity groups' results of a query tile become one partial: each group hands half of its columns to the
+    // other through the idle ring (lane-linear, the lanes of both hold the same rows), so that a segment writes 512
+    // bytes per query row and the merge kernel reads as many.
     const float l_row = st.l_half + __shfl_xor(st.l_half, 32, kWave);
-    if (row_ok) {
-      const size_t prow = (((size_t)slot * 2 + grp) * row_tiles + rt) * 32 + li;
+    __syncthreads();  // every wavefront is done with the ring
+    if (lh == 0) { s_ml[grp][wq][0][li] = st.m_run; s_ml[grp][wq][1][li] = l_row; }
+    f32x4_t* give = (f32x4_t*)(ring + wave * kAtTileBytes) + lane;
+    const f32x4_t* take = (const f32x4_t*)(ring + (wave ^ 4) * kAtTileBytes) + lane;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x16_t& src = grp == 0 ? st.o[2 + db] : st.o[db];
+        give[(db * 4 + g) * kWave] = f32x4_t{src[4 * g], src[4 * g + 1], src[4 * g + 2], src[4 * g + 3]};
+      }
+    __syncthreads();
+    const float m_own = st.m_run, m_oth = s_ml[grp ^ 1][wq][0][li], l_oth = s_ml[grp ^ 1][wq][1][li];
+    const float m_new = fmaxf(m_own, m_oth), m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float f_own = __builtin_amdgcn_exp2f(m_own - m_ref), f_oth = __builtin_amdgcn_exp2f(m_oth - m_ref);
+    if (row_ok) {
+      const size_t prow = ((size_t)slot * row_tiles + rt) * 32 + li;
+      const float vs = kFp8KV ? v_scale[hk] : 1.f;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          f32x4_t o = {st.o[db][4 * g], st.o[db][4 * g + 1], st.o[db][4 * g + 2], st.o[db][4 * g + 3]};
-          if constexpr (kFp8KV) o *= v_scale[hk];
-          *(f32x4_t*)(part_o + prow * kAtD + 32 * db + 8 * g + 4 * lh) = o;
+          const f32x16_t& src = grp == 0 ? st.o[db] : st.o[2 + db];
+          const f32x4_t own = {src[4 * g], src[4 * g + 1], src[4 * g + 2], src[4 * g + 3]};
+          const f32x4_t o = own * (f_own * vs) + take[(db * 4 + g) * kWave] * (f_oth * vs);
+          *(f32x4_t*)(part_o + prow * kAtD + 32 * (2 * grp + db) + 8 * g + 4 * lh) = o;
         }
-      if (lh == 0) {
-        part_ml[prow * 2 + 0] = st.m_run * (1.0f / kLog2e);  // natural-log units (-inf if nothing was visible)
-        part_ml[prow * 2 + 1] = l_row;
+      if (grp == 0 && lh == 0) {
+        part_ml[prow * 2 + 0] = m_new * (1.0f / kLog2e);  // natural-log units (-inf if nothing was visible)
+        part_ml[prow * 2 + 1] = f_own * l_row + f_oth * l_oth;
       }
     }
     __syncthreads();  // the query tiles and the ring are about to be rewritten
@@ -551,59 +594,92 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
 
 // Merge the partials of one output row (request b, node n, query head hq): the segments of its
 // (request, KV head) pair sit in slots w + pair for the workgroups w whose unit range meets the pair's.
-// Thirty-two threads per row (four output columns each), eight rows per workgroup: the merge is a short chain
-// of dependent loads, so what counts is how many rows a compute unit has in flight.
-constexpr int kCombineRows = 8;
-__global__ __launch_bounds__(32 * kCombineRows) void attn_mfma_combine(const float* __restrict__ part_o,
-                                                                       const float* __restrict__ part_ml,
-                                                                       const int32_t* __restrict__ seq_lens,
-                                                                       const int32_t* __restrict__ PB,
-                                                                       bf16_t* __restrict__ out, int B, int Nq, int Hq,
-                                                                       int Hkv, int wgs, int row_tiles, int groups,
-                                                                       unsigned n_rows, float* __restrict__ lse_out) {
-  const size_t row = (size_t)blockIdx.x * kCombineRows + (threadIdx.x >> 5);  // (b*Nq + n)*Hq + hq
-  if (row >= n_rows) return;
-  const int hq = (int)(row % Hq);
-  const int n = (int)((row / Hq) % Nq);
-  const int b = (int)(row / ((size_t)Hq * Nq));
-  const int G = Hq / Hkv;
-  const int hk = hq / G;
-  const int mrow = n * G + hq % G;
-  const int rt = mrow >> 5, li = mrow & 31;
-  const int n_b = (seq_lens[b] + kAtTile - 1) / kAtTile;
-  const int u0 = PB[b] + hk * n_b, u1 = u0 + n_b;
-  // (a sequence of length 0 has no unit and no partial: w1 < w0, nothing is merged and the row comes out as zeros)
-  const int w0 = n_b > 0 ? unit_owner(PB[B], wgs, u0) : 0, w1 = n_b > 0 ? unit_owner(PB[B], wgs, u1 - 1) : -1;
-  const int pair = b * Hkv + hk;
+// Thirty-two threads (four output columns each) fold a run of a row's partials, a few at a time: the merge is a short
+// chain of dependent loads, so what counts is how many loads are in flight.  A row is given to kSplit such groups of
+// threads, whose results meet in LDS; a workgroup is eight groups.  One request of 2777 tokens (22 partials a row; 64 before
+// active_wgs): 27 us one row per group, four partials at a time -> 4.1 us with kSplit = 8.
+constexpr int kCombineGroups = 8;
+template <int kSplit>
+__global__ __launch_bounds__(32 * kCombineGroups) void attn_mfma_combine(const float* __restrict__ part_o,
+                                                                         const float* __restrict__ part_ml,
+                                                                         const int32_t* __restrict__ seq_lens,
+                                                                         const int32_t* __restrict__ PB,
+                                                                         bf16_t* __restrict__ out, int B, int Nq, int Hq,
+                                                                         int Hkv, int wgs_launched, int row_tiles,
+                                                                         int par, float* __restrict__ lse_out) {
+  const int grp = threadIdx.x >> 5, sub = grp % kSplit;
+  const int b = blockIdx.x / Nq, n = blockIdx.x - b * Nq;
+  const int hq = blockIdx.y * (kCombineGroups / kSplit) + grp / kSplit;
+  const size_t row = (size_t)blockIdx.x * Hq + hq;  // (b*Nq + n)*Hq + hq
+  const bool row_ok = hq < Hq;
+  if (kSplit == 1 && !row_ok) return;
   const int d4 = threadIdx.x & 31;  // columns 4 d4 .. 4 d4 + 3
-  // online merge, four partials' loads in flight at a time; partial p of the pair is segment
-  // (w0 + p / groups), tile parity p % groups
   float M = -INFINITY, den = 0.f;
   f32x4_t num = {0.f, 0.f, 0.f, 0.f};
-  const int np = (w1 - w0 + 1) * groups;
-  for (int p0 = 0; p0 < np; p0 += 4) {
-    float ms[4], ls[4];
-    f32x4_t os[4];
+  if (row_ok) {
+    const int G = Hq / Hkv;
+    const int hk = hq / G;
+    const int mrow = n * G + hq - hk * G;
+    const int rt = mrow >> 5, li = mrow & 31;
+    const int n_b = (seq_lens[b] + kAtTile - 1) / kAtTile;
+    const int U = PB[B];
+    const int u0 = PB[b] + hk * n_b, u1 = u0 + n_b;
+    const int wgs = active_wgs(U, wgs_launched, par);
+    // (a sequence of length 0 has no unit and no partial: w1 < w0, nothing is merged and the row comes out as zeros)
+    const int w0 = n_b > 0 ? unit_owner(U, wgs, u0) : 0, w1 = n_b > 0 ? unit_owner(U, wgs, u1 - 1) : -1;
+    const int pair = b * Hkv + hk;
+    const int np = w1 - w0 + 1;
+    const int per = (np + kSplit - 1) / kSplit;
+    const int p_end = min(np, (sub + 1) * per);
+    const size_t prow0 = ((size_t)(w0 + pair) * row_tiles + rt) * 32 + li;
+    constexpr int kU = kSplit == 1 ? 4 : 8;
+    for (int p0 = sub * per; p0 < p_end; p0 += kU) {
+      float ms[kU], ls[kU];
+      f32x4_t os[kU];
+      float top = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int pp = p0 + i < np ? p0 + i : 0;
-      const bool ok = p0 + i < np;
-      const size_t sl = (size_t)(w0 + pp / groups + pair) * groups + pp % groups;
-      const size_t prow = (sl * row_tiles + rt) * 32 + li;
-      const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
-      ms[i] = ok ? part_ml[prow * 2] : -INFINITY;
-      ls[i] = ok ? part_ml[prow * 2 + 1] : 0.f;
-      os[i] = ok ? *(const f32x4_t*)(part_o + prow * kAtD + 4 * d4) : z;
-    }
+      for (int i = 0; i < kU; ++i) {
+        const bool ok = p0 + i < p_end;
+        const size_t prow = prow0 + (size_t)(ok ? p0 + i : p0) * row_tiles * 32;
+        const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+        ms[i] = ok ? part_ml[prow * 2] : -INFINITY;
+        ls[i] = ok ? part_ml[prow * 2 + 1] : 0.f;
+        os[i] = ok ? *(const f32x4_t*)(part_o + prow * kAtD + 4 * d4) : z;
+        top = fmaxf(top, ms[i]);
+      }
+      const float nm = fmaxf(M, top);
+      if (nm == -INFINITY) continue;  // nothing visible so far
+      const float fo = __expf(M - nm);
+      num *= fo;
+      den *= fo;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (ms[i] == -INFINITY) continue;
-      const float nm = fmaxf(M, ms[i]);
-      const float fo = M == -INFINITY ? 0.f : __expf(M - nm);
-      const float fn = __expf(ms[i] - nm);
-      num = num * fo + os[i] * fn;
-      den = den * fo + fn * ls[i];
+      for (int i = 0; i < kU; ++i) {
+        const float fn = __expf(ms[i] - nm);  // a partial with nothing visible: exp(-inf) = 0, and its sums are zeros
+        num += os[i] * fn;
+        den += ls[i] * fn;
+      }
       M = nm;
+    }
+  }
+  if constexpr (kSplit > 1) {
+    __shared__ float s_m[kCombineGroups], s_den[kCombineGroups];
+    __shared__ f32x4_t s_num[kCombineGroups][32];
+    s_num[grp][d4] = num;
+    if (d4 == 0) { s_m[grp] = M; s_den[grp] = den; }
+    __syncthreads();
+    if (sub != 0 || !row_ok) return;
+#pragma unroll
+    for (int i = 1; i < kSplit; ++i) M = fmaxf(M, s_m[grp + i]);
+    if (M > -INFINITY) {
+      const float f0 = __expf(s_m[grp] - M);
+      num *= f0;
+      den *= f0;
+#pragma unroll
+      for (int i = 1; i < kSplit; ++i) {
+        const float f = __expf(s_m[grp + i] - M);
+        num += s_num[grp + i][d4] * f;
+        den += s_den[grp + i] * f;
+      }
     }
   }
   if (lse_out && d4 == 0) lse_out[row] = den > 0.f ? M + __logf(den) : -INFINITY;
@@ -612,6 +688,14 @@ __global__ __launch_bounds__(32 * kCombineRows) void attn_mfma_combine(const flo
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(den > 0.f ? num[e] / den : 0.f);
   *(u16x4_t*)(out + row * kAtD + 4 * d4) = o;
+}
+
+template <int kSplit>
+static void launch_combine(const AttnLaunch& a, hipStream_t st, int wgs, int row_tiles) {
+  constexpr unsigned per_wg = kCombineGroups / kSplit;
+  hipLaunchKernelGGL(attn_mfma_combine<kSplit>, dim3(a.B * a.Nq, (a.Hq + per_wg - 1) / per_wg), dim3(32 * kCombineGroups), 0,
+                     st, a.part_o, a.part_ml, a.seq_lens, a.plan_pb, (bf16_t*)a.out, a.B, a.Nq, a.Hq, a.Hkv, wgs, row_tiles,
+                     row_tiles == 1 ? kNarrowPar : kWidePar, a.lse_out);
 }
 
 bool attn_mfma_supported(const AttnLaunch& a) {
@@ -666,10 +750,12 @@ hipError_t launch_attn_mfma(const AttnLaunch& a, hipStream_t st) {
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const unsigned rows = (unsigned)((size_t)a.B * a.Nq * a.Hq);
-  hipLaunchKernelGGL(attn_mfma_combine, dim3((rows + kCombineRows - 1) / kCombineRows), dim3(32 * kCombineRows), 0, st,
-                     a.part_o, a.part_ml, a.seq_lens, a.plan_pb, (bf16_t*)a.out, a.B, a.Nq, a.Hq, a.Hkv, wgs, row_tiles,
-                     row_tiles == 1 ? 1 : 2, rows, a.lse_out);
+  // Partials of a row if the requests are about equally long.  From a dozen on, splitting a row over all groups of a
+  // workgroup shortens the chain (4.1 against 13 us at 22 partials); below it the eight times as many workgroups cost more
+  // than the one or two rounds of loads they save (4096 rows of nine partials: 13.0 split, 6.9 whole).
+  const int per_row = wgs / (a.B * a.Hkv) + 1;
+  if (per_row >= 12) launch_combine<8>(a, st, wgs, row_tiles);
+  else launch_combine<1>(a, st, wgs, row_tiles);
   return hipGetLastError();
 }
 

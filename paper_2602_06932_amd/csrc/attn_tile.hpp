@@ -42,8 +42,16 @@ __device__ __forceinline__ int units_per_wg(int U, int wgs) {
   return (c + 3) & ~3;  // a multiple of four tiles: the four wavefronts of a workgroup stay balanced
 }
 
+// Workgroups of a forward sweep that get units: all `wgs` launched ones, or so few that a run still gives each of the
+// `par` wavefront groups that share a run a tile.  Shorter runs would leave wavefronts idle without ending any sooner, and
+// every run adds a partial per query row to the merge.  The sweep and the merge kernel evaluate this alike.
+__device__ __forceinline__ int active_wgs(int U, int wgs, int par) {
+  const int w = (U + par - 1) / par;
+  return w < wgs ? (w > 0 ? w : 1) : wgs;
+}
+
 // The forward sweeps deal the U units to the workgroups as evenly as they divide: contiguous runs of U / wgs units, one
-// more for the first U % wgs workgroups - every resident workgroup has work and no compute unit holds more than its share.
+// more for the first U % wgs workgroups - every active workgroup has work and no compute unit holds more than its share.
 __device__ __forceinline__ int unit_begin(int U, int wgs, int w) {
   const int q = U / wgs, r = U % wgs;
   return w * q + (w < r ? w : r);
@@ -69,6 +77,15 @@ __device__ __forceinline__ void softmax_state_reset(SoftmaxState& st) {
     for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
   st.m_run = -INFINITY;
   st.l_half = 0.f;
+}
+
+// Chunk slots node n may see: itself and its ancestors (par: the request's parents, in LDS; NULL is a chain, where that is
+// every slot up to its own).
+__device__ __forceinline__ unsigned long long ancestor_mask(const int* par, int n, int Nq) {
+  if (!par) return n == 63 ? ~0ull : ((1ull << (n + 1)) - 1);
+  unsigned long long anc = 0;
+  for (int a = n, hops = 0; a >= 0 && hops <= Nq; a = par[a], ++hops) anc |= 1ull << a;
+  return anc;
 }
 
 // Placed between a tile loop and the code that consumes the accumulators piecewise: the accumulators leave the
