@@ -235,32 +235,79 @@ __device__ __forceinline__ void issue_rows(const bf16_t* pool, char* buf, int j,
 }
 
 // ---- KV cache held as E4M3 codes (one byte per element, one scale per KV head) ----------------------------
-// A 32-token tile of codes is 32 rows x 128 B.  It is loaded into registers (four 16-byte loads per lane for
-// K, four for V: 8 lanes cover a token row, so an instruction covers 8 rows = 1 KB of a page), widened
-// exactly to bf16 in registers and written to the wavefront's LDS tile in the layout the LDS-direct loads
-// of the bf16 path produce, so that the score and P.V code is shared.  The scales are applied outside the
-// products: K's folds into the softmax scale, V's multiplies the segment's partial O.
-struct Tile8 { u32x4_t k[4], v[4]; };
+// A 32-token tile of codes is 32 rows x 128 B = 4 KB each of K and V.  The narrow kernel brings the codes into LDS as
+// they are and widens them to bf16 (exactly) between the LDS read and the matrix instruction: half the LDS bytes of a
+// bf16 tile and no registers for tiles on their way.  The scales are applied outside the products: K's folds into the
+// softmax scale, V's multiplies the segment's partial O.
+constexpr int kAtRow8 = kAtD;                  // bytes of a token row of codes
+constexpr int kAtTile8 = kAtTile * kAtRow8;    // 4 KB
 
-// row of a V load instruction's lane group g: consecutive groups take rows four apart, whose swizzle keys
-// have different parity, so that the sixteen lanes an LDS write instruction serves at a time hit distinct banks
-__device__ __forceinline__ int v_row_of_group(int g) { return ((g & 1) << 2) | (g >> 1); }
+// LDS position of 16-byte chunk c of row r: c ^ key.  K rows are read sixteen at a time, one chunk each (key (r >> 1) & 7
+// puts them into different bank groups); a transposing V read takes 32 bytes of rows {0-3, 8-11} or {4-7, 12-15}, and rows
+// of equal parity share a 128-byte bank half, whose four 32-byte slots the key deals out.
+__device__ __forceinline__ int k8_key(int r) { return (r >> 1) & 7; }
+__device__ __forceinline__ int v8_key(int r) { return (((r >> 1) & 1) | (((r >> 3) & 1) << 1)) << 1; }
 
-__device__ __forceinline__ void load_tile8(Tile8& t, const uint8_t* __restrict__ kp, const uint8_t* __restrict__ vp, int j0,
-                                           int L, int page_shift, int Hkv, int hk, int pid_a, int pid_b, int lane) {
-  const int pa = j0 >> page_shift;
-  const int g = lane >> 3, f = lane & 7;
+// one of the 4 load instructions of a K or V tile of codes: token rows 8j .. 8j+7 of the tile starting at j0
+template <bool kIsV>
+__device__ __forceinline__ void issue_rows8(const uint8_t* pool, char* buf, int j, int j0, int L, int page_shift, int Hkv,
+                                            int hk, int pid_a, int pid_b, int lane) {
+  const int r = 8 * j + (lane >> 3);
+  const int tok = min(j0 + r, L - 1);
+  const int pid = (tok >> page_shift) == (j0 >> page_shift) ? pid_a : pid_b;
+  const int chunk = (lane & 7) ^ (kIsV ? v8_key(r) : k8_key(r));
+  const uint8_t* src =
+      pool + ((((size_t)pid * Hkv + hk) << page_shift) + (tok & ((1 << page_shift) - 1))) * kAtRow8 + chunk * 16;
+  load_to_lds_16(src, buf + j * 1024);
+}
+
+// eight E4M3 codes -> eight bf16 (exact: 3 mantissa bits and the exponent range fit)
+__device__ __forceinline__ bf16x8_t widen8(unsigned lo, unsigned hi) {
+  const u32x4_t w = {__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false)),
+                     __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true)),
+                     __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, false)),
+                     __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, true))};
+  return __builtin_bit_cast(bf16x8_t, w);
+}
+
+// S^T = K Q^T from a tile of codes: lane half lh takes the sixteen codes 32 j + 16 lh .. of its token row for the products
+// 2j and 2j + 1, so the query fragments are read in the same order.
+__device__ __forceinline__ void load_q_frags8(QFrags& qf, const char* qtile, int li, int lh) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tok_k = min(j0 + 8 * i + g, L - 1);
-    const int tok_v = min(j0 + 8 * i + v_row_of_group(g), L - 1);
-    const int pid_k = (tok_k >> page_shift) == pa ? pid_a : pid_b;
-    const int pid_v = (tok_v >> page_shift) == pa ? pid_a : pid_b;
-    const size_t ok = ((((size_t)pid_k * Hkv + hk) << page_shift) + (tok_k & ((1 << page_shift) - 1))) * kAtD + f * 16;
-    const size_t ov = ((((size_t)pid_v * Hkv + hk) << page_shift) + (tok_v & ((1 << page_shift) - 1))) * kAtD + f * 16;
-    t.k[i] = __builtin_nontemporal_load((const u32x4_t*)(kp + ok));
-    t.v[i] = __builtin_nontemporal_load((const u32x4_t*)(vp + ov));
+  for (int s = 0; s < 8; ++s)
+    qf.f[s] = *(const bf16x8_t*)(qtile + li * kAtRowBytes + (((4 * (s >> 1) + 2 * lh + (s & 1)) ^ (li & 15)) * 16));
+}
+__device__ __forceinline__ f32x16_t tile_scores8(const char* kbuf, const QFrags& qf, int li, int lh) {
+  f32x16_t s_acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s_acc[r] = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const u32x4_t c = *(const u32x4_t*)(kbuf + li * kAtRow8 + (((2 * j + lh) ^ k8_key(li)) * 16));
+    s_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(widen8(c[0], c[1]), qf.f[2 * j], s_acc, 0, 0, 0);
+    s_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(widen8(c[2], c[3]), qf.f[2 * j + 1], s_acc, 0, 0, 0);
   }
+  return s_acc;
+}
+
+// O^T += V^T P^T from a tile of codes.  ds_read_b64_tr_b8: within 16 lanes, lane i receives byte i % 8 of the 8-byte vectors
+// addressed by lanes i / 8, 2 + i / 8, .., 14 + i / 8 - one column of eight token rows, all an MFMA operand needs.  Lane k
+// of a 16-lane group therefore addresses token row 16 u + 8 (t / 4) + 4 lh + t % 4, t = k / 2, bytes 8 (k % 2) .. of the
+// group's 16 columns.
+__device__ __forceinline__ void tile_pv8(const char* vbuf, const bf16x8_t pb2[2], SoftmaxState& st, int lane) {
+  typedef __attribute__((ext_vector_type(2))) int i32x2_t;
+  typedef __attribute__((address_space(3))) i32x2_t* lds_v2;
+  const int lh = lane >> 5, k = lane & 15, t = k >> 1, g1 = (lane >> 4) & 1;
+  const int row = 8 * (t >> 2) + 4 * lh + (t & 3);
+  const int base = row * kAtRow8 + g1 * 16 + 8 * (k & 1);
+  const int key = v8_key(row) * 16;
+#pragma unroll
+  for (int uu = 0; uu < 2; ++uu)
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      const i32x2_t c = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2)(vbuf + uu * 16 * kAtRow8 + base + ((32 * db) ^ key)));
+      st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(widen8(c[0], c[1]), pb2[uu], st.o[db], 0, 0, 0);
+    }
 }
 
 // sixteen E4M3 codes -> sixteen bf16 (exact: 3 mantissa bits and the exponent range fit), as two 16-byte chunks
@@ -275,22 +322,6 @@ __device__ __forceinline__ void widen16(const u32x4_t c, u32x4_t& lo, u32x4_t& h
   }
   lo = u32x4_t{out[0], out[1], out[2], out[3]};
   hi = u32x4_t{out[4], out[5], out[6], out[7]};
-}
-
-__device__ __forceinline__ void spill_tile8(const Tile8& t, char* kbuf, char* vbuf, int lane) {
-  const int g = lane >> 3, f = lane & 7;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    u32x4_t lo, hi;
-    const int rk = 8 * i + g;
-    widen16(t.k[i], lo, hi);
-    *(u32x4_t*)(kbuf + rk * kAtRowBytes + (((2 * f) ^ (rk & 15)) * 16)) = lo;
-    *(u32x4_t*)(kbuf + rk * kAtRowBytes + (((2 * f + 1) ^ (rk & 15)) * 16)) = hi;
-    const int rv = 8 * i + v_row_of_group(g);
-    widen16(t.v[i], lo, hi);
-    *(u32x4_t*)(vbuf + rv * kAtRowBytes + (((2 * f) ^ v_key(rv)) * 16)) = lo;
-    *(u32x4_t*)(vbuf + rv * kAtRowBytes + (((2 * f + 1) ^ v_key(rv)) * 16)) = hi;
-  }
 }
 
 // prefix of tiles per request (see attn_plan_kernel) built by the whole workgroup into s_pb[0..B], B <= 1024
