@@ -177,8 +177,8 @@ int aurora_verify_attn_static(const aurora_attn_desc* desc, const void* q, const
  *
  * Tree walks at T > 0 over large vocabularies are split over several workgroups per request that wait for each
  * other between vocabulary sweeps.  They fit the device together when nothing else occupies it; the wait is
- * bounded all the same: when the workgroups of a request do not meet in time (a GPU shared with other work), one
- * of them finishes the request alone inside the same call, with the same result bit for bit, only later.  The
+ * bounded all the same: a workgroup that has waited too long for the others (a GPU shared with other work) finishes
+ * the request alone inside the same call, with the same result bit for bit, only later.  The
  * outputs are therefore always complete and valid once the stream is synchronised.  Chains and greedy calls
  * never wait.
  */
@@ -340,7 +340,7 @@ int aurora_trace_emit(const aurora_trace_desc* desc,
                       int8_t* traj,                /* [B, Nq]                                  */
                       void* hip_stream);
 
-/* For tests of the bounded wait described at aurora_verify_accept: the number of polls of the arrival counter a
+/* For tests of the bounded wait described at aurora_verify_accept: the number of polls of the others' sums a
  * workgroup of a split tree walk makes before it stops waiting (process-wide, applies to later calls; negative
  * restores the default of 2^15, some tens of milliseconds).  0 makes every wait fail at once unless the others have
  * already arrived, which forces the finish-alone path; results do not depend on the setting. */

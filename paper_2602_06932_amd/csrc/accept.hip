@@ -17,8 +17,8 @@
 //                       u * total, rescan that group with a wavefront prefix sum for the token.
 // Trees at T > 0 may need one sweep per rejected sibling, each depending on the previous one:
 // accept_tree_kernel walks a request in up to 16 workgroups that split every sweep and exchange their
-// partial sums behind a counting barrier.  The same kernel, one workgroup per request, serves every
-// greedy (T = 0) call, where no sweep exists.
+// partial sums.  The same kernel, one workgroup per request, serves every greedy (T = 0) call, where no
+// sweep exists.
 // All sums are fp64 in a fixed order: results are reproducible bit for bit.
 #include "common.hpp"
 #include "launch.hpp"
@@ -34,8 +34,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // Probability of token v at the current node after `nres` residual steps, in fp64 throughout (used
 // for the accept tests).  p0 = exp(l / T - lse);  p_{s+1} = max(0, p_s - q) / Z_s.
-__device__ __forceinline__ double node_weight(float l, float qv, double lse, double T, int nres, const double* Zs) {
-  double x = exp((double)l / T - lse);
+__device__ __forceinline__ double node_weight(double p0, float qv, int nres, const double* Zs) {
+  double x = p0;
   for (int s = 0; s < nres; ++s) x = fmax(0.0, x - (double)qv) / Zs[s];
   return x;
 }
@@ -71,9 +71,8 @@ __device__ __forceinline__ bool in_list(int v, const int* list, int n) {
   for (int i = 0; i < n; ++i) hit |= list[i] == v;
   return hit;
 }
-__device__ __forceinline__ double node_weight_wor(float l, float qv, int v, double lse, double T, int nres, const double* Zs,
-                                                  const QLevels& ql) {
-  double x = exp((double)l / T - lse);
+__device__ __forceinline__ double node_weight_wor(double p0, float qv, int v, int nres, const double* Zs, const QLevels& ql) {
+  double x = p0;
   for (int s = 0; s < nres; ++s) {
     const double qs = in_list(v, ql.rej, ql.len[s]) ? 0.0 : (double)qv * ql.fac[s];
     x = fmax(0.0, x - qs) / Zs[s];
@@ -125,10 +124,8 @@ struct AcceptParams {
   int32_t* st_rej;    // [B] 1: draw from max(0, p - q); 0: draw from p
   double* gsum;       // [B, ngroups]
   int32_t* lastpos;   // [B, slices] largest token with positive weight per slice, or -1
-  // tree path with several workgroups per request: gsum is [B, 2, ngroups] and lastpos [B, 2, tree_slices]
-  // (two copies, alternating by sweep), tree_bar [B] counts workgroup arrivals (zero at launch)
-  int tree_slices;
-  int32_t* tree_bar;
+  // tree path with several workgroups per request: [B, Nq, tree_slices] sums of the slices of every sweep, kNotYet at launch
+  unsigned long long* exch;
   const float* temps;  // [B] one temperature per request (0 = that request is verified greedily), or NULL
   int wor;             // tree walk: siblings were drawn without replacement
   int spin_limit;      // tree walk with several workgroups: polls of the arrival counter before giving up
@@ -478,73 +475,93 @@ __global__ __launch_bounds__(kSmallThreads) void accept_chain_pick(AcceptParams 
 }
 
 // ============================================================================================
-// Trees at T > 0, and every greedy call.  Grid (S, B): S workgroups per request.  With S = 1 the
-// request's walk and all its vocabulary sweeps run in one workgroup.  With S > 1 every workgroup of a
-// request repeats the walk (the same inputs give the same decisions, bit for bit) and sweeps only its
-// slice of the vocabulary; after each sweep the group sums are exchanged through global memory behind a
-// counting barrier, and every workgroup scans all of them in the same order as the one-workgroup form -
-// so both forms return identical results.  The launcher keeps S * B within the number of compute units,
-// so all workgroups of a request are resident together; the wait on the counter is bounded all the same.
+// Trees at T > 0, and every greedy call.  Grid (S, B): S workgroups per request, each sweeping one slice of the vocabulary.
+// Every workgroup repeats the walk (the same inputs give the same decisions, bit for bit); a sweep's slice sums are
+// exchanged through global memory and added in slice order by all.  The final draw is made by the workgroup whose slice
+// holds the crossing.
+//
+// The walk is a chain of dependent sweeps (a rejected sibling's residual needs the normaliser of the level before), so what
+// counts is the time from one exchange to the next.  A sweep at the node of the previous one finds its logits and draft
+// probabilities in registers; a rejection needs only the slice's total (group sums are formed for the draw alone); the walk's
+// state lives in registers of every wavefront - the tree is a lane per node, the next child a ballot - so a step has two
+// workgroup barriers; and a slice sum is its own flag: its word is kNotYet until it is written, so one store and one load
+// cross the dies.  16 trees of 32 nodes over 128 256 ids: 90 us with group sums exchanged behind an arrival counter
+// (release, acquire, then the loads; the rows re-read for every sweep) -> 50 us.
+// The launcher keeps S * B within the number of compute units, so all workgroups of a request are resident together;
+// the wait is bounded all the same.
 // ============================================================================================
 constexpr int kTreeMaxSlices = 16;
-constexpr int kSpinLimit = 1 << 15;  // default number of polls of the arrival counter (tens of milliseconds) before a workgroup stops waiting
+constexpr int kSpinLimit = 1 << 15;  // default number of polls (tens of milliseconds) before a workgroup stops waiting
+constexpr unsigned long long kNotYet = ~0ull;  // no sum has this pattern (it is a NaN; a NaN sum is stored as another one)
 
-// The values exchanged between the workgroups of a request are written and read with device-scope
-// atomic accesses: on this multi-die part they go past the die-local L2 to the point all dies see, so the
-// hand-over needs no L2 write-back or invalidate - only "my stores have been acknowledged" before the
-// arrival is counted.
-__device__ __forceinline__ void store_agent(int32_t* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// What a workgroup reads from another is one 64-bit word per slice and sweep, written and read with device-scope atomic
+// accesses that go past the die-local caches; nothing else is handed over, so no fence is needed.
+__device__ __forceinline__ void store_sum(unsigned long long* p, double v) {
+  unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  if (u == kNotYet) u = 0x7ff8000000000000ull;
+  __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void store_agent(double* p, double v) {
-  __hip_atomic_store((unsigned long long*)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void wait_stores_acknowledged() {
-  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0), nothing else
-  asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ int load_agent(const int32_t* p) {
+__device__ __forceinline__ unsigned long long load_sum(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ double load_agent(const double* p) {
-  const unsigned long long u = __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return __builtin_bit_cast(double, u);
+__device__ __forceinline__ int lane_value(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(u & 0xffffffffu), lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// kHeld: a slice has at most kHold groups per wavefront, whose operands stay in registers from sweep to sweep.
+// kWor: siblings were drawn without replacement.
+constexpr int kHold = 4;
+#define AURORA_INLINE __attribute__((always_inline))
+template <bool kHeld, bool kWor>
 __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P) {
   __shared__ double s_lse[kMaxNq];
   __shared__ int s_arg[kMaxNq];
-  __shared__ double s_Z[kMaxNq], s_invZ[kMaxNq];
   __shared__ double s_gsum[kMaxGroups];
-  __shared__ double s_wtot[kAccWaves];
-  __shared__ int s_cur, s_depth, s_nres, s_last_child, s_state, s_have_gsum, s_pick, s_lastpos, s_fail;
+  __shared__ double s_wtot[kAccWaves], s_tot[kTreeMaxSlices];
+  __shared__ int s_fail, s_pick, s_lastpos;
   __shared__ double s_pick_prefix;
-  // the request's tree, tokens and uniforms: the walk below is one thread chasing them, so they are
-  // staged once instead of being fetched from global memory one dependent load at a time
   __shared__ int s_par[kMaxNq], s_tok[kMaxNq];
   __shared__ float s_u0[kMaxNq], s_u1[kMaxNq];
-  __shared__ float s_ltok[kMaxNq], s_qtok[kMaxNq];  // logit and draft probability of node n's token in its parent's row
-  // siblings without replacement: tokens rejected at the current node, the draft distribution each residual level
-  // was formed with (see QLevels), and the one the next sibling was drawn from
-  __shared__ int s_rej[kMaxNq], s_qlen[kMaxNq], s_cur_len;
-  __shared__ double s_qfac[kMaxNq], s_cur_fac, s_rej_mass;
+  __shared__ float s_qtok[kMaxNq];  // draft probability of node n's token in its parent's row
+  __shared__ double s_p0[kMaxNq];   // target probability of node n's token in its parent's row
+  // Residual levels of the current node, one copy per wavefront (no barrier orders one wavefront's next step against
+  // another's): normalisers; and, for siblings drawn without replacement, the tokens rejected here and the draft
+  // distribution each level was formed with (see QLevels).
+  __shared__ double s_Zw[kAccWaves][kMaxNq], s_invZw[kAccWaves][kMaxNq], s_qfacw[kAccWaves][kMaxNq];
+  __shared__ int s_rejw[kAccWaves][kMaxNq], s_qlenw[kAccWaves][kMaxNq];
 
   const int b = blockIdx.y;
   const int S = (int)gridDim.x, slice = blockIdx.x;  // S > 1 only for sampling walks
-  const bool writer = slice == 0;                     // the workgroup that stores the request's outputs
-  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  const bool writer = slice == 0;                     // the workgroup that stores the walk's outputs
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int Nq = P.Nq, V = P.V;
   const float Tf = request_temperature(P, b);
   const bool greedy = !(Tf > 0.f);
   const double T = greedy ? 1.0 : (double)Tf;
   const double inv_t = 1.0 / T;
   const size_t row0 = (size_t)b * Nq;
+  // operands of the accept tests: their addresses do not depend on the statistics, so the loads fly during the merge
+  int t_par = -1, t_tok = 0;
+  float t_l = 0.f, t_q = 0.f;
   if (tid < Nq) {
-    s_par[tid] = P.parents ? P.parents[row0 + tid] : tid - 1;
-    s_tok[tid] = P.tok[row0 + tid];
+    t_par = P.parents ? P.parents[row0 + tid] : tid - 1;
+    t_tok = P.tok[row0 + tid];
+    s_par[tid] = t_par;
+    s_tok[tid] = t_tok;
     s_u0[tid] = greedy ? 0.f : P.un[(row0 + tid) * 2 + 0];
     s_u1[tid] = greedy ? 0.f : P.un[(row0 + tid) * 2 + 1];
+    if (tid > 0 && !greedy) {
+      t_l = P.logits[(row0 + t_par) * V + t_tok];
+      t_q = q_at(q_row(P, row0 + t_par), t_tok);
+    }
   }
 
   // ---- 1. per-row (logsumexp, arg-max) from the tile statistics ---------------------------------
@@ -556,6 +573,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
     merge_row_stats<32>(P, row0 + nc, T, lane, &mx, &lse, &arg, greedy);
     if ((lane & 31) == 0 && n < Nq) { s_lse[n] = lse; s_arg[n] = arg; }
   }
+  if (tid == 0) s_fail = 0;
   __syncthreads();
 
   // ---- per-node outputs ------------------------------------------------------------------------
@@ -564,15 +582,13 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
     if (P.row_lse && writer) P.row_lse[row0 + n] = (float)s_lse[n];
     float pv = 0.f;
     if (n > 0) {
-      const int par = s_par[n];
-      const int tk = s_tok[n];
       if (greedy) {
-        pv = (tk == s_arg[par]) ? 1.f : 0.f;
+        pv = (t_tok == s_arg[t_par]) ? 1.f : 0.f;
       } else {
-        const float l = P.logits[(row0 + par) * V + tk];
-        s_ltok[n] = l;
-        s_qtok[n] = q_at(q_row(P, row0 + par), tk);
-        pv = (float)exp((double)l / T - s_lse[par]);
+        const double p0 = exp((double)t_l / T - s_lse[t_par]);
+        s_p0[n] = p0;
+        s_qtok[n] = t_q;
+        pv = (float)p0;
       }
     }
     if (writer) {
@@ -604,253 +620,286 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
     return;
   }
 
-  // ---- 2b. sampling walk ------------------------------------------------------------------------
+  // ---- 2b. sampling walk: every wavefront for itself, meeting in the sweeps ----------------------
+  // lane n of every wavefront holds node n
+  const bool node = lane < Nq;
+  const int n_par = node ? s_par[lane] : -2, n_tok = node ? s_tok[lane] : 0;
+  const float n_u0 = node ? s_u0[lane] : 0.f, n_q = node && lane > 0 ? s_qtok[lane] : 0.f;
+  const double n_p0 = node && lane > 0 ? s_p0[lane] : 0.0;
+  double *Zs = s_Zw[wv], *invZs = s_invZw[wv], *qfac = s_qfacw[wv];
+  int *rej = s_rejw[wv], *qlen = s_qlenw[wv];
+
   const int ngroups = (V + kGroup - 1) / kGroup;  // <= kMaxGroups (checked by the launcher)
   const bool vec_ok = rows_vec_ok(P);
   const int per_slice = (ngroups + S - 1) / S;
-  int g_lo = slice * per_slice;
-  int g_hi = min(ngroups, g_lo + per_slice);
-  bool split = S > 1;  // false once the writer has stopped waiting for the others and carries on alone
-  int sweeps = 0;      // sweeps done so far: the same in every workgroup of the request
-  const bool wor = P.wor != 0;
-  const QLevels ql = {s_rej, s_qlen, s_qfac};
-  if (tid == 0) {
-    s_cur = 0; s_depth = 0; s_nres = 0; s_last_child = 0; s_have_gsum = 0; s_fail = 0;
-    s_cur_len = 0; s_cur_fac = 1.0; s_rej_mass = 0.0;
-  }
-  enum { ST_DONE = 0, ST_ACCEPTED = 1, ST_REJECTED = 2 };
-  for (;;) {
-    __syncthreads();
-    if (tid == 0) {
-      const int cur = s_cur;
-      int c = s_last_child + 1;
-      for (; c < Nq; ++c)
-        if (s_par[c] == cur) break;
-      if (c >= Nq) {
-        s_state = ST_DONE;
-      } else {
-        const float l = s_ltok[c];
-        const float qv = s_qtok[c];
-        const int tk = s_tok[c];
-        const double p = wor ? node_weight_wor(l, qv, tk, s_lse[cur], T, s_nres, s_Z, ql)
-                             : node_weight(l, qv, s_lse[cur], T, s_nres, s_Z);
-        // the probability this sibling was drawn with
-        const double qd = !wor ? (double)qv : in_list(tk, s_rej, s_cur_len) ? 0.0 : (double)qv * s_cur_fac;
-        const double u = (double)s_u0[c];
-        s_last_child = c;
-        if (u * qd < p) {
-          s_cur = c;
-          s_depth = s_depth + 1;
-          s_nres = 0;
-          s_have_gsum = 0;
-          s_cur_len = 0; s_cur_fac = 1.0; s_rej_mass = 0.0;
-          if (writer) P.accept_mask[row0 + c] = 1;
-          s_state = ST_ACCEPTED;
-        } else {
-          // the residual level that the sweep below forms subtracts the distribution this sibling was drawn from
-          s_qlen[s_nres] = s_cur_len;
-          s_qfac[s_nres] = s_cur_fac;
-          s_state = ST_REJECTED;
+  auto slice_lo = [&](int s) AURORA_INLINE { return min(ngroups, s * per_slice); };
+  bool solo = S == 1;  // this workgroup sweeps every slice itself
+  const QLevels ql = {rej, qlen, qfac};
+
+  int cur = 0, depth = 0, last_child = 0, nres = 0, sweeps = 0;
+  bool have_total = false;  // `total` and s_tot are those of the current node's weights
+  double total = 0.0;
+  int cur_len = 0;          // siblings without replacement: the distribution the next sibling was drawn from
+  double cur_fac = 1.0, rej_mass = 0.0;
+  Lane4 held[kHold];
+  int held_node = -1, held_slice = -1;
+
+  // the weights (of residual level `level`; skip_last leaves its last step unnormalised) of the four tokens v0 ..
+  auto weights = [&](const Lane4& r, int v0, int level, bool skip_last, double x[4]) AURORA_INLINE {
+    if constexpr (kWor) lane_weights_wor(r, v0, V, s_lse[cur], inv_t, level, x, invZs, skip_last, ql);
+    else lane_weights(r, v0, V, s_lse[cur], inv_t, level, x, invZs, skip_last);
+  };
+  // f(group, its weights in this lane's four tokens) for this wavefront's groups of slice sl, in ascending order
+  auto for_groups = [&](int sl, int level, bool skip_last, auto f) AURORA_INLINE {
+    const int lo = slice_lo(sl), hi = slice_lo(sl + 1);
+    const float* lrow = P.logits + (row0 + cur) * V;
+    const QRow qrow = q_row(P, row0 + cur);
+    if constexpr (kHeld) {
+      if (held_node != cur || held_slice != sl) {
+#pragma unroll
+        for (int i = 0; i < kHold; ++i) {
+          const int gi = lo + wv + i * kAccWaves;
+          if (gi < hi) held[i] = lane_load(lrow, qrow, gi * kGroup + lane * 4, V, vec_ok);
+        }
+        held_node = cur;
+        held_slice = sl;
+      }
+#pragma unroll
+      for (int i = 0; i < kHold; ++i) {
+        const int gi = lo + wv + i * kAccWaves;
+        if (gi < hi) {  // wave-uniform
+          double x[4];
+          weights(held[i], gi * kGroup + lane * 4, level, skip_last, x);
+          f(gi, x);
+        }
+      }
+    } else {
+      for (int g = lo + wv; g < hi; g += kHold * kAccWaves) {
+        Lane4 r[kHold];
+#pragma unroll
+        for (int i = 0; i < kHold; ++i) {
+          const int gi = g + i * kAccWaves;
+          if (gi < hi) r[i] = lane_load(lrow, qrow, gi * kGroup + lane * 4, V, vec_ok);
+        }
+#pragma unroll
+        for (int i = 0; i < kHold; ++i) {
+          const int gi = g + i * kAccWaves;
+          if (gi < hi) {
+            double x[4];
+            weights(r[i], gi * kGroup + lane * 4, level, skip_last, x);
+            f(gi, x);
+          }
         }
       }
     }
-    __syncthreads();
-    const int state = s_state;
-    if (state == ST_ACCEPTED) continue;
+  };
+  // this wavefront's share of a slice's total, parked for the workgroup
+  auto park_share = [&](int sl, int level, bool skip_last) AURORA_INLINE {
+    double acc = 0.0;
+    for_groups(sl, level, skip_last, [&](int, const double* x) AURORA_INLINE { acc += (x[0] + x[1]) + (x[2] + x[3]); });
+    acc = wave_sum(acc);
+    if (lane == 0) s_wtot[wv] = acc;
+  };
+  auto slice_sum = [&]() AURORA_INLINE {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < kAccWaves; ++i) t += s_wtot[i];
+    return t;
+  };
+  for (;;) {
+    const unsigned long long kids = __ballot(n_par == cur && lane > last_child);
+    const int c = kids ? __ffsll((long long)kids) - 1 : -1;  // the next child to test; -1: draw here
+    const float qv = c < 0 ? 0.f : lane_value(n_q, c);
+    const int tk = c < 0 ? -1 : lane_value(n_tok, c);
+    if (c < 0) {
+      if (have_total) break;
+    } else {
+      last_child = c;
+      const double p0 = lane_value(n_p0, c), u = (double)lane_value(n_u0, c);
+      double p, qd;  // qd: the probability this sibling was drawn with
+      if constexpr (kWor) {
+        p = node_weight_wor(p0, qv, tk, nres, Zs, ql);
+        qd = in_list(tk, rej, cur_len) ? 0.0 : (double)qv * cur_fac;
+      } else {
+        p = node_weight(p0, qv, nres, Zs);
+        qd = (double)qv;
+      }
+      if (u * qd < p) {
+        cur = c;
+        ++depth;
+        nres = 0;
+        have_total = false;
+        cur_len = 0; cur_fac = 1.0; rej_mass = 0.0;
+        if (writer && tid == 0) P.accept_mask[row0 + c] = 1;
+        continue;
+      }
+      // the next residual level subtracts the distribution this sibling was drawn from
+      if constexpr (kWor) {
+        qlen[nres] = cur_len;
+        qfac[nres] = cur_fac;
+      }
+    }
 
-    const int cur = s_cur;
-    const float* lrow = P.logits + (row0 + cur) * V;
-    const QRow qrow = q_row(P, row0 + cur);
-    const double lse = s_lse[cur];
-
-    if (state == ST_REJECTED || !s_have_gsum) {
-      // group sums of the weights: after a rejection the unnormalised next residual level,
-      // otherwise (nothing rejected at this node, or its residual vanished) the current level
-      const int nres = state == ST_REJECTED ? s_nres + 1 : s_nres;
-      const bool skip_last = state == ST_REJECTED;
-      int lastpos = -1;
-      constexpr int kBatch = 5;  // groups whose loads a wavefront keeps in flight together (160 KB per workgroup)
-      double* gs_out = P.gsum + ((size_t)b * 2 + (sweeps & 1)) * ngroups;  // used while split
-    sweep_again:
-      for (int g = g_lo + wv; g < g_hi; g += kBatch * kAccWaves) {
-        Lane4 r[kBatch];
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const int gi = g + i * kAccWaves;
-          if (gi < g_hi) r[i] = lane_load(lrow, qrow, gi * kGroup + lane * 4, V, vec_ok);
-        }
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const int gi = g + i * kAccWaves;
-          if (gi < g_hi) {  // wave-uniform
-            const int v0 = gi * kGroup + lane * 4;
-            double x[4];
-            if (wor) lane_weights_wor(r[i], v0, V, lse, inv_t, nres, x, s_invZ, skip_last, ql);
-            else lane_weights(r[i], v0, V, lse, inv_t, nres, x, s_invZ, skip_last);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (x[e] > 0.0) lastpos = max(lastpos, v0 + e);
-            const double sg = wave_sum((x[0] + x[1]) + (x[2] + x[3]));
-            if (lane == 0) {
-              if (split) store_agent(&gs_out[gi], sg); else s_gsum[gi] = sg;
-            }
-          }
+    // The total over the vocabulary of the current level's weights (draw), or of the next one's before it is normalised
+    // (rejection): s_tot per slice and their sum in slice order.
+    const int level = c < 0 ? nres : nres + 1;
+    const bool raw = c >= 0;
+    for (bool done = false; !done;) {
+      const int s0 = solo ? 0 : slice, s1 = solo ? S : slice + 1;
+      for (int sl = s0; sl < s1; ++sl) {
+        park_share(sl, level, raw);
+        __syncthreads();
+        if (solo) {
+          if (tid == 0) s_tot[sl] = slice_sum();
+          __syncthreads();
         }
       }
-      lastpos = wave_max(lastpos);
-      if (tid == 0) s_lastpos = -1;
-      __syncthreads();
-      if (lane == 0) atomicMax(&s_lastpos, lastpos);
-      if (split) {
-        // ---- exchange with the request's other workgroups ----------------------------------------
-        wait_stores_acknowledged();  // this thread's group sums, before the arrival is counted
-        __syncthreads();
-        int32_t* lp = P.lastpos + ((size_t)b * 2 + (sweeps & 1)) * S;
-        if (tid == 0) {
-          store_agent(&lp[slice], s_lastpos);
-          wait_stores_acknowledged();
-          // release: everything this workgroup stored (ordered before this thread by the barrier above) is
-          // visible device-wide before the arrival is
-          __hip_atomic_fetch_add(&P.tree_bar[b], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-          const int target = S * (sweeps + 1);
-          int polls = 0;
-          while (load_agent(&P.tree_bar[b]) < target) {
+      done = true;
+      if (!solo) {
+        unsigned long long* ex = P.exch + ((size_t)b * Nq + sweeps) * S;
+        if (wv == 0) {
+          const double own = slice_sum();
+          if (lane == 0) store_sum(&ex[slice], own);
+          unsigned long long u = lane < S && lane != slice ? kNotYet : 0ull;
+          for (int polls = 0;;) {
+            if (u == kNotYet) u = load_sum(&ex[lane]);
+            if (!__any(u == kNotYet)) break;
             if (++polls > P.spin_limit) { s_fail = 1; break; }
-            __builtin_amdgcn_s_sleep(4);
+            __builtin_amdgcn_s_sleep(1);
           }
-          // acquire: pairs with the release of every arrival counted above
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          if (lane < S) s_tot[lane] = lane == slice ? own : __builtin_bit_cast(double, u);
         }
         __syncthreads();
         if (s_fail) {
-          // A workgroup of the request has not arrived within the bound (the GPU is shared and they are not all
-          // resident, or one of them gave up earlier).  The others leave; the writer, which holds the whole walk
-          // state like every workgroup, repeats this sweep over the entire vocabulary by itself and finishes the
-          // request as the one-workgroup form would: same sums in the same order, so the same result.
-          if (!writer) return;
-          split = false;
-          g_lo = 0;
-          g_hi = ngroups;
-          lastpos = -1;
-          goto sweep_again;
+          // A workgroup of the request has not arrived within the bound (the GPU is shared and they are not all resident,
+          // or one of them gave up earlier): this one, which holds the whole walk state like every workgroup, repeats the
+          // sweep over the entire vocabulary and finishes the request by itself - same sums in the same order, so the same
+          // result.  Others that wait for it run into their own bound and do likewise; what several then write is the same.
+          solo = true;
+          done = false;
+          __syncthreads();  // s_wtot and s_tot are about to be rewritten
         }
-        // loads that bypass this compute unit's L1, which may still hold the copy of two sweeps ago
-        for (int g = tid; g < ngroups; g += kAccThreads) s_gsum[g] = load_agent(&gs_out[g]);
-        if (tid < S) atomicMax(&s_lastpos, load_agent(&lp[tid]));
-        ++sweeps;
       }
-      __syncthreads();
     }
+    ++sweeps;
+    total = 0.0;
+    for (int sl = 0; sl < S; ++sl) total += s_tot[sl];
+    if (c < 0) break;
 
-    // exclusive scan of the group sums: thread t owns groups 4t .. 4t+3
-    double mine[4];
-    double loc = 0.0;
+    have_total = total > 0.0;  // otherwise the residual vanished: the distribution is left as it was
+    if (have_total) {
+      Zs[nres] = total;
+      invZs[nres] = 1.0 / total;
+      ++nres;
+    }
+    if constexpr (kWor) {
+      if (!in_list(tk, rej, cur_len)) {
+        // the rejected token leaves the distribution the later siblings were drawn from
+        rej[cur_len] = tk;
+        ++cur_len;
+        rej_mass += (double)qv;
+        const double left = 1.0 - rej_mass;
+        cur_fac = left > 0.0 ? 1.0 / left : 0.0;
+      }
+    }
+  }
+
+  // ---- 3. inverse-CDF draw ------------------------------------------------------------------------
+  const bool skip_last = have_total;  // the total at hand is that of the unnormalised last level
+  const double thr = (double)lane_value(node ? s_u1[lane] : 0.f, cur) * total;
+  int sl = -1;        // the slice that holds the crossing; if rounding left none, the last one with any weight
+  double base = 0.0;  // the weights before it
+  {
+    double run = 0.0;
+    for (int i = 0; i < S; ++i) {
+      const double t = s_tot[i];
+      if (t > 0.0) { sl = i; base = run; }
+      run += t;
+      if (t > 0.0 && run > thr) break;
+    }
+  }
+  if (writer && tid == 0) P.accept_len[b] = depth;
+  if (sl < 0) {  // no weight anywhere
+    if (writer && tid == 0) P.next_token[b] = -1;
+    return;
+  }
+  if (!solo && sl != slice) return;  // no barrier between workgroups follows
+  if (tid == 0) { s_pick = 0x7fffffff; s_lastpos = -1; }
+  __syncthreads();
+  const int lo = slice_lo(sl), n_loc = slice_lo(sl + 1) - lo;
+  int lastpos = -1;
+  for_groups(sl, nres, skip_last, [&](int gi, const double* x) AURORA_INLINE {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (x[e] > 0.0) lastpos = max(lastpos, gi * kGroup + lane * 4 + e);
+    const double sg = wave_sum((x[0] + x[1]) + (x[2] + x[3]));
+    if (lane == 0) s_gsum[gi - lo] = sg;
+  });
+  lastpos = wave_max(lastpos);
+  if (lane == 0) atomicMax(&s_lastpos, lastpos);
+  __syncthreads();
+  // scan of the slice's group sums: thread t owns groups 4t .. 4t+3
+  double mine[4], loc = 0.0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int g = tid * 4 + i;
+    mine[i] = g < n_loc ? s_gsum[g] : 0.0;
+    loc += mine[i];
+  }
+  const double incl = wave_incl_scan(loc, lane);
+  if (lane == kWave - 1) s_wtot[wv] = incl;
+  __syncthreads();
+  double excl = base + (incl - loc);
+  for (int i = 0; i < kAccWaves; ++i)
+    if (i < wv) excl += s_wtot[i];
+  int found = 0x7fffffff;
+  double before = 0.0;
+  {
+    double run = excl;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int g = tid * 4 + i;
-      mine[i] = g < ngroups ? s_gsum[g] : 0.0;
-      loc += mine[i];
+      const double nxt = run + mine[i];
+      if (g < n_loc && found == 0x7fffffff && mine[i] > 0.0 && nxt > thr) { found = g; before = run; }
+      run = nxt;
     }
-    const double incl = wave_incl_scan(loc, lane);
-    if (lane == kWave - 1) s_wtot[wv] = incl;
-    __syncthreads();
-    double wbase = 0.0, total = 0.0;
-    for (int i = 0; i < kAccWaves; ++i) {
-      if (i < wv) wbase += s_wtot[i];
-      total += s_wtot[i];
-    }
-    const double excl = wbase + incl - loc;
-
-    if (state == ST_REJECTED) {
-      __syncthreads();
-      if (tid == 0) {
-        if (total > 0.0) {
-          s_Z[s_nres] = total;
-          s_invZ[s_nres] = 1.0 / total;
-          s_nres = s_nres + 1;
-          s_have_gsum = 1;
-        } else {
-          s_have_gsum = 0;  // residual vanished: the distribution is left as it was
-        }
-        if (wor) {
-          // the rejected token leaves the distribution the later siblings were drawn from
-          const int c = s_last_child, tk = s_tok[c];
-          if (!in_list(tk, s_rej, s_cur_len)) {
-            s_rej[s_cur_len] = tk;
-            s_cur_len = s_cur_len + 1;
-            s_rej_mass = s_rej_mass + (double)s_qtok[c];
-            const double left = 1.0 - s_rej_mass;
-            s_cur_fac = left > 0.0 ? 1.0 / left : 0.0;
-          }
-        }
-      }
-      continue;
-    }
-
-    // ---- 3. state == ST_DONE: inverse-CDF draw --------------------------------------------------
-    const double u = (double)s_u1[cur];
-    const double thr = u * total;
-    if (tid == 0) s_pick = 0x7fffffff;
-    __syncthreads();
-    {
-      double run = excl;
-      int found = 0x7fffffff;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = tid * 4 + i;
-        run += mine[i];
-        if (g < ngroups && found == 0x7fffffff && run > thr) found = g;
-      }
-      if (found != 0x7fffffff) atomicMin(&s_pick, found);
-    }
-    __syncthreads();
-    const int pick = s_pick;
-    if (!writer) return;  // no barrier between workgroups follows
-    if (pick != 0x7fffffff && pick / 4 == tid) {
-      double run = excl;
-      for (int i = 0; i < pick % 4; ++i) run += mine[i];
-      s_pick_prefix = run;
-    }
-    __syncthreads();
-    if (wv == 0) {
-      int token = s_lastpos;  // rounding left no crossing: the largest token with positive weight
-      if (pick != 0x7fffffff) {
-        const bool have = s_have_gsum;
-        const int nres = s_nres;
-        const int v0 = pick * kGroup + lane * 4;
-        double x[4];
-        if (wor) lane_weights_wor(lane_load(lrow, qrow, v0, V, vec_ok), v0, V, lse, inv_t, nres, x, s_invZ, have, ql);
-        else lane_weights(lane_load(lrow, qrow, v0, V, vec_ok), v0, V, lse, inv_t, nres, x, s_invZ, have);
-        const double lane_tot = (x[0] + x[1]) + (x[2] + x[3]);
-        const double lane_incl = wave_incl_scan(lane_tot, lane) + s_pick_prefix;
-        const unsigned long long hit = __ballot(lane_incl > thr);
-        const unsigned long long pos = __ballot(lane_tot > 0.0);
-        if (hit) {
-          const int hl = __ffsll((long long)hit) - 1;  // first lane whose running sum crosses
-          const double r0 = __shfl(lane_incl - lane_tot, hl, kWave);
-          const double y0 = __shfl(x[0], hl, kWave), y1 = __shfl(x[1], hl, kWave), y2 = __shfl(x[2], hl, kWave);
-          int e_hit = 3;
-          if (r0 + y0 > thr) e_hit = 0;
-          else if (r0 + y0 + y1 > thr) e_hit = 1;
-          else if (r0 + y0 + y1 + y2 > thr) e_hit = 2;
-          const int cand = pick * kGroup + hl * 4 + e_hit;
-          if (cand < V) token = cand;
-        } else if (pos) {
-          const int pl = 63 - __clzll((long long)pos);
-          int e_last = 0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (__shfl(x[e], pl, kWave) > 0.0) e_last = e;
-          token = pick * kGroup + pl * 4 + e_last;
-        }
-      }
-      if (lane == 0) {
-        P.next_token[b] = token;
-        P.accept_len[b] = s_depth;
-      }
-    }
-    return;
+    if (found != 0x7fffffff) atomicMin(&s_pick, found);
   }
+  __syncthreads();
+  const int pick = s_pick;
+  if (pick == found && found != 0x7fffffff) s_pick_prefix = before;
+  __syncthreads();
+  if (wv != 0) return;
+  int token = s_lastpos;  // rounding left no crossing: the slice's largest token with positive weight
+  if (pick != 0x7fffffff) {
+    const float* lrow = P.logits + (row0 + cur) * V;
+    const int v0 = (lo + pick) * kGroup + lane * 4;
+    double x[4];
+    weights(lane_load(lrow, q_row(P, row0 + cur), v0, V, vec_ok), v0, nres, skip_last, x);
+    const double lane_tot = (x[0] + x[1]) + (x[2] + x[3]);
+    const double lane_incl = wave_incl_scan(lane_tot, lane) + s_pick_prefix;
+    const unsigned long long hit = __ballot(lane_incl > thr);
+    const unsigned long long pos = __ballot(lane_tot > 0.0);
+    if (hit) {
+      const int hl = __ffsll((long long)hit) - 1;  // first lane whose running sum crosses
+      const double r0 = __shfl(lane_incl - lane_tot, hl, kWave);
+      const double y0 = __shfl(x[0], hl, kWave), y1 = __shfl(x[1], hl, kWave), y2 = __shfl(x[2], hl, kWave);
+      int e_hit = 3;
+      if (r0 + y0 > thr) e_hit = 0;
+      else if (r0 + y0 + y1 > thr) e_hit = 1;
+      else if (r0 + y0 + y1 + y2 > thr) e_hit = 2;
+      const int cand = (lo + pick) * kGroup + hl * 4 + e_hit;
+      if (cand < V) token = cand;
+    } else if (pos) {
+      const int pl = 63 - __clzll((long long)pos);
+      int e_last = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (__shfl(x[e], pl, kWave) > 0.0) e_last = e;
+      token = (lo + pick) * kGroup + pl * 4 + e_last;
+    }
+  }
+  if (lane == 0) P.next_token[b] = token;
 }
 
 void accept_chain_geometry(int batch, int vocab, int* slices, int* gmul, int* ngroups) {
@@ -867,23 +916,25 @@ void accept_chain_geometry(int batch, int vocab, int* slices, int* gmul, int* ng
   *ngroups = ng;
 }
 
-// polls before a workgroup of a split tree walk gives up waiting for the others (host-side setting, see the header)
+// polls before a workgroup of a split tree walk stops waiting for the others (host-side setting, see the header)
 static int g_tree_spin_limit = kSpinLimit;
 void set_tree_spin_limit(int polls) { g_tree_spin_limit = polls < 0 ? kSpinLimit : polls; }
 
-__global__ void zero_i32_kernel(int32_t* p, int n) {
+__global__ void fill_not_yet_kernel(unsigned long long* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+  if (i < n) p[i] = kNotYet;
 }
 
 int accept_tree_max_slices() { return kTreeMaxSlices; }
 
 // Workgroups per request for a sampling tree walk: as many as leave every workgroup at least 16 groups
-// to sweep, at most kTreeMaxSlices, and S * B within the number of compute units (all of them resident
-// at once); 1 when that leaves fewer than two.
-static int tree_slices_for(int B, int ngroups, int cus) {
+// to sweep, at most kTreeMaxSlices, S * B within the number of compute units (all of them resident
+// at once), and one sum per slice and sweep (at most Nq sweeps) within the exchange buffer, 2 ngroups
+// doubles per request; 1 when that leaves fewer than two.
+static int tree_slices_for(int B, int Nq, int ngroups, int cus) {
   int s = ngroups / 16;
   if (s > kTreeMaxSlices) s = kTreeMaxSlices;
+  if (s > 2 * ngroups / Nq) s = 2 * ngroups / Nq;
   if (B > 0 && s > cus / B) s = cus / B;
   return s >= 2 ? s : 1;
 }
@@ -898,7 +949,7 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
   P.p_at_draft = a.p_at_draft; P.row_lse = a.row_lse;
   P.slices = a.plan.slices; P.gmul = a.plan.gmul; P.ngroups = a.plan.ngroups;
   P.st_lse = a.st_lse; P.st_row = a.st_row; P.st_rej = a.st_rej; P.gsum = a.gsum; P.lastpos = a.lastpos;
-  P.tree_bar = a.tree_bar;
+  P.exch = (unsigned long long*)a.gsum;
   P.temps = a.temps;
   P.wor = a.wor;
   P.spin_limit = g_tree_spin_limit;
@@ -911,14 +962,21 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
     if (sampling) {
       int cus = 0;
       if (hipError_t e = device_cu_count(&cus); e != hipSuccess) return e;
-      S = tree_slices_for(a.B, ngroups, cus);
+      S = tree_slices_for(a.B, a.Nq, ngroups, cus);
     }
     if (S > 1) {
-      hipLaunchKernelGGL(zero_i32_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a.tree_bar, a.B);
+      const int words = a.B * a.Nq * S;
+      hipLaunchKernelGGL(fill_not_yet_kernel, dim3((words + 255) / 256), dim3(256), 0, st, P.exch, words);
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    P.tree_slices = S;
-    hipLaunchKernelGGL(accept_tree_kernel, dim3(S, a.B), dim3(kAccThreads), 0, st, P);
+    const bool held = (ngroups + S - 1) / S <= kHold * kAccWaves;
+#define AURORA_TREE(HELD, WOR) hipLaunchKernelGGL((accept_tree_kernel<HELD, WOR>), dim3(S, a.B), dim3(kAccThreads), 0, st, P)
+    if (held) {
+      if (P.wor) AURORA_TREE(true, true); else AURORA_TREE(true, false);
+    } else {
+      if (P.wor) AURORA_TREE(false, true); else AURORA_TREE(false, false);
+    }
+#undef AURORA_TREE
     return hipGetLastError();
   }
   hipLaunchKernelGGL(accept_chain_sweep, dim3(P.slices, a.B), dim3(kSweepThreads), 0, st, P);

@@ -87,7 +87,7 @@ struct AcceptPlan {
   int ngroups;      // chain draw: ceil(V / (64 * gmul))
   int n_half;       // group maxima per row kept for the top-K emission (0: the LM-head kernel in use writes none)
   size_t hmax_off;
-  size_t logits_off, pmax_off, psum_off, parg_off, st_lse_off, st_row_off, st_rej_off, gsum_off, lastpos_off, tree_bar_off, bytes;
+  size_t logits_off, pmax_off, psum_off, parg_off, st_lse_off, st_row_off, st_rej_off, gsum_off, lastpos_off, bytes;
 };
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }

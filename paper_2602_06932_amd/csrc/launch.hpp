@@ -40,7 +40,6 @@ struct AcceptLaunch {
   float* hmax;  // [rows, n_tiles * kLmHalfPerTile] maxima of groups of 32 vocabulary entries (matrix-core LM head only)
   double *st_lse, *gsum;
   int32_t *st_row, *st_rej, *lastpos;
-  int32_t* tree_bar;  // [B] arrival counters of the several-workgroups-per-request tree walk
   AcceptPlan plan;
 };
 
