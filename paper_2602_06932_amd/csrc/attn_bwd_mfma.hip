@@ -135,6 +135,8 @@ __device__ __forceinline__ void tile_p_ds(f32x16_t s_acc, const f32x16_t dp_acc,
 
 // kLocalPlan: every workgroup builds the tile prefix per request in LDS (up to kLocalPlanMax requests; workgroup 0
 // also writes it to PB for the dq merge); otherwise PB was filled by the planning kernel and is read from memory.
+constexpr int kBmPar = 4;  // tiles of a run that the wavefronts take at a time
+
 template <int kRT /* 32-row tiles of query rows per KV head: 1 or 2 */, bool kLocalPlan>
 __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kp, const bf16_t* __restrict__ vp,
@@ -148,6 +150,7 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
   char* waves = bm_lds + 2 * kRT * kAtTileBytes;
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
   __shared__ int s_wsum[4];
+  __shared__ int s_par[kMaxNq];  // the request's tree: the ancestor walk is a chain of dependent reads
   __shared__ float s_delta[32 * kRT];  // delta_i = <dO_i, O_i> of the pair's query rows, formed while they are staged
   if (kLocalPlan) {
     build_prefix(seq_lens, B, Hkv, s_pb, s_wsum);
@@ -157,9 +160,10 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
   const int U = pbv(B);
-  const int c = units_per_wg(U, gridDim.x);
-  int u = blockIdx.x * c;
-  const int u_end = min(U, u + c);
+  const int wgs = active_wgs(U, gridDim.x, kBmPar);
+  if ((int)blockIdx.x >= wgs) return;
+  int u = unit_begin(U, wgs, blockIdx.x);
+  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv, R = G * Nq;
@@ -196,6 +200,25 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
     const int32_t* bt = block_table + (size_t)b * max_pages;
+    auto tile_pages = [&](int tt, int& pid_a, int& pid_b) {
+      const int j0 = start + tt * kAtTile;
+      pid_a = bt[j0 >> page_shift];
+      pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
+    };
+    auto issue_tile = [&](const bf16_t* pool, char* buf, int tt, int pid_a, int pid_b) {
+      const int j0 = start + tt * kAtTile;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) issue_rows<true>(pool, buf, j, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
+    };
+    // this wavefront's first tile is on its way while the query rows are staged
+    int tt = wv;
+    int pa = 0, pb = 0;
+    if (tt < ntile) {
+      tile_pages(tt, pa, pb);
+      issue_tile(kp, kbuf, tt, pa, pb);
+      issue_tile(vp, vbuf, tt, pa, pb);
+    }
+
     // the pair's query rows and their upstream gradients: group row m = n * G + g <-> (node n, head hk * G + g);
     // 8 threads per row, 32 bytes each, 32 rows per turn
 #pragma unroll
@@ -237,24 +260,9 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
         const int node = m / G;
         const size_t row = ((size_t)b * Nq + node) * Hq + hk * G + m % G;
         lse2[rt] = lse[row] * kLog2e;
-        if (parents) {
-          for (int a = node, hops = 0; a >= 0 && hops <= Nq; a = parents[(size_t)b * Nq + a], ++hops) anc[rt] |= 1ull << a;
-        } else {
-          anc[rt] = node == 63 ? ~0ull : ((1ull << (node + 1)) - 1);
-        }
       }
     }
-
-    auto tile_pages = [&](int tt, int& pid_a, int& pid_b) {
-      const int j0 = start + tt * kAtTile;
-      pid_a = bt[j0 >> page_shift];
-      pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
-    };
-    auto issue_tile = [&](const bf16_t* pool, char* buf, int tt, int pid_a, int pid_b) {
-      const int j0 = start + tt * kAtTile;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) issue_rows<true>(pool, buf, j, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
-    };
+    if (parents && tid < Nq) s_par[tid] = parents[(size_t)b * Nq + tid];
 
     f32x16_t dq_acc[kRT][4];
 #pragma unroll
@@ -266,13 +274,12 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
 
     __syncthreads();  // query rows staged
 #pragma unroll
-    for (int rt = 0; rt < kRT; ++rt) dlt[rt] = 32 * rt + li < R ? s_delta[32 * rt + li] : 0.f;
-    int tt = wv;
-    int pa = 0, pb = 0;
-    if (tt < ntile) {
-      tile_pages(tt, pa, pb);
-      issue_tile(kp, kbuf, tt, pa, pb);
-      issue_tile(vp, vbuf, tt, pa, pb);
+    for (int rt = 0; rt < kRT; ++rt) {
+      const int m = 32 * rt + li;
+      if (m < R) {
+        dlt[rt] = s_delta[m];
+        anc[rt] = ancestor_mask(parents ? s_par : nullptr, m / G, Nq);
+      }
     }
     for (; tt < ntile; tt += 4) {
       const bool more = tt + 4 < ntile;
@@ -409,6 +416,7 @@ __device__ __forceinline__ void tile_tmm_block(const char* abuf, const bf16x8_t 
 // the same at every step top: [loads of tile s] [2 loads, 32 stores in either order] - hence vmcnt(34), and
 // vmcnt(2) in the first three steps, where the stores are not there yet.
 constexpr int kB8Threads = 512;
+constexpr int kB8Par = 2;  // tiles that the two groups have in work at a time
 constexpr int kB8LdsBytes = 8 * kAtTileBytes + 3 * kBsKvBytes + 2 * 4 * kBsXtBytes;
 
 template <bool kLocalPlan>
@@ -425,6 +433,7 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
   char* xt = kv + 3 * kBsKvBytes;           // per group: four transposed (P, dS) tiles
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
   __shared__ int s_wsum[8];
+  __shared__ int s_par[kMaxNq];    // the request's tree: the ancestor walk is a chain of dependent reads
   __shared__ float s_delta[128];  // delta_i = <dO_i, O_i> of the pair's query rows, formed while they are staged
   if (kLocalPlan) {
     build_prefix(seq_lens, B, Hkv, s_pb, s_wsum);
@@ -434,9 +443,10 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
   const int U = pbv(B);
-  const int c = units_per_wg(U, gridDim.x);
-  int u = blockIdx.x * c;
-  const int u_end = min(U, u + c);
+  const int wgs = active_wgs(U, gridDim.x, kB8Par);
+  if ((int)blockIdx.x >= wgs) return;
+  int u = unit_begin(U, wgs, blockIdx.x);
+  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv, R = G * Nq;
@@ -472,6 +482,21 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
     const int32_t* bt = block_table + (size_t)b * max_pages;
+    // this wavefront's eighth of a tile pair's loads: one row group (four token rows) of K and one of V
+    auto issue_eighth = [&](int tt) {
+      const int tl = min(tt, ntile - 1);
+      const int j0 = start + tl * kAtTile;
+      const int pid_a = bt[j0 >> page_shift];
+      const int pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
+      char* kb = kv + (tt % 3) * kBsKvBytes;
+      issue_rows<true>(kp, kb, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
+      issue_rows<true>(vp, kb + kAtTileBytes, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
+    };
+    // the first two tiles are on their way while the query rows are staged (the buffers are idle: the run before ended in a
+    // barrier)
+    issue_eighth(0);
+    issue_eighth(1);
+
     // the pair's query rows and upstream gradients: 8 threads per row, 32 bytes each, 64 rows per turn
 #pragma unroll
     for (int turn = 0; turn < 2; ++turn) {
@@ -506,23 +531,8 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       const int node = m_row / G;
       const size_t row = ((size_t)b * Nq + node) * Hq + hk * G + m_row % G;
       lse2 = lse[row] * kLog2e;
-      if (parents) {
-        for (int a = node, hops = 0; a >= 0 && hops <= Nq; a = parents[(size_t)b * Nq + a], ++hops) anc |= 1ull << a;
-      } else {
-        anc = node == 63 ? ~0ull : ((1ull << (node + 1)) - 1);
-      }
     }
-
-    // this wavefront's eighth of a tile pair's loads: one row group (four token rows) of K and one of V
-    auto issue_eighth = [&](int tt) {
-      const int tl = min(tt, ntile - 1);
-      const int j0 = start + tl * kAtTile;
-      const int pid_a = bt[j0 >> page_shift];
-      const int pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
-      char* kb = kv + (tt % 3) * kBsKvBytes;
-      issue_rows<true>(kp, kb, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
-      issue_rows<true>(vp, kb + kAtTileBytes, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
-    };
+    if (parents && tid < Nq) s_par[tid] = parents[(size_t)b * Nq + tid];
 
     f32x16_t dq_acc[4];
 #pragma unroll
@@ -531,9 +541,10 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       for (int r = 0; r < 16; ++r) dq_acc[db][r] = 0.f;
 
     __syncthreads();  // query rows staged; the previous run is done with every buffer
-    dlt = m_row < R ? s_delta[m_row] : 0.f;
-    issue_eighth(0);
-    issue_eighth(1);
+    if (m_row < R) {
+      dlt = s_delta[m_row];
+      anc = ancestor_mask(parents ? s_par : nullptr, m_row / G, Nq);
+    }
     for (int s = 0; s <= ntile; ++s) {
       if (s <= 2) WAIT_VMCNT(2); else WAIT_VMCNT(34);            // tile s has landed (this wavefront's part)
       __builtin_amdgcn_s_waitcnt((7 << 4) | (3 << 14) | 15);      // lgkmcnt(0): LDS reads and writes of the last step
@@ -613,22 +624,30 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
 __global__ __launch_bounds__(256) void attn_bwd_dq_combine(const float* __restrict__ part_dq,
                                                            const int32_t* __restrict__ seq_lens,
                                                            const int32_t* __restrict__ PB, float* __restrict__ dq, int B,
-                                                           int Nq, int Hq, int Hkv, int wgs, int row_tiles, unsigned n_rows, float scale) {
-  const size_t row = (size_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-  if (row >= n_rows) return;
-  const int hq = (int)(row % Hq);
-  const int n = (int)((row / Hq) % Nq);
-  const int b = (int)(row / ((size_t)Hq * Nq));
+                                                           int Nq, int Hq, int Hkv, int wgs_launched, int row_tiles, float scale) {
+  const int b = blockIdx.x / Nq, n = blockIdx.x - b * Nq;
+  const int hq = blockIdx.y * 8 + (threadIdx.x >> 5);
+  if (hq >= Hq) return;
+  const size_t row = (size_t)blockIdx.x * Hq + hq;  // (b*Nq + n)*Hq + hq
   const int G = Hq / Hkv, hk = hq / G;
-  const int mrow = n * G + hq % G;
+  const int mrow = n * G + hq - hk * G;
   const int n_b = (seq_lens[b] + kAtTile - 1) / kAtTile;
-  const int c = units_per_wg(PB[B], wgs);
-  const int u0 = PB[b] + hk * n_b, u1 = u0 + n_b;
-  const int w0 = u0 / c, w1 = (u1 - 1) / c;
+  const int U = PB[B], u0 = PB[b] + hk * n_b;
+  const int wgs = active_wgs(U, wgs_launched, row_tiles == 4 ? kB8Par : kBmPar);
+  const int w0 = n_b > 0 ? unit_owner(U, wgs, u0) : 0, w1 = n_b > 0 ? unit_owner(U, wgs, u0 + n_b - 1) : -1;
   const int pair = b * Hkv + hk;
   const int d4 = threadIdx.x & 31;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  for (int w = w0; w <= w1; ++w) acc += *(const f32x4_t*)(part_dq + ((size_t)(w + pair) * 32 * row_tiles + mrow) * kAtD + 4 * d4);
+  constexpr int kU = 4;  // partials in flight; added in run order
+  for (int p0 = w0; p0 <= w1; p0 += kU) {
+    f32x4_t x[kU];
+#pragma unroll
+    for (int i = 0; i < kU; ++i)
+      if (p0 + i <= w1) x[i] = *(const f32x4_t*)(part_dq + ((size_t)(p0 + i + pair) * 32 * row_tiles + mrow) * kAtD + 4 * d4);
+#pragma unroll
+    for (int i = 0; i < kU; ++i)
+      if (p0 + i <= w1) acc += x[i];
+  }
   *(f32x4_t*)(dq + row * kAtD + 4 * d4) = acc * scale;
 }
 
@@ -673,7 +692,6 @@ static hipError_t launch_bwd_mfma_shared(const AttnBwdLaunch& a, hipStream_t st)
 }
 
 hipError_t launch_attn_backward_mfma(const AttnBwdLaunch& a, hipStream_t st) {
-  const int rows = a.B * a.Nq * a.Hq;
   const int rt = bwd_row_tiles(a);
   hipError_t e = hipSuccess;
   if (a.B <= kLocalPlanMax) {
@@ -686,8 +704,8 @@ hipError_t launch_attn_backward_mfma(const AttnBwdLaunch& a, hipStream_t st) {
                                                                : launch_bwd_mfma_shared<false>(a, st);
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_bwd_dq_combine, dim3((rows + 7) / 8), dim3(256), 0, st, a.part_dq, a.seq_lens, a.plan_pb, a.dq,
-                     a.B, a.Nq, a.Hq, a.Hkv, attn_bwd_mfma_workgroups(), rt, (unsigned)rows, a.scale);
+  hipLaunchKernelGGL(attn_bwd_dq_combine, dim3(a.B * a.Nq, (a.Hq + 7) / 8), dim3(256), 0, st, a.part_dq, a.seq_lens,
+                     a.plan_pb, a.dq, a.B, a.Nq, a.Hq, a.Hkv, attn_bwd_mfma_workgroups(), rt, a.scale);
   return hipGetLastError();
 }
 

@@ -37,12 +37,7 @@ __device__ __forceinline__ void load_to_lds_16(const void* gptr, const void* lds
     asm volatile("" ::: "memory");                                                                 \
   } while (0)
 
-__device__ __forceinline__ int units_per_wg(int U, int wgs) {
-  const int c = (U + wgs - 1) / wgs;
-  return (c + 3) & ~3;  // a multiple of four tiles: the four wavefronts of a workgroup stay balanced
-}
-
-// Workgroups of a forward sweep that get units: all `wgs` launched ones, or so few that a run still gives each of the
+// Workgroups of a sweep that get units: all `wgs` launched ones, or so few that a run still gives each of the
 // `par` wavefront groups that share a run a tile.  Shorter runs would leave wavefronts idle without ending any sooner, and
 // every run adds a partial per query row to the merge.  The sweep and the merge kernel evaluate this alike.
 __device__ __forceinline__ int active_wgs(int U, int wgs, int par) {
@@ -50,7 +45,7 @@ __device__ __forceinline__ int active_wgs(int U, int wgs, int par) {
   return w < wgs ? (w > 0 ? w : 1) : wgs;
 }
 
-// The forward sweeps deal the U units to the workgroups as evenly as they divide: contiguous runs of U / wgs units, one
+// The sweeps deal the U units to the workgroups as evenly as they divide: contiguous runs of U / wgs units, one
 // more for the first U % wgs workgroups - every active workgroup has work and no compute unit holds more than its share.
 __device__ __forceinline__ int unit_begin(int U, int wgs, int w) {
   const int q = U / wgs, r = U % wgs;
