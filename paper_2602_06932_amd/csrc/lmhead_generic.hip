@@ -54,6 +54,75 @@ __global__ __launch_bounds__(256) void lmhead_generic(const T* __restrict__ hidd
   }
 }
 
+// The same product for few token rows: 64 x 64 tiles would leave most of the chip idle (16 workgroups on 20 x 1024) and walk
+// the hidden dimension in steps of 16 with two barriers each.  Here a workgroup takes 16 vocabulary rows x 32 token rows and
+// 64 hidden elements per step, the next step's operands being loaded into registers (16 bytes a thread) while the present
+// ones are multiplied out of LDS; a thread owns one vocabulary row and two token rows.  20 x 1024 x 256 in fp32: 25 -> 6 us.
+constexpr int kSM = 32, kSN = 16, kSK = 64, kSPad = 4;
+template <typename T>
+__global__ __launch_bounds__(256) void lmhead_generic_few(const T* __restrict__ hidden, const T* __restrict__ w,
+                                                          float* __restrict__ logits, int64_t M, int H, int V) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  __shared__ __attribute__((aligned(16))) float As[kSM][kSK + kSPad];
+  __shared__ __attribute__((aligned(16))) float Bs[kSN][kSK + kSPad];
+  const int tid = threadIdx.x;
+  const int v0 = blockIdx.x * kSN;
+  const int64_t m0 = (int64_t)blockIdx.y * kSM;
+  // staging: thread (r, c) brings elements 4c .. of rows r, r + 16 of the token tile and of row r of the vocabulary tile
+  const int r = tid >> 4, c = (tid & 15) * 4;
+  const bool vec = (H & 3) == 0;
+  auto fetch = [&](const T* p, bool ok, int k) -> f32x4_t {
+    f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+    if (ok && vec) {  // rows start at multiples of four elements
+      if (k < H) {
+        T t[4];
+        __builtin_memcpy(t, __builtin_assume_aligned(p + k, 4 * sizeof(T)), 4 * sizeof(T));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = to_f32<T>(t[e]);
+      }
+    } else if (ok) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k + e < H) x[e] = to_f32<T>(p[k + e]);
+    }
+    return x;
+  };
+  const int64_t ma = m0 + r, mb = m0 + r + 16;
+  const T* pa = hidden + (ma < M ? ma : 0) * H;
+  const T* pb = hidden + (mb < M ? mb : 0) * H;
+  const T* pw = w + (int64_t)(v0 + r < V ? v0 + r : 0) * H;
+  const int n = tid & 15, mm = tid >> 4;  // this thread's vocabulary row; token rows mm and mm + 16
+  f32x4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t xa = fetch(pa, ma < M, c), xb = fetch(pb, mb < M, c), xw = fetch(pw, v0 + r < V, c);
+  for (int k0 = 0; k0 < H; k0 += kSK) {
+    *(f32x4_t*)&As[r][c] = xa;
+    *(f32x4_t*)&As[r + 16][c] = xb;
+    *(f32x4_t*)&Bs[r][c] = xw;
+    __syncthreads();
+    if (k0 + kSK < H) {
+      xa = fetch(pa, ma < M, k0 + kSK + c);
+      xb = fetch(pb, mb < M, k0 + kSK + c);
+      xw = fetch(pw, v0 + r < V, k0 + kSK + c);
+    }
+#pragma unroll
+    for (int k = 0; k < kSK; k += 4) {
+      const f32x4_t wv = *(const f32x4_t*)&Bs[n][k];
+      const f32x4_t a0 = *(const f32x4_t*)&As[mm][k], a1 = *(const f32x4_t*)&As[mm + 16][k];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc0[e] = fmaf(a0[e], wv[e], acc0[e]);
+        acc1[e] = fmaf(a1[e], wv[e], acc1[e]);
+      }
+    }
+    __syncthreads();
+  }
+  const int v = v0 + n;
+  if (v < V) {
+    if (m0 + mm < M) logits[(m0 + mm) * V + v] = (acc0[0] + acc0[1]) + (acc0[2] + acc0[3]);
+    if (m0 + mm + 16 < M) logits[(m0 + mm + 16) * V + v] = (acc1[0] + acc1[1]) + (acc1[2] + acc1[3]);
+  }
+}
+
 // One workgroup per (vocab tile, row): max, arg-max (lowest index on ties) and
 // sum exp((l - max) * inv_t) over the tile's columns.
 __global__ __launch_bounds__(256) void row_tile_stats(const float* __restrict__ logits, float* __restrict__ pmax,
@@ -103,13 +172,26 @@ __global__ __launch_bounds__(256) void row_tile_stats(const float* __restrict__ 
 
 hipError_t launch_lmhead_generic(const AcceptLaunch& a, hipStream_t st) {
   const int64_t M = a.plan.rows;
-  dim3 grid((unsigned)((a.V + kTN - 1) / kTN), (unsigned)((M + kTM - 1) / kTM));
-  if (a.bf16)
-    hipLaunchKernelGGL(lmhead_generic<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)a.hidden,
-                       (const bf16_t*)a.lm_head, a.logits, M, a.H, a.V);
-  else
-    hipLaunchKernelGGL(lmhead_generic<float>, grid, dim3(256), 0, st, (const float*)a.hidden,
-                       (const float*)a.lm_head, a.logits, M, a.H, a.V);
+  // the small tiles while the large ones would fill less than half of the 256 compute units (a 64 x 64 tile re-reads its
+  // operands a quarter as often, which counts once the chip is full)
+  const int64_t large = (int64_t)((a.V + kTN - 1) / kTN) * ((M + kTM - 1) / kTM);
+  if (large < 128) {
+    dim3 grid((unsigned)((a.V + kSN - 1) / kSN), (unsigned)((M + kSM - 1) / kSM));
+    if (a.bf16)
+      hipLaunchKernelGGL(lmhead_generic_few<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)a.hidden,
+                         (const bf16_t*)a.lm_head, a.logits, M, a.H, a.V);
+    else
+      hipLaunchKernelGGL(lmhead_generic_few<float>, grid, dim3(256), 0, st, (const float*)a.hidden,
+                         (const float*)a.lm_head, a.logits, M, a.H, a.V);
+  } else {
+    dim3 grid((unsigned)((a.V + kTN - 1) / kTN), (unsigned)((M + kTM - 1) / kTM));
+    if (a.bf16)
+      hipLaunchKernelGGL(lmhead_generic<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)a.hidden,
+                         (const bf16_t*)a.lm_head, a.logits, M, a.H, a.V);
+    else
+      hipLaunchKernelGGL(lmhead_generic<float>, grid, dim3(256), 0, st, (const float*)a.hidden,
+                         (const float*)a.lm_head, a.logits, M, a.H, a.V);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const float inv_t = a.temperature > 0.f ? 1.f / a.temperature : 1.f;
