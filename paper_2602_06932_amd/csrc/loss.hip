@@ -8,7 +8,8 @@
 // the drafter's logits over its whole vocabulary.  Row classes are the trajectory codes of the trace
 // record (appendix A.1): 1 accepted, 2 discarded, 0 unused.
 //
-// Three small kernels: class counts, one workgroup per row, and a fixed-order fp64 reduction of the row values.
+// One workgroup per row and a fixed-order fp64 reduction of the row values; many rows have their classes counted by a
+// kernel of its own first, of few every row's workgroup counts them by itself.
 #include "launch.hpp"
 
 namespace aurora {
@@ -59,40 +60,84 @@ __global__ __launch_bounds__(kLossThreads) void loss_count_kernel(const int8_t* 
   }
 }
 
-// One workgroup of four wavefronts per row.  kInRegs: the row is 16-byte aligned and at most kRowRegVals values
-// long, so every thread keeps its share (up to 32 x 4 values) in registers: the row is read once, each exponential
-// is taken once, and the gradient is that exponential times w / sum.  Four-wavefront workgroups at this register
-// count put three rows on a compute unit at a time, so one row's loads and stores overlap another's reductions.
-// Otherwise three passes over the row (the second and third hit L2).
-constexpr int kRowThreads = 256;
+// One workgroup of eight wavefronts per row.  kInRegs: a row of at most kRowRegVals values stays in registers (up to 16 x 4
+// per thread): it is read once, each exponential is taken once, and the gradient is that exponential times w / sum.  At 128
+// registers a thread two rows share a compute unit, so one row's loads and stores overlap another's reductions.
+// A row need not start at 16 bytes: the vectors start at its first aligned element, and the up to three elements before and
+// after them are held by six threads.
+// The kernel is bound by the row's bytes in and out, so every line of the gradient is written once and whole: w p_target is
+// laid out in LDS, half a row at a time (the ids are distinct, a plain scatter; the first half early, behind the row's
+// loads), and subtracted before the store.  Rewriting the kept tokens' entries in global memory afterwards found their lines
+// partly evicted - 64 rows are in flight per 4 MB L2 - and cost 4 M partial writes.  4096 rows x 32000, 1024 kept: 245 ->
+// 228 us, 4.7 TB/s (64 kept: 209 -> 212); 900 rows x 16001, which took three passes for want of alignment: 90 -> 47 us.
+// Otherwise (longer rows, draft_logits and grad aligned differently) three passes over the row, the second and third from L2.
+constexpr int kRowThreads = 512;
 constexpr int kRowWaves = kRowThreads / kWave;
-constexpr int kRowRounds = 32;
+constexpr int kRowRounds = 16;
 constexpr int kRowRegVals = kRowThreads * 4 * kRowRounds;  // 32768
 constexpr int kRowKept = 1024 / kRowThreads;               // kept target logits per thread
+constexpr int kScatRounds = 8;                             // rounds per turn of the scatter
+constexpr int kScatVals = kScatRounds * kRowThreads * 4;   // 16384 floats, 64 KB of LDS: two workgroups a unit
+constexpr int kCountRows = 8192;  // up to here a row's workgroup counts the classes itself (a few KB from L2, behind the row's loads)
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
+// whether the rows' workgroups count the classes themselves (their sums are the same whoever forms them)
+__host__ __device__ inline bool counts_classes(const LossLaunch& P) {
+  return P.grad && P.M <= kCountRows && ((uintptr_t)P.traj & 3) == 0;
+}
+
 template <bool kInRegs>
-__global__ __launch_bounds__(kRowThreads) void loss_rows_kernel(LossLaunch P) {
+__global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel(LossLaunch P) {
   __shared__ float s_redf[kRowWaves];
   __shared__ double s_redd[kRowWaves];
   const int m = blockIdx.x, tid = threadIdx.x;
   const int Vd = P.Vd, K = P.K;
   const float* z = P.draft_logits + (size_t)m * Vd;
-  const int n4 = Vd / 4;
+  // elements before the first 16-byte boundary, vectors, and the first element after them (in registers only)
+  const int h = kInRegs ? min((int)(((16 - ((uintptr_t)z & 15)) & 15) >> 2), Vd) : 0;
+  const int n4 = (Vd - h) / 4, tail = h + 4 * n4;
 
   // the row first: its loads are in flight while the target side is worked out
   f32x4_t r[kInRegs ? kRowRounds : 1];
+  int edge = -1;  // the element outside the vectors that this thread holds
+  float r_edge = -INFINITY;
   if constexpr (kInRegs) {
 #pragma unroll
     for (int j = 0; j < kRowRounds; ++j) {
       const int i = tid + j * kRowThreads;
-      const f32x4_t ninf = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-      r[j] = i < n4 ? *((const f32x4_t*)z + i) : ninf;
+      r[j] = *((const f32x4_t*)(z + h) + min(i, n4 - 1));  // (past the end: re-read, and masked below)
     }
+    if (tid < 3 && tid < h) edge = tid;
+    if (tid >= 4 && tid < 7 && tail + tid - 4 < Vd) edge = tail + tid - 4;
+    if (edge >= 0) r_edge = z[edge];
   }
   const int cls = P.traj[m];
+  // rows of the two classes, counted here if they are few: four codes a load, in flight behind the row's own
+  int na = 0, nd = 0;
+  const bool count = counts_classes(P);
+  if (count) {
+    uint32_t c4[kCountRows / 4 / kRowThreads];
+#pragma unroll
+    for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e) {
+      const int i = tid + e * kRowThreads;
+      c4[e] = 0u;
+      if (4 * i + 3 < P.M) {
+        c4[e] = ((const uint32_t*)P.traj)[i];
+      } else {
+        for (int k = 4 * i; k < P.M; ++k) c4[e] |= (uint32_t)(uint8_t)P.traj[k] << (8 * (k & 3));
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int c = (int8_t)(c4[e] >> (8 * k));
+        na += c == 1;
+        nd += c == 2;
+      }
+  }
 
-  // ---- the row's target distribution: thread t holds kept entries t, t + 256, ... ------------------------
+  // ---- the row's target distribution: thread t holds kept entries t, t + 512, ... ------------------------
   const int k_eff = (cls == 2 && P.discard_k > 0) ? min(P.discard_k, K) : K;
   int id[kRowKept];
   float lt[kRowKept], zt_at[kRowKept];
@@ -120,20 +165,72 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_kernel(LossLaunch P) {
   tsum = block_sum<kRowWaves>(tsum, s_redd);
   const double lse_t = (double)tmax + log(tsum);
 
+  float pt[kRowKept];
+#pragma unroll
+  for (int e = 0; e < kRowKept; ++e) pt[e] = kept[e] ? __expf((float)((double)lt[e] - lse_t)) : 0.f;
+
+  // ---- the row's weight, and its share of w p_target laid out in LDS for the first turn of the gradient below ------------
+  float w = 0.f;
+  if (P.grad) {
+    float n_acc, n_disc;
+    if (count) {  // both in one sum of whole numbers
+      const int both = (int)block_sum<kRowWaves>((double)(na + (nd << 14)), s_redd);
+      n_acc = (float)(both & ((1 << 14) - 1));
+      n_disc = (float)(both >> 14);
+    } else {
+      n_acc = P.loss_out[3];
+      n_disc = P.loss_out[4];
+    }
+    if (any && cls == 1) w = 1.f / n_acc;
+    if (any && cls == 2) w = P.lambda / n_disc;
+  }
+  constexpr int kLdsVals = kInRegs ? kScatVals : 4;
+  __shared__ __attribute__((aligned(16))) float s_pt[kLdsVals];
+  __shared__ float s_edge[8];
+  auto scatter = [&](int first) {  // entries first .. of the vectors (distinct ids: a plain scatter)
+#pragma unroll
+    for (int e = 0; e < kRowKept; ++e)
+      if (kept[e] && id[e] >= first && id[e] < min(first + kScatVals, tail)) s_pt[id[e] - first] = w * pt[e];
+  };
+  if constexpr (kInRegs) {
+    if (P.grad) {
+      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < kScatRounds; ++j) *(f32x4_t*)(s_pt + 4 * (tid + j * kRowThreads)) = zero;
+      if (tid < 8) s_edge[tid] = 0.f;
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < kRowKept; ++e)
+        if (kept[e]) {
+          if (id[e] < h) s_edge[id[e]] = w * pt[e];
+          if (id[e] >= tail) s_edge[4 + id[e] - tail] = w * pt[e];
+        }
+      scatter(h);  // the reductions below put barriers between this and its readers
+    }
+  }
+
   // ---- the drafter's logsumexp over its whole vocabulary ---------------------------------------------------
   const bool vec_ok = (Vd & 3) == 0 && ((uintptr_t)P.draft_logits & 15) == 0;
   float zmax = -INFINITY;
   double zsum = 0.0;
   if constexpr (kInRegs) {
+    const f32x4_t ninf = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int j = 0; j < kRowRounds; ++j)
+      if (tid + j * kRowThreads >= n4) r[j] = ninf;
 #pragma unroll
     for (int j = 0; j < kRowRounds; ++j) zmax = fmaxf(zmax, fmaxf(fmaxf(r[j][0], r[j][1]), fmaxf(r[j][2], r[j][3])));
+    zmax = fmaxf(zmax, r_edge);
     zmax = block_max<kRowWaves>(zmax, s_redf);
 #pragma unroll
     for (int j = 0; j < kRowRounds; ++j) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) r[j][e] = __expf(r[j][e] - zmax);  // exp(-inf) = 0 past the end of the row
       zsum += ((double)r[j][0] + (double)r[j][1]) + ((double)r[j][2] + (double)r[j][3]);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    r_edge = edge >= 0 ? __expf(r_edge - zmax) : 0.f;
+    zsum += (double)r_edge;
   } else {
     if (vec_ok) {
       const float4* z4 = (const float4*)z;
@@ -161,31 +258,39 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_kernel(LossLaunch P) {
   const float lse_df = (float)lse_d;
 
   // ---- KL(p_target || p_draft) of the row --------------------------------------------------------------------
-  float pt[kRowKept];
   double term = 0.0;
 #pragma unroll
-  for (int e = 0; e < kRowKept; ++e) {
-    const double logpt = (double)lt[e] - lse_t;
-    pt[e] = kept[e] ? __expf((float)logpt) : 0.f;
-    term += kept[e] ? (double)pt[e] * (logpt - ((double)zt_at[e] - lse_d)) : 0.0;
-  }
+  for (int e = 0; e < kRowKept; ++e)
+    term += kept[e] ? (double)pt[e] * ((double)lt[e] - lse_t - ((double)zt_at[e] - lse_d)) : 0.0;
   const double kl = block_sum<kRowWaves>(term, s_redd);
   if (tid == 0) P.row_kl[m] = any ? (float)kl : 0.f;
 
   // ---- gradient: w (p_draft - p_target) ------------------------------------------------------------------------
   if (!P.grad) return;
-  const float n_acc = P.loss_out[3], n_disc = P.loss_out[4];
-  float w = 0.f;
-  if (any && cls == 1) w = 1.f / n_acc;
-  if (any && cls == 2) w = P.lambda / n_disc;
   float* g = P.grad + (size_t)m * Vd;
   if constexpr (kInRegs) {
     const float scale = w * (float)(1.0 / zsum);
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < kRowRounds; ++j) {
-      const int i = tid + j * kRowThreads;
-      if (i < n4) *((f32x4_t*)g + i) = r[j] * scale;
+    for (int j0 = 0; j0 < kRowRounds; j0 += kScatRounds) {
+      if (j0 * kRowThreads >= n4) break;  // uniform
+      if (j0 > 0) {
+        __syncthreads();  // the turn before has been read and cleared
+        scatter(h + 4 * j0 * kRowThreads);
+        __syncthreads();
+      }
+#pragma unroll
+      for (int j = 0; j < kScatRounds; ++j) {
+        const int i = tid + (j0 + j) * kRowThreads;
+        f32x4_t* at = (f32x4_t*)(s_pt + 4 * (tid + j * kRowThreads));
+        const f32x4_t o = r[j0 + j] * scale - *at;
+        if (j0 + kScatRounds < kRowRounds) *at = zero;  // for the next turn; nobody else reads it
+        if (i < n4) *((f32x4_t*)(g + h) + i) = o;
+        __builtin_amdgcn_sched_barrier(0);  // one round at a time: nothing but r[] may take registers here
+      }
     }
+    if (edge >= 0) g[edge] = r_edge * scale - s_edge[tid];
+    return;
   } else {
     const bool gvec = vec_ok && ((uintptr_t)P.grad & 15) == 0;
     if (gvec) {
@@ -214,17 +319,21 @@ __global__ __launch_bounds__(kLossThreads) void loss_reduce_kernel(const float* 
                                                                     const int8_t* __restrict__ traj, int M, float lambda,
                                                                     float* __restrict__ loss_out) {
   __shared__ double s_red[kLossWaves];
-  double sa = 0.0, sd = 0.0;
+  double sa = 0.0, sd = 0.0, both = 0.0;  // both counts in one sum of whole numbers
+  constexpr double kStep = 4294967296.0;
   for (int m = threadIdx.x; m < M; m += kLossThreads) {
     const int c = traj[m];
     const double x = (double)row_kl[m];
-    if (c == 1) sa += x;
-    if (c == 2) sd += x;
+    if (c == 1) { sa += x; both += 1.0; }
+    if (c == 2) { sd += x; both += kStep; }
   }
   sa = block_sum(sa, s_red);
   sd = block_sum(sd, s_red);
+  both = block_sum(both, s_red);
   if (threadIdx.x == 0) {
-    const double na = loss_out[3], nd = loss_out[4];
+    const double nd = floor(both / kStep), na = both - nd * kStep;
+    loss_out[3] = (float)na;
+    loss_out[4] = (float)nd;
     const double ma = na > 0 ? sa / na : 0.0, md = nd > 0 ? sd / nd : 0.0;
     loss_out[0] = (float)(ma + (double)lambda * md);
     loss_out[1] = (float)ma;
@@ -235,12 +344,15 @@ __global__ __launch_bounds__(kLossThreads) void loss_reduce_kernel(const float* 
 int loss_max_k() { return kRowKept * kRowThreads; }
 
 hipError_t launch_draft_loss(const LossLaunch& P, hipStream_t st) {
-  hipLaunchKernelGGL(loss_count_kernel, dim3(1), dim3(kLossThreads), 0, st, P.traj, P.M, P.loss_out);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e;
+  if (P.grad && !counts_classes(P)) {
+    hipLaunchKernelGGL(loss_count_kernel, dim3(1), dim3(kLossThreads), 0, st, P.traj, P.M, P.loss_out);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   if (P.M > 0) {
-    const bool in_regs = (P.Vd & 3) == 0 && P.Vd <= kRowRegVals && ((uintptr_t)P.draft_logits & 15) == 0 &&
-                         (!P.grad || ((uintptr_t)P.grad & 15) == 0);
+    // rows and gradient rows have to start at the same place within 16 bytes
+    const bool in_regs = P.Vd >= 8 && P.Vd <= kRowRegVals && (!P.grad || (((uintptr_t)P.grad ^ (uintptr_t)P.draft_logits) & 15) == 0);
     if (in_regs)
       hipLaunchKernelGGL(loss_rows_kernel<true>, dim3(P.M), dim3(kRowThreads), 0, st, P);
     else

@@ -1,0 +1,37 @@
+"""Drafter loss where its row kernel can go wrong: rows that do not start at 16 bytes (elements before and after the vectors),
+vocabularies at the edges of the register path, kept tokens on every side of the LDS turns, and class counts formed by the
+rows' workgroups or by a kernel of their own - against the float64 oracle."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,vd,k", [(5, 8, 4), (6, 9, 9), (7, 11, 3), (9, 16385, 1000), (5, 16387, 1024), (4, 32767, 1024),
+                                       (3, 32768, 700), (3, 32769, 64), (8193, 40, 8), (8192, 41, 8), (4099, 33, 33)])
+def test_rows_of_any_alignment_and_length(gpu_lib, rows, vd, k):
+    av = gpu_lib
+    z, ids, bits, traj = gen.loss_inputs(7 + vd, rows, vd, top_k=k)
+    keep = min(k, vd)
+    if vd > 40:  # the first and last entries of the row, and both sides of the turns' edge, among the kept tokens
+        for m in range(rows):
+            want = [v for v in dict.fromkeys((0, 2, 3, vd - 1, vd - 4, 16383, 16384, 16387)) if 0 <= v < vd][:keep]
+            rest = [i for i in ids[m, :keep].tolist() if i not in want]
+            ids[m, :keep] = (want + rest)[:keep]
+    ref = oracle.draft_loss(z, ids, bits, traj, 0.5, None)
+    d = av.aurora_loss_desc(rows=rows, draft_vocab=vd, top_k=k, discard_top_k=0, lambda_discard=0.5)
+    dev = [torch.from_numpy(a).cuda() for a in (z, ids, bits.view(np.int16), traj)]
+    kl, loss = torch.empty(rows, device="cuda"), torch.empty(5, device="cuda")
+    grad = torch.full((rows, vd), float("nan"), device="cuda")
+    av.aurora_draft_loss(d, *dev, kl, loss, grad)
+    torch.cuda.synchronize()
+    w = max(1.0 / max(1, ref["n_accept"]), 0.5 / max(1, ref["n_discard"]))
+    # fp32 exponentials (a few ulp of a probability of at most 1) in both terms, times the row's weight
+    assert np.abs(grad.cpu().numpy() - ref["grad"]).max() <= 4e-6 * w
+    assert (np.abs(kl.cpu().numpy() - ref["row_kl"]) <= 2e-5 + 1e-5 * np.abs(ref["row_kl"])).all()
+    assert loss[3].item() == ref["n_accept"] and loss[4].item() == ref["n_discard"]
+    assert abs(loss[0].item() - ref["loss"]) <= 2e-5 * max(1.0, abs(ref["loss"]))
