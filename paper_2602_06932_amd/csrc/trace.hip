@@ -226,8 +226,17 @@ __global__ __launch_bounds__(kRecWaves * kWave) void trace_records_kernel(RecArg
 // over the whole row say nothing about a subset of it).
 // kOcc: workgroups per compute unit the kernel is built for.  Up to one row per compute unit (kOcc = 1) a thread
 // keeps sixteen 16-byte loads of the row in flight; with more rows than units two workgroups share a unit.
+constexpr int kTrBins = 2048;
+__device__ __forceinline__ int wave_incl_scan(int x, int lane) {
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  return x;
+}
 template <bool kMapped, bool kGroups, int kOcc>
-__global__ __launch_bounds__(kTrThreads, kOcc) void trace_topk_kernel(const float* __restrict__ logits, int Vrow, int V, int K,
+__global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) void trace_topk_kernel(const float* __restrict__ logits, int Vrow, int V, int K,
                                                                const int32_t* __restrict__ map,
                                                                const float* __restrict__ group_max, int n_groups,
                                                                int32_t* __restrict__ out_ids,
@@ -243,10 +252,35 @@ __global__ __launch_bounds__(kTrThreads, kOcc) void trace_topk_kernel(const floa
   }
   uint64_t* s_top = s_buck;             // the whole-row route keeps its K selected words here
   __shared__ SelectShared s_sel;
+  __shared__ int s_hist[kTrBins];
+  __shared__ int s_wave[kTrThreads / kWave];
   __shared__ unsigned s_count;
   __shared__ unsigned s_kmax, s_nkmin, s_big;
-  __shared__ unsigned long long s_scale;
-  const int tid = threadIdx.x;
+  __shared__ int s_bin, s_bin_count, s_bin_above;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // sum of x over the threads before this one
+  auto block_excl_scan = [&](int x) -> int {
+    const int incl = wave_incl_scan(x, lane);
+    if (lane == kWave - 1) s_wave[wv] = incl;
+    __syncthreads();
+    int base = incl - x;
+    for (int i = 0; i < kTrThreads / kWave; ++i) base += i < wv ? s_wave[i] : 0;
+    return base;
+  };
+  // the smallest and largest key over all threads' (kmin_l, kmax_l); two barriers
+  auto key_range = [&](unsigned kmin_l, unsigned kmax_l, unsigned& kmin, unsigned& kmax) {
+    if (tid == 0) { s_kmax = 0u; s_nkmin = 0u; }
+    __syncthreads();
+    // the smallest key is found as the largest of the complements: one atomicMax per wavefront each
+    kmax_l = wave_umax(kmax_l);
+    const unsigned nkmin_l = wave_umax(~kmin_l);
+    if (lane == 0) { atomicMax(&s_kmax, kmax_l); atomicMax(&s_nkmin, nkmin_l); }
+    __syncthreads();
+    kmax = s_kmax;
+    kmin = ~s_nkmin;
+  };
+  // bits to drop from a key offset within `range` (largest - smallest) so that it indexes fewer than 2^bits bins
+  auto shift_for = [](unsigned range, int bits) -> int { return range >> bits ? 32 - __clz((int)(range >> bits)) : 0; };
   const float* row = logits + (size_t)blockIdx.x * Vrow;
   auto at = [&](int i) -> float { return kMapped ? row[map[i]] : row[i]; };
   int32_t* ids = out_ids + (size_t)blockIdx.x * K;
@@ -276,55 +310,113 @@ __global__ __launch_bounds__(kTrThreads, kOcc) void trace_topk_kernel(const floa
     uint32_t* s_sample = (uint32_t*)s_cand;
     uint32_t cut;
     if constexpr (kGroups) {
-      // the K-th largest group maximum: K distinct entries of the row are at or above it
+      // A cut-off that the K largest group maxima - K distinct entries of the row - reach, and few others: histograms of
+      // the maxima's keys, every thread's share in registers, over the range that still holds the K-th (linear bins of the
+      // key, 2^11 times finer each turn), until its bin holds a few maxima or a single key.  One turn for an LM head's rows.
       const int used = (V + 31) >> 5;  // groups that hold entries; the others are padding
       const float* gm = group_max + (size_t)blockIdx.x * n_groups;
-      for (int i = tid; i < used; i += kTrThreads) s_sample[i] = order_key(gm[i]);
-      cut = (uint32_t)radix_threshold<32, 16>(s_sel, used, want, [&](int i) { return (uint64_t)s_sample[i]; });
-      __syncthreads();
+      constexpr int kKeys = 2 * kTrCap / kTrThreads;
+      uint32_t key[kKeys];
+      unsigned lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+      for (int e = 0; e < kKeys; ++e) {
+        const int i = tid + e * kTrThreads;
+        key[e] = 0u;
+        if (i < used) {
+          key[e] = order_key(gm[i]);
+          lo = min(lo, key[e]);
+          hi = max(hi, key[e]);
+        }
+      }
+      key_range(lo, hi, lo, hi);
+      for (int left = want;;) {
+        const int shift = shift_for(hi - lo, 11);
+        s_hist[tid] = 0;
+        s_hist[tid + kTrThreads] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kKeys; ++e)
+          if (tid + e * kTrThreads < used && key[e] >= lo && key[e] <= hi) atomicAdd(&s_hist[(key[e] - lo) >> shift], 1);
+        __syncthreads();
+        // bins from the top; this thread's are b1 and b1 - 1
+        const int b1 = kTrBins - 1 - 2 * tid, c1 = s_hist[b1], c0 = s_hist[b1 - 1];
+        const int above = block_excl_scan(c1 + c0);
+        if (above < left && left <= above + c1 + c0) {
+          const bool first = left <= above + c1;
+          s_bin = first ? b1 : b1 - 1;
+          s_bin_count = first ? c1 : c0;
+          s_bin_above = first ? above : above + c1;
+        }
+        __syncthreads();
+        lo += (unsigned)s_bin << shift;
+        if (hi - lo >= (1u << shift)) hi = lo + ((1u << shift) - 1u);
+        if (s_bin_count <= 32 || shift == 0) break;
+        left -= s_bin_above;
+      }
+      cut = lo;
+      // the groups that can hold an entry at or above the cut-off: one place in the list per wavefront and its share
       if (tid == 0) s_count = 0;
       __syncthreads();
-      // the groups that can hold an entry at or above the cut-off
       int* s_list = (int*)s_buck;  // up to 2 kTrCap group numbers
-      for (int i = tid; i < used; i += kTrThreads)
-        if (s_sample[i] >= cut) s_list[atomicAdd(&s_count, 1u)] = i;
+      auto reserve = [&](int mine) -> int {  // places in a list that s_count numbers, for `mine` entries of this thread
+        const int incl = wave_incl_scan(mine, lane);
+        int base = 0;
+        if (lane == kWave - 1 && incl > 0) base = (int)atomicAdd(&s_count, (unsigned)incl);
+        return __shfl(base, kWave - 1, kWave) + incl - mine;
+      };
+      {
+        int mine = 0;
+#pragma unroll
+        for (int e = 0; e < kKeys; ++e) mine += tid + e * kTrThreads < used && key[e] >= cut;
+        int at_ = reserve(mine);
+#pragma unroll
+        for (int e = 0; e < kKeys; ++e)
+          if (tid + e * kTrThreads < used && key[e] >= cut) s_list[at_++] = tid + e * kTrThreads;
+      }
       __syncthreads();
       const int ngl = (int)s_count;
       __syncthreads();
       if (tid == 0) s_count = 0;
-      __syncthreads();  // the keys are dead from here on: s_cand takes the candidates
+      __syncthreads();
       float cut_f;
       {
         const uint32_t u = (cut & 0x80000000u) ? (cut ^ 0x80000000u) : ~cut;
         cut_f = __uint_as_float(u);
         if (cut_f != cut_f) cut_f = -INFINITY;
       }
-      // eight lanes per group, 16 bytes each; eight groups in flight per lane
+      // Eight lanes per group, 16 bytes each; nine groups in flight per lane, so that the about 1040 groups of K = 1024 are
+      // one round.  A lane marks its entries that reach the cut-off in a mask and then lists the ids of the few marked ones
+      // (1.2 a lane): the values are fetched again below, by all threads at once.  Appending each entry where it was found
+      // cost an LDS atomic and twenty instructions a wavefront for every one of its 36 compares.
       const int oct = tid >> 3, ol = tid & 7;
       const bool vec_ok = (((uintptr_t)row | ((size_t)V * sizeof(float))) & 15) == 0;
-      constexpr int kG = 8, kOcts = kTrThreads / 8;
-      for (int j0 = oct; j0 < ngl; j0 += kG * kOcts) {
+      constexpr int kG = 9, kOcts = kTrThreads / 8;
+      int* s_ids = (int*)s_cand;
+      for (int j0 = oct; j0 - oct < ngl; j0 += kG * kOcts) {
         f32x4_t x[kG];
-        int e0[kG];
 #pragma unroll
         for (int u = 0; u < kG; ++u) {
           const int j = j0 + u * kOcts;
-          e0[u] = j < ngl ? s_list[j] * 32 + ol * 4 : V;  // first of this lane's four entries (V: nothing to read)
-          if (e0[u] + 3 < V && vec_ok) {
-            x[u] = *(const f32x4_t*)(row + e0[u]);
+          const int e0 = j < ngl ? s_list[j] * 32 + ol * 4 : V;  // first of this lane's four entries (V: nothing to read)
+          if (e0 + 3 < V && vec_ok) {
+            x[u] = *(const f32x4_t*)(row + e0);
           } else {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) x[u][q] = e0[u] + q < V ? row[e0[u] + q] : -INFINITY;
+            for (int q = 0; q < 4; ++q) x[u][q] = e0 + q < V ? row[e0 + q] : __builtin_nanf("");  // never reaches a cut-off
           }
         }
+        unsigned long long hits = 0;
 #pragma unroll
         for (int u = 0; u < kG; ++u)
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (e0[u] + q < V && x[u][q] >= cut_f) {
-              const unsigned slot = atomicAdd(&s_count, 1u);
-              if (slot < (unsigned)kTrCap) s_cand[slot] = entry_word(x[u][q], e0[u] + q);
-            }
+          for (int q = 0; q < 4; ++q) hits |= x[u][q] >= cut_f ? 1ull << (4 * u + q) : 0ull;
+        unsigned at_ = (unsigned)reserve(__popcll(hits));
+        while (hits) {
+          const int k = __ffsll((long long)hits) - 1;
+          hits &= hits - 1;
+          if (at_ < (unsigned)kTrCap) s_ids[at_] = s_list[j0 + (k >> 2) * kOcts] * 32 + ol * 4 + (k & 3);
+          ++at_;
+        }
       }
       __syncthreads();
       count = (int)s_count;
@@ -396,84 +488,78 @@ __global__ __launch_bounds__(kTrThreads, kOcc) void trace_topk_kernel(const floa
 
   // ---- a list that fits is ranked in place: bucket by value range, count the larger words inside the bucket ----
   // Words are distinct, so the rank of a word (how many are larger) is its position in the output.  The upper 32
-  // bits of a word are an order-preserving key of the value: a monotone map of the key onto 256 buckets (linear
+  // bits of a word are an order-preserving key of the value: a monotone map of the key onto 1024 buckets (linear
   // between the smallest and the largest key of the list, highest values first) keeps the order between buckets,
-  // and inside a bucket - a few dozen words for logits of an LM head - ranks come from direct comparison.  A bucket
+  // and inside a bucket - a few words for logits of an LM head - ranks come from direct comparison.  A bucket
   // of more than 256 words (heavy ties) sends the list to the radix select and bitonic sort below instead.
   __syncthreads();
   if (!from_row) {
     constexpr int kPer = kTrCap / kTrThreads;  // list entries per thread
-    if (tid < 256) s_sel.hist[tid] = 0;
-    if (tid == 0) { s_kmax = 0u; s_nkmin = 0u; s_big = 0u; }
-    __syncthreads();
+    constexpr int kBuckets = kTrThreads;       // one per thread in the scan below
+    s_hist[tid] = 0;
+    if (tid == 0) s_big = 0u;
     uint64_t w[kPer];
-    unsigned kmin_l = 0xffffffffu, kmax_l = 0u;
+    const bool ids_only = kGroups && V > kTrCap;  // the list holds ids: fetch their values
+    if (ids_only) {
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int i = tid + e * kTrThreads;
-      w[e] = i < count ? s_cand[i] : 0ull;
-      if (i < count) {
-        const unsigned k = (unsigned)(w[e] >> 32);
-        kmin_l = min(kmin_l, k);
-        kmax_l = max(kmax_l, k);
+      for (int e = 0; e < kPer; ++e) {
+        const int i = tid + e * kTrThreads;
+        const int id = i < count ? ((const int*)s_cand)[i] : -1;
+        w[e] = id >= 0 ? entry_word(at(id), id) : 0ull;
+      }
+      __syncthreads();  // every id is read: the words take their place (the sort of heavily tied lists reads them there)
+#pragma unroll
+      for (int e = 0; e < kPer; ++e)
+        if (tid + e * kTrThreads < count) s_cand[tid + e * kTrThreads] = w[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int i = tid + e * kTrThreads;
+        w[e] = i < count ? s_cand[i] : 0ull;
       }
     }
-    // the smallest key is found as the largest of the complements: one atomicMax per wavefront each
-    kmax_l = wave_umax(kmax_l);
-    const unsigned nkmin_l = wave_umax(~kmin_l);
-    if ((tid & 63) == 0) { atomicMax(&s_kmax, kmax_l); atomicMax(&s_nkmin, nkmin_l); }
-    __syncthreads();
-    const unsigned kmax = s_kmax, kmin = ~s_nkmin;
-    if (tid == 0) {
-      const unsigned long long range = (unsigned long long)(kmax - kmin) + 1ull;
-      s_scale = range <= 256ull ? 0ull : ((256ull << 32) / range);  // 0: the key offset is the bucket
-    }
-    __syncthreads();
-    const unsigned long long scale = s_scale;
+    unsigned kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e)
+      if (tid + e * kTrThreads < count) {
+        const unsigned k = (unsigned)(w[e] >> 32);
+        kmin = min(kmin, k);
+        kmax = max(kmax, k);
+      }
+    key_range(kmin, kmax, kmin, kmax);
+    const int shift = shift_for(kmax - kmin, 10);
     int bucket[kPer], pos[kPer];
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
       const int i = tid + e * kTrThreads;
       bucket[e] = 0; pos[e] = 0;
       if (i < count) {
-        const unsigned d = (unsigned)(w[e] >> 32) - kmin;
-        const unsigned up = scale ? (unsigned)(((unsigned long long)d * scale) >> 32) : d;  // 0 .. 255, rising with the value
-        bucket[e] = 255 - (int)up;                                                           // highest values first
-        pos[e] = atomicAdd(&s_sel.hist[bucket[e]], 1);
+        bucket[e] = kBuckets - 1 - (int)(((unsigned)(w[e] >> 32) - kmin) >> shift);  // highest values first
+        pos[e] = atomicAdd(&s_hist[bucket[e]], 1);
       }
     }
     __syncthreads();
-    if (tid < kWave) {
-      // exclusive scan of the 256 bucket sizes (four per lane), in place; remember whether a bucket is too large
-      int c[4], tot = 0, big = 0;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) { c[jj] = s_sel.hist[4 * tid + jj]; tot += c[jj]; big |= c[jj] > 256; }
-      int incl = tot;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(incl, o, kWave);
-        if (tid >= o) incl += y;
-      }
-      int run = incl - tot;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) { s_sel.hist[4 * tid + jj] = run; run += c[jj]; }
-      if (big) s_big = 1u;
+    {
+      const int c = s_hist[tid];
+      if (c > 256) s_big = 1u;
+      const int before = block_excl_scan(c);
+      s_hist[tid] = before;
     }
     __syncthreads();
     if (!s_big) {
-      // bucket b occupies s_buck[hist[b] .. hist[b + 1]) (the last one ends at count)
+      // bucket b occupies s_buck[s_hist[b] .. s_hist[b + 1]) (the last one ends at count)
 #pragma unroll
       for (int e = 0; e < kPer; ++e) {
         const int i = tid + e * kTrThreads;
-        if (i < count) s_buck[s_sel.hist[bucket[e]] + pos[e]] = w[e];
+        if (i < count) s_buck[s_hist[bucket[e]] + pos[e]] = w[e];
       }
       __syncthreads();
 #pragma unroll
       for (int e = 0; e < kPer; ++e) {
         const int i = tid + e * kTrThreads;
         if (i < count) {
-          const int lo = s_sel.hist[bucket[e]];
-          const int hi = bucket[e] == 255 ? count : s_sel.hist[bucket[e] + 1];
+          const int lo = s_hist[bucket[e]];
+          const int hi = bucket[e] == kBuckets - 1 ? count : s_hist[bucket[e] + 1];
           int rank = lo;
           for (int jj = lo; jj < hi; ++jj) rank += s_buck[jj] > w[e];
           if (rank < want) {
