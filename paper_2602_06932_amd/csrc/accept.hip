@@ -137,59 +137,61 @@ __device__ __forceinline__ float request_temperature(const AcceptParams& P, int 
 }
 
 // (max, logsumexp(l / T), arg-max) of one logits row, merged from its tile statistics by one
-// wavefront; result valid in every lane.  Each lane folds its tiles into a running (max, scaled
-// sum) pair - the loads of eight tiles are issued together - then the lanes are folded by
-// butterfly exchanges.  Scale factors go through the hardware exp2 of an fp64-formed exponent.
-// kLanes = 32: the two halves of the wavefront merge two different rows at the same time (`row` then
-// differs between the halves), so a workgroup gets through twice as many rows per round of loads.
-template <int kLanes = kWave>
+// wavefront; result valid in every lane.  The row's maximum first, over the lanes, then the sums scaled to it: no running
+// rescale, so no chain of exponentials.  All of a row's statistics are in flight together and stay in registers up to
+// kHeldTiles of them; the later ones of a larger vocabulary are read twice.  Scale factors go through the hardware exp2 of an
+// fp64-formed exponent.
+constexpr int kHeldTiles = 832;  // 212 992 vocabulary entries
 __device__ __forceinline__ void merge_row_stats(const AcceptParams& P, size_t row, double T, int lane, float* out_max,
                                                 double* out_lse, int* out_arg, bool want_arg = true) {
+  constexpr int kHeld = kHeldTiles / kWave;
   const int nt = P.n_tiles;
   const float* pm = P.pmax + row * nt;
   const float* ps = P.psum + row * nt;
   const double c = 1.4426950408889634 / T;
-  const int sub = lane & (kLanes - 1);
+  float xm[kHeld], xs[kHeld];
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) {
+    xm[u] = -INFINITY;
+    xs[u] = 0.f;
+    if (u * kWave < nt) {  // uniform
+      const int t = u * kWave + lane, tc = t < nt ? t : nt - 1;
+      xm[u] = pm[tc];
+      xs[u] = t < nt ? ps[tc] : 0.f;
+    }
+  }
   float m = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) m = fmaxf(m, xm[u]);  // (past the end: the last tile once more)
+  for (int t = kHeldTiles + lane; t < nt; t += kWave) m = fmaxf(m, pm[t]);
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
+  const double md = m > -INFINITY ? (double)m : 0.0;
   double s = 0.0;
   int mt = 0x7fffffff;
-  for (int t0 = 0; t0 < nt; t0 += kLanes * 8) {
-    float xm[8], xs[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + u * kLanes + sub;
-      xm[u] = t < nt ? pm[t] : -INFINITY;
-      xs[u] = t < nt ? ps[t] : 0.f;
+  for (int u = kHeld - 1; u >= 0; --u)
+    if (u * kWave < nt) {
+      // (a tile of -inf alone has no sum; whatever stands in its place is not read into s)
+      s += xm[u] > -INFINITY ? (double)xs[u] * (double)__builtin_amdgcn_exp2f((float)(((double)xm[u] - md) * c)) : 0.0;
+      if (xm[u] == m) mt = min(u * kWave + lane, nt - 1);
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (xm[u] > m) {
-        s = s * (double)__builtin_amdgcn_exp2f((float)(((double)m - (double)xm[u]) * c)) + (double)xs[u];
-        m = xm[u];
-        mt = t0 + u * kLanes + sub;
-      } else if (xm[u] > -INFINITY) {
-        s += (double)xs[u] * (double)__builtin_amdgcn_exp2f((float)(((double)xm[u] - (double)m) * c));
-      }
-    }
+  for (int t = kHeldTiles + lane; t < nt; t += kWave) {
+    const float x = pm[t];
+    if (x > -INFINITY) s += (double)ps[t] * (double)__builtin_amdgcn_exp2f((float)(((double)x - md) * c));
+    if (x == m) mt = min(mt, t);
   }
 #pragma unroll
-  for (int o = kLanes / 2; o > 0; o >>= 1) {
-    const float om = __shfl_xor(m, o, kWave);
-    const double os = __shfl_xor(s, o, kWave);
-    const int ot = __shfl_xor(mt, o, kWave);
-    const float nm = fmaxf(m, om);
-    if (nm > -INFINITY) {
-      const double fa = m > -INFINITY ? (double)__builtin_amdgcn_exp2f((float)(((double)m - (double)nm) * c)) : 0.0;
-      const double fb = om > -INFINITY ? (double)__builtin_amdgcn_exp2f((float)(((double)om - (double)nm) * c)) : 0.0;
-      s = s * fa + os * fb;
-    }
-    if (om > m || (om == m && ot < mt)) mt = ot;
-    m = nm;
-  }
+  for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
   *out_max = m;
   *out_lse = (double)m / T + log(s);
-  // the arg-max id sits behind one more dependent load; only greedy verification reads it
-  *out_arg = want_arg ? P.parg[row * nt + mt] : 0;
+  *out_arg = 0;
+  if (want_arg) {
+    // the arg-max id (lowest tile that holds the maximum) sits behind one more dependent load; only greedy verification reads it
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) mt = min(mt, __shfl_xor(mt, o, kWave));
+    *out_arg = P.parg[row * nt + (mt < nt ? mt : 0)];
+  }
 }
 
 // ============================================================================================
@@ -486,7 +488,7 @@ __global__ __launch_bounds__(kSmallThreads) void accept_chain_pick(AcceptParams 
 // state lives in registers of every wavefront - the tree is a lane per node, the next child a ballot - so a step has two
 // workgroup barriers; and a slice sum is its own flag: its word is kNotYet until it is written, so one store and one load
 // cross the dies.  16 trees of 32 nodes over 128 256 ids: 90 us with group sums exchanged behind an arrival counter
-// (release, acquire, then the loads; the rows re-read for every sweep) -> 50 us.
+// (release, acquire, then the loads; the rows re-read for every sweep) -> 39 us.
 // The launcher keeps S * B within the number of compute units, so all workgroups of a request are resident together;
 // the wait is bounded all the same.
 // ============================================================================================
@@ -515,9 +517,9 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// kHeld: a slice has at most kHold groups per wavefront, whose operands stay in registers from sweep to sweep.
-// kWor: siblings were drawn without replacement.
-constexpr int kHold = 4;
+// kHeld: a slice has at most held_groups(kWor) groups per wavefront, whose operands stay in registers from sweep to sweep (as
+// many as 128 registers a thread take without spilling).  kWor: siblings were drawn without replacement.
+__host__ __device__ constexpr int held_groups(bool wor) { return wor ? 2 : 3; }
 #define AURORA_INLINE __attribute__((always_inline))
 template <bool kHeld, bool kWor>
 __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P) {
@@ -565,13 +567,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
   }
 
   // ---- 1. per-row (logsumexp, arg-max) from the tile statistics ---------------------------------
-  // half a wavefront per row: 32 rows per round
-  for (int n0 = 0; n0 < Nq; n0 += 2 * kAccWaves) {
-    const int n = n0 + 2 * wv + (lane >> 5);
-    const int nc = n < Nq ? n : Nq - 1;  // idle halves repeat the last row (the shuffles need every lane)
+  for (int n = wv; n < Nq; n += kAccWaves) {
     float mx; double lse; int arg;
-    merge_row_stats<32>(P, row0 + nc, T, lane, &mx, &lse, &arg, greedy);
-    if ((lane & 31) == 0 && n < Nq) { s_lse[n] = lse; s_arg[n] = arg; }
+    merge_row_stats(P, row0 + n, T, lane, &mx, &lse, &arg, greedy);
+    if (lane == 0) { s_lse[n] = lse; s_arg[n] = arg; }
   }
   if (tid == 0) s_fail = 0;
   __syncthreads();
@@ -641,13 +640,21 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
   double total = 0.0;
   int cur_len = 0;          // siblings without replacement: the distribution the next sibling was drawn from
   double cur_fac = 1.0, rej_mass = 0.0;
-  Lane4 held[kHold];
-  int held_node = -1, held_slice = -1;
+  constexpr int kHold = kHeld ? held_groups(kWor) : 4;  // groups of a wavefront at a time
+  // Held operands: the weights of residual level held_level and the draft probabilities of this lane's tokens.
+  double held_x[kHeld ? kHold : 1][4];
+  float held_q[kHeld ? kHold : 1][4];
+  int held_node = -1, held_slice = -1, held_level = 0;
 
   // the weights (of residual level `level`; skip_last leaves its last step unnormalised) of the four tokens v0 ..
   auto weights = [&](const Lane4& r, int v0, int level, bool skip_last, double x[4]) AURORA_INLINE {
     if constexpr (kWor) lane_weights_wor(r, v0, V, s_lse[cur], inv_t, level, x, invZs, skip_last, ql);
     else lane_weights(r, v0, V, s_lse[cur], inv_t, level, x, invZs, skip_last);
+  };
+  // one residual step from level s, as the functions above take it: max(0, x - q), not yet normalised
+  auto step = [&](double x, float q, int v, int s) AURORA_INLINE -> double {
+    if constexpr (kWor) return fmax(0.0, x - (in_list(v, rej, qlen[s]) ? 0.0 : (double)q * qfac[s]));
+    return fmax(0.0, x - (double)q);
   };
   // f(group, its weights in this lane's four tokens) for this wavefront's groups of slice sl, in ascending order
   auto for_groups = [&](int sl, int level, bool skip_last, auto f) AURORA_INLINE {
@@ -656,22 +663,49 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
     const QRow qrow = q_row(P, row0 + cur);
     if constexpr (kHeld) {
       if (held_node != cur || held_slice != sl) {
+        Lane4 r[kHold];
 #pragma unroll
         for (int i = 0; i < kHold; ++i) {
           const int gi = lo + wv + i * kAccWaves;
-          if (gi < hi) held[i] = lane_load(lrow, qrow, gi * kGroup + lane * 4, V, vec_ok);
+          if (gi < hi) r[i] = lane_load(lrow, qrow, gi * kGroup + lane * 4, V, vec_ok);
+        }
+#pragma unroll
+        for (int i = 0; i < kHold; ++i) {
+          const int gi = lo + wv + i * kAccWaves;
+          if (gi < hi) {
+            weights(r[i], gi * kGroup + lane * 4, 0, false, held_x[i]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) held_q[i][e] = r[i].q[e];
+          }
+          __builtin_amdgcn_sched_barrier(0);  // a group at a time: the registers hold the operands
         }
         held_node = cur;
         held_slice = sl;
+        held_level = 0;
+      }
+      for (; held_level < (skip_last ? level - 1 : level); ++held_level) {
+        const double iz = invZs[held_level];
+#pragma unroll
+        for (int i = 0; i < kHold; ++i) {
+          const int gi = lo + wv + i * kAccWaves;
+          if (gi < hi)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              held_x[i][e] = step(held_x[i][e], held_q[i][e], gi * kGroup + lane * 4 + e, held_level) * iz;
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
 #pragma unroll
       for (int i = 0; i < kHold; ++i) {
         const int gi = lo + wv + i * kAccWaves;
         if (gi < hi) {  // wave-uniform
           double x[4];
-          weights(held[i], gi * kGroup + lane * 4, level, skip_last, x);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            x[e] = skip_last ? step(held_x[i][e], held_q[i][e], gi * kGroup + lane * 4 + e, held_level) : held_x[i][e];
           f(gi, x);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     } else {
       for (int g = lo + wv; g < hi; g += kHold * kAccWaves) {
@@ -969,7 +1003,7 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
       hipLaunchKernelGGL(fill_not_yet_kernel, dim3((words + 255) / 256), dim3(256), 0, st, P.exch, words);
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    const bool held = (ngroups + S - 1) / S <= kHold * kAccWaves;
+    const bool held = (ngroups + S - 1) / S <= held_groups(P.wor != 0) * kAccWaves;
 #define AURORA_TREE(HELD, WOR) hipLaunchKernelGGL((accept_tree_kernel<HELD, WOR>), dim3(S, a.B), dim3(kAccThreads), 0, st, P)
     if (held) {
       if (P.wor) AURORA_TREE(true, true); else AURORA_TREE(true, false);

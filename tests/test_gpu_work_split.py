@@ -1,0 +1,53 @@
+"""How the work is split, where a split changes: attention batches of so few tiles that only some workgroups get any and a row's
+partials are merged by several groups of threads (and the first sizes past either), their backward, and tree walks whose slices
+are held in registers or not.  Against the float64 oracle, at the tolerances of parity_util."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+torch = pytest.importorskip("torch")
+
+
+def _workload(batch, context, nodes, kv8, hq=8, hkv=2):
+    kw = dict(batch=batch, vocab=64, hidden_size=64, num_q_heads=hq, num_kv_heads=hkv, kv_fp8=kv8)
+    if nodes:
+        return gen.llama_tree(300 + batch + context, num_q=nodes, context=context, **kw)
+    return gen.llama_chain(300 + batch + context, len_lo=max(5, context - 40), len_hi=context, **kw)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("batch,context,nodes,hkv", [(1, 5, 0, 2), (1, 33, 0, 2), (1, 700, 0, 1), (1, 2777, 0, 2), (3, 1500, 7, 2),
+                                                     (12, 300, 0, 2), (24, 200, 0, 2), (1, 40, 24, 1), (1, 2777, 32, 2),
+                                                     (9, 500, 32, 2), (2, 900, 61, 2)])
+def test_attention_of_few_tiles(gpu_lib, batch, context, nodes, hkv, kv8):
+    from paper_2602_06932_amd.device import DeviceVerify
+    from parity_util import check_attention
+    w = _workload(batch, context, nodes, kv8, hq=4 * hkv, hkv=hkv)
+    dv = DeviceVerify(w)
+    dv.attn_out.fill_(float("nan"))
+    dv.attn()
+    torch.cuda.synchronize()
+    check_attention(dv.attn_out_host(), oracle.attn_workload(w), w.dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,context,nodes", [(1, 40, 0), (1, 1500, 0), (1, 1500, 12), (1, 1500, 32), (5, 333, 32)])
+def test_backward_of_few_tiles(gpu_lib, batch, context, nodes):
+    from test_gpu_attn_bwd import _check
+    _check(_workload(batch, context, nodes, False), 11)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,num_q,vocab,wor", [(130, 6, 9000, False), (130, 6, 9000, True),  # one slice of more groups than are held
+                                                   (50, 8, 70000, False),                       # five slices of 55 groups: the last held one is 48
+                                                   (64, 8, 49152, False),                       # four slices of 48 groups: held
+                                                   (3, 64, 20011, False)])                      # slices bounded by the exchange buffer
+def test_tree_walk_slices(gpu_lib, batch, num_q, vocab, wor):
+    from test_gpu_parity import _full_check
+    w = gen.llama_tree(400 + batch, batch=batch, num_q=num_q, vocab=vocab, hidden_size=64, context=70, num_q_heads=2,
+                       num_kv_heads=1, draft_noise=1.5, siblings_without_replacement=wor)
+    _, a = _full_check(gpu_lib, w)
+    assert 0 < np.mean(a.accept_len) < num_q - 1
