@@ -14,7 +14,8 @@
 //                       draft was kept - over groups of 256 tokens of its slice; slice 0 writes
 //                       accept_len / accept_mask / p_at_draft / row_lse;
 //   accept_chain_pick   one workgroup per request: scan the group sums, find the group holding
-//                       u * total, rescan that group with a wavefront prefix sum for the token.
+//                       u * total, rescan that group with a wavefront prefix sum for the token
+//                       (done by the sweep's workgroup itself where S is 1).
 // Trees at T > 0 may need one sweep per rejected sibling, each depending on the previous one:
 // accept_tree_kernel walks a request in up to 16 workgroups that split every sweep and exchange their
 // partial sums.  The same kernel, one workgroup per request, serves every greedy (T = 0) call, where no
@@ -259,6 +260,111 @@ __device__ __forceinline__ void lane_weights_wor(const Lane4& r, int v0, int V, 
     x[e] = v0 + e < V ? sweep_weight_wor(r.l[e], r.q[e], v0 + e, lse, inv_t, nres, invZs, skip_last, ql) : 0.0;
 }
 
+// Inverse-CDF draw from the group sums of one request by a workgroup of kThreads: the stop row, whether the draw is from the
+// residual (nres = 1) or from p, and the row's logsumexp are the sweep's.
+// A residual that vanished (sum 0) falls back to the row's p: rare enough for one workgroup.
+template <int kThreads>
+__device__ __forceinline__ void chain_pick(const AcceptParams& P, int b, int row, int nres, double lse) {
+  __shared__ double s_wtot[kThreads / kWave];
+  __shared__ int s_pick;
+  __shared__ double s_prefix;
+  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  const int V = P.V, ng = P.ngroups;
+  const double inv_t = 1.0 / (double)request_temperature(P, b);
+  const float* lrow = P.logits + ((size_t)b * P.Nq + row) * V;
+  const QRow qrow = q_row(P, (size_t)b * P.Nq + row);
+  const bool vec_ok = rows_vec_ok(P);
+  double* gs = P.gsum + (size_t)b * ng;
+  const int per = (ng + kThreads - 1) / kThreads;
+  const int ga = min(ng, tid * per), gb = min(ng, ga + per);
+
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    double loc = 0.0;
+    for (int g = ga; g < gb; ++g) loc += gs[g];
+    const double incl = wave_incl_scan(loc, lane);
+    if (lane == kWave - 1) s_wtot[wv] = incl;
+    if (tid == 0) s_pick = 0x7fffffff;
+    __syncthreads();
+    double wbase = 0.0, total = 0.0;
+    for (int i = 0; i < kThreads / kWave; ++i) {
+      if (i < wv) wbase += s_wtot[i];
+      total += s_wtot[i];
+    }
+    if (total > 0.0 || nres == 0) {
+      const double thr = (double)P.un[((size_t)b * P.Nq + row) * 2 + 1] * total;
+      double run = wbase + incl - loc;
+      int found = 0x7fffffff;
+      double before = 0.0;
+      for (int g = ga; g < gb; ++g) {
+        const double nxt = run + gs[g];
+        if (found == 0x7fffffff && nxt > thr) { found = g; before = run; }
+        run = nxt;
+      }
+      if (found != 0x7fffffff) atomicMin(&s_pick, found);
+      __syncthreads();
+      const int pick = s_pick;
+      if (pick == found && found != 0x7fffffff) s_prefix = before;
+      __syncthreads();
+      if (wv == 0) {
+        int token = -1;
+        if (pick != 0x7fffffff) {
+          const int v0 = pick * kGroup + lane * 4;
+          double x[4];
+          lane_weights(lane_load(lrow, qrow, v0, V, vec_ok), v0, V, lse, inv_t, nres, x);
+          const double lane_tot = (x[0] + x[1]) + (x[2] + x[3]);
+          const double lane_incl = wave_incl_scan(lane_tot, lane) + s_prefix;
+          const unsigned long long hit = __ballot(lane_incl > thr);
+          const unsigned long long pos = __ballot(lane_tot > 0.0);
+          if (hit) {
+            const int hl = __ffsll((long long)hit) - 1;  // first lane whose running sum crosses
+            double r0 = __shfl(lane_incl - lane_tot, hl, kWave);
+            int e_hit = 3;
+            const double y0 = __shfl(x[0], hl, kWave), y1 = __shfl(x[1], hl, kWave), y2 = __shfl(x[2], hl, kWave);
+            if (r0 + y0 > thr) e_hit = 0;
+            else if (r0 + y0 + y1 > thr) e_hit = 1;
+            else if (r0 + y0 + y1 + y2 > thr) e_hit = 2;
+            token = pick * kGroup + hl * 4 + e_hit;
+            if (token >= V) token = -1;
+          } else if (pos) {
+            // rounding left no crossing inside the group: its last token with positive weight
+            const int pl = 63 - __clzll((long long)pos);
+            int e_last = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (__shfl(x[e], pl, kWave) > 0.0) e_last = e;
+            token = pick * kGroup + pl * 4 + e_last;
+          }
+        }
+        if (token < 0) {  // no crossing at all: the largest token with positive weight
+          int m = -1;
+          for (int i = lane; i < P.slices; i += kWave) m = max(m, P.lastpos[(size_t)b * P.slices + i]);
+          token = wave_max(m);
+        }
+        if (lane == 0) P.next_token[b] = token;
+      }
+      return;
+    }
+    // residual identically zero: recompute the group sums of p itself with this workgroup, then draw
+    __syncthreads();
+    nres = 0;
+    int lastpos = -1;
+    for (int g = wv; g < ng; g += kThreads / kWave) {
+      const int v0 = g * kGroup + lane * 4;
+      double x[4];
+      lane_weights(lane_load(lrow, qrow, v0, V, vec_ok), v0, V, lse, inv_t, 0, x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (x[e] > 0.0) lastpos = max(lastpos, v0 + e);
+      const double acc = wave_sum((x[0] + x[1]) + (x[2] + x[3]));
+      if (lane == 0) gs[g] = acc;
+    }
+    lastpos = wave_max(lastpos);
+    if (lane == 0) atomicMax(&P.lastpos[(size_t)b * P.slices], lastpos);
+    __threadfence_block();
+    __syncthreads();
+  }
+}
+
 // Kernel 1: S workgroups per request.  Every workgroup repeats the (cheap) walk - merge the tile
 // statistics of the request's rows, evaluate the k accept tests in parallel in fp64, find the first
 // failure - then sums the draw weights over its slice of the vocabulary.  Slice 0 writes the
@@ -366,114 +472,20 @@ __global__ __launch_bounds__(kSweepThreads) void accept_chain_sweep(AcceptParams
     for (int i = 0; i < kSweepThreads / kWave; ++i) m = max(m, s_last[i]);
     P.lastpos[(size_t)b * P.slices + slice] = m;
   }
-}
-
-// Kernel 2: inverse-CDF draw from the group sums, one workgroup per request.
-// A residual that vanished (sum 0) falls back to the row's p: rare enough for one workgroup.
-__global__ __launch_bounds__(kSmallThreads) void accept_chain_pick(AcceptParams P) {
-  __shared__ double s_wtot[kSmallThreads / kWave];
-  __shared__ int s_pick;
-  __shared__ double s_prefix;
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
-  const int V = P.V, ng = P.ngroups;
-  const int row = P.st_row[b];
-  int nres = P.st_rej[b];
-  if (nres == 2) return;  // a greedy request (one temperature per request): its token is already written
-  const double lse = P.st_lse[b];
-  const double inv_t = 1.0 / (double)request_temperature(P, b);
-  const float* lrow = P.logits + ((size_t)b * P.Nq + row) * V;
-  const QRow qrow = q_row(P, (size_t)b * P.Nq + row);
-  const bool vec_ok = rows_vec_ok(P);
-  double* gs = P.gsum + (size_t)b * ng;
-  const int per = (ng + kSmallThreads - 1) / kSmallThreads;
-  const int ga = min(ng, tid * per), gb = min(ng, ga + per);
-
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    double loc = 0.0;
-    for (int g = ga; g < gb; ++g) loc += gs[g];
-    const double incl = wave_incl_scan(loc, lane);
-    if (lane == kWave - 1) s_wtot[wv] = incl;
-    if (tid == 0) s_pick = 0x7fffffff;
-    __syncthreads();
-    double wbase = 0.0, total = 0.0;
-    for (int i = 0; i < kSmallThreads / kWave; ++i) {
-      if (i < wv) wbase += s_wtot[i];
-      total += s_wtot[i];
-    }
-    if (total > 0.0 || nres == 0) {
-      const double thr = (double)P.un[((size_t)b * P.Nq + row) * 2 + 1] * total;
-      double run = wbase + incl - loc;
-      int found = 0x7fffffff;
-      double before = 0.0;
-      for (int g = ga; g < gb; ++g) {
-        const double nxt = run + gs[g];
-        if (found == 0x7fffffff && nxt > thr) { found = g; before = run; }
-        run = nxt;
-      }
-      if (found != 0x7fffffff) atomicMin(&s_pick, found);
-      __syncthreads();
-      const int pick = s_pick;
-      if (pick == found && found != 0x7fffffff) s_prefix = before;
-      __syncthreads();
-      if (wv == 0) {
-        int token = -1;
-        if (pick != 0x7fffffff) {
-          const int v0 = pick * kGroup + lane * 4;
-          double x[4];
-          lane_weights(lane_load(lrow, qrow, v0, V, vec_ok), v0, V, lse, inv_t, nres, x);
-          const double lane_tot = (x[0] + x[1]) + (x[2] + x[3]);
-          const double lane_incl = wave_incl_scan(lane_tot, lane) + s_prefix;
-          const unsigned long long hit = __ballot(lane_incl > thr);
-          const unsigned long long pos = __ballot(lane_tot > 0.0);
-          if (hit) {
-            const int hl = __ffsll((long long)hit) - 1;  // first lane whose running sum crosses
-            double r0 = __shfl(lane_incl - lane_tot, hl, kWave);
-            int e_hit = 3;
-            const double y0 = __shfl(x[0], hl, kWave), y1 = __shfl(x[1], hl, kWave), y2 = __shfl(x[2], hl, kWave);
-            if (r0 + y0 > thr) e_hit = 0;
-            else if (r0 + y0 + y1 > thr) e_hit = 1;
-            else if (r0 + y0 + y1 + y2 > thr) e_hit = 2;
-            token = pick * kGroup + hl * 4 + e_hit;
-            if (token >= V) token = -1;
-          } else if (pos) {
-            // rounding left no crossing inside the group: its last token with positive weight
-            const int pl = 63 - __clzll((long long)pos);
-            int e_last = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (__shfl(x[e], pl, kWave) > 0.0) e_last = e;
-            token = pick * kGroup + pl * 4 + e_last;
-          }
-        }
-        if (token < 0) {  // no crossing at all: the largest token with positive weight
-          int m = -1;
-          for (int i = lane; i < P.slices; i += kWave) m = max(m, P.lastpos[(size_t)b * P.slices + i]);
-          token = wave_max(m);
-        }
-        if (lane == 0) P.next_token[b] = token;
-      }
-      return;
-    }
-    // residual identically zero: recompute the group sums of p itself with this workgroup, then draw
-    __syncthreads();
-    nres = 0;
-    int lastpos = -1;
-    for (int g = wv; g < ng; g += kSmallThreads / kWave) {
-      const int v0 = g * kGroup + lane * 4;
-      double x[4];
-      lane_weights(lane_load(lrow, qrow, v0, V, vec_ok), v0, V, lse, inv_t, 0, x);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (x[e] > 0.0) lastpos = max(lastpos, v0 + e);
-      const double acc = wave_sum((x[0] + x[1]) + (x[2] + x[3]));
-      if (lane == 0) gs[g] = acc;
-    }
-    lastpos = wave_max(lastpos);
-    if (lane == 0) atomicMax(&P.lastpos[(size_t)b * P.slices], lastpos);
+  // one slice (small vocabularies, or batches that fill the chip): the draw follows here instead of behind another launch
+  if (P.slices == 1) {
     __threadfence_block();
     __syncthreads();
+    chain_pick<kSweepThreads>(P, b, row, nres, lse);
   }
+}
+
+// Kernel 2: the draw for requests whose sweep was spread over several workgroups.
+__global__ __launch_bounds__(kSmallThreads) void accept_chain_pick(AcceptParams P) {
+  const int b = blockIdx.x;
+  const int nres = P.st_rej[b];
+  if (nres == 2) return;  // a greedy request (one temperature per request): its token is already written
+  chain_pick<kSmallThreads>(P, b, P.st_row[b], nres, P.st_lse[b]);
 }
 
 // ============================================================================================
@@ -1015,7 +1027,7 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
   }
   hipLaunchKernelGGL(accept_chain_sweep, dim3(P.slices, a.B), dim3(kSweepThreads), 0, st, P);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || P.slices == 1) return e;
   hipLaunchKernelGGL(accept_chain_pick, dim3(a.B), dim3(kSmallThreads), 0, st, P);
   return hipGetLastError();
 }

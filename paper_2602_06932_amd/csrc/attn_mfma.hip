@@ -327,9 +327,12 @@ constexpr int kWideStageBytes = 2 * 2 * kAtTileBytes;                // two tile
 constexpr int kWideQBytes = 4 * 32 * kAtRowBytes;                    // four query tiles
 constexpr int kWideLdsBytes = kWideQBytes + kWideStages * kWideStageBytes;
 
-// kFp8KV: the cache holds E4M3 codes.  A wavefront then fetches its eighth of a step - four
-// token rows of K in lanes 0..31, of V in lanes 32..63, for each of the step's two tiles - into registers
-// two steps ahead, and widens it into the ring stage right before the step's barrier.
+// kFp8KV: the cache holds E4M3 codes, which go into the ring as they are and are widened behind the LDS read, as in the
+// narrow kernel: a stage is half as large, so the ring holds twice as many.  16 trees of 32 nodes over 4096 tokens: sweep 69 us
+// with codes staged in registers and widened into the ring -> 59 us; 20 trees of 45 nodes, 0.9K-7K: 174 -> 153 us.
+constexpr int kWide8Stages = 6;
+constexpr int kWide8StageBytes = 2 * 2 * kAtTile8;
+static_assert(kWide8Stages == 6 && kWide8Stages * kWide8StageBytes <= kWideStages * kWideStageBytes, "the ring's bytes");
 template <bool kLocalPlan, bool kFp8KV>
 __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
     const bf16_t* __restrict__ q, const void* __restrict__ kp_, const void* __restrict__ vp_,
@@ -473,7 +476,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
       }
       if (tid < Nq) s_par[tid] = par_n;
       __syncthreads();
-      load_q_frags(qf, qtile, li, lh);
+      if constexpr (kFp8KV) load_q_frags8(qf, qtile, li, lh); else load_q_frags(qf, qtile, li, lh);
       anc = ancestor_mask(parents ? s_par : nullptr, node, Nq);
     };
     auto compute_step = [&](int sidx) {
@@ -487,55 +490,39 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
       }
     };
     if constexpr (kFp8KV) {
-      struct Step8 { u32x4_t t[2]; };
-      const bool is_v = lane >= 32;
-      const int r8 = 4 * wave + ((lane & 31) >> 3), f8 = lane & 7;  // token row of the tile, 16-byte chunk of its codes
-      const uint8_t* pool8 = (const uint8_t*)(is_v ? vp_ : kp_);
-      // steps past the segment's last re-read it: every turn of the loop below has the same loads and waits
-      auto fetch = [&](Step8& r, int sidx) {
-        const int sc = min(sidx, nstep - 1);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          const int j0 = min(start + (2 * sc + g) * kAtTile, last_tile_start);
-          const int pid_a = bt[j0 >> page_shift];
-          const int pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
-          const int tok = min(j0 + r8, L - 1);
-          const int pid = (tok >> page_shift) == (j0 >> page_shift) ? pid_a : pid_b;
-          const size_t off = ((((size_t)pid * Hkv + hk) << page_shift) + (tok & ((1 << page_shift) - 1))) * kAtD + f8 * 16;
-          r.t[g] = __builtin_nontemporal_load((const u32x4_t*)(pool8 + off));
-        }
+      // a wavefront's eighth of a step: eight token rows of K and of V of one of the step's two tiles
+      const uint8_t* kp8 = (const uint8_t*)kp_;
+      const uint8_t* vp8 = (const uint8_t*)vp_;
+      auto issue_step8 = [&](int sidx) {
+        char* kb = ring + (sidx % kWide8Stages) * kWide8StageBytes + grp * (2 * kAtTile8);
+        const int j0 = min(start + (2 * sidx + grp) * kAtTile, last_tile_start);
+        const int pid_a = bt[j0 >> page_shift];
+        const int pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
+        issue_rows8<false>(kp8, kb, wq, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
+        issue_rows8<true>(vp8, kb + kAtTile8, wq, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
       };
-      auto spill = [&](const Step8& r, int sidx) {
-        char* stage = ring + (sidx % kWideStages) * kWideStageBytes + (is_v ? kAtTileBytes : 0);
-        const int key = is_v ? v_key(r8) : (r8 & 15);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          u32x4_t lo, hi;
-          widen16(r.t[g], lo, hi);
-          char* row = stage + g * (2 * kAtTileBytes) + r8 * kAtRowBytes;
-          *(u32x4_t*)(row + (((2 * f8) ^ key) * 16)) = lo;
-          *(u32x4_t*)(row + (((2 * f8 + 1) ^ key) * 16)) = hi;
-        }
-      };
-      // A turn writes stage sidx % 3 while slower wavefronts may still read stage (sidx - 1) % 3; the stage it
-      // overwrites was last read two barriers ago.
-      auto turn = [&](Step8& r, int sidx, bool live) {
-        spill(r, sidx);
-        // LDS writes done, then the bare barrier: a fenced one would also wait for the loads in flight
-        __builtin_amdgcn_s_waitcnt((7 << 4) | (3 << 14) | 15);  // lgkmcnt(0) only
-        __builtin_amdgcn_s_barrier();  // the step's stage is complete from all eight wavefronts
-        asm volatile("" ::: "memory");
-        fetch(r, sidx + 2);
-        if (live) compute_step(sidx);
-      };
-      Step8 ra, rb;
-      fetch(ra, 0);
-      __builtin_amdgcn_sched_barrier(0);  // issue order = use order, or the first wait covers both steps
-      fetch(rb, 1);
+      for (int i = 0; i < kWide8Stages - 1 && i < nstep; ++i) issue_step8(i);
       stage_query();
-      for (int sidx = 0; sidx < nstep; sidx += 2) {
-        turn(ra, sidx, true);
-        turn(rb, sidx + 1, sidx + 1 < nstep);  // nstep is the same for the whole workgroup
+      for (int sidx = 0; sidx < nstep; ++sidx) {
+        // steps sidx+1 .. sidx+kWide8Stages-2 may stay in flight; near the end of the segment fewer were issued
+        const int younger = nstep - 1 - sidx;
+        if (younger >= 4) WAIT_VMCNT(8);
+        else if (younger == 3) WAIT_VMCNT(6);
+        else if (younger == 2) WAIT_VMCNT(4);
+        else if (younger == 1) WAIT_VMCNT(2);
+        else WAIT_VMCNT(0);
+        __builtin_amdgcn_s_barrier();  // step complete from all eight wavefronts; the previous step's stage is free
+        asm volatile("" ::: "memory");
+        if (sidx + kWide8Stages - 1 < nstep) issue_step8(sidx + kWide8Stages - 1);
+        const int tt = 2 * sidx + grp;
+        if (rt_ok && tt < ntile) {
+          const char* kb = ring + (sidx % kWide8Stages) * kWide8StageBytes + grp * (2 * kAtTile8);
+          const f32x16_t s_acc = tile_scores8(kb, qf, li, lh);
+          bf16x8_t pb2[2];
+          tile_softmax(s_acc, st, pb2, scale_log2, start + tt * kAtTile, prefix, L, anc, lh);
+          tile_pv8(kb + kAtTile8, pb2, st, lane);
+        }
+        asm volatile("" ::: "memory");
       }
     } else {
       for (int i = 0; i < kWideStages - 1 && i < nstep; ++i) issue_step(i);

@@ -305,20 +305,6 @@ __device__ __forceinline__ void tile_pv8(const char* vbuf, const bf16x8_t pb2[2]
     }
 }
 
-// sixteen E4M3 codes -> sixteen bf16 (exact: 3 mantissa bits and the exponent range fit), as two 16-byte chunks
-__device__ __forceinline__ void widen16(const u32x4_t c, u32x4_t& lo, u32x4_t& hi) {
-  unsigned int out[8];
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const f32x2_t a = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[w], false);  // bytes 0, 1
-    const f32x2_t b = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[w], true);   // bytes 2, 3
-    out[2 * w] = __builtin_bit_cast(unsigned int, __builtin_convertvector(a, bf16x2_t));
-    out[2 * w + 1] = __builtin_bit_cast(unsigned int, __builtin_convertvector(b, bf16x2_t));
-  }
-  lo = u32x4_t{out[0], out[1], out[2], out[3]};
-  hi = u32x4_t{out[4], out[5], out[6], out[7]};
-}
-
 // prefix of tiles per request (see attn_plan_kernel) built by the whole workgroup into s_pb[0..B], B <= 1024
 __device__ __forceinline__ void build_prefix(const int32_t* __restrict__ seq_lens, int B, int Hkv, int* s_pb,
                                              int* s_wsum) {
