@@ -66,10 +66,12 @@ __global__ __launch_bounds__(kLossThreads) void loss_count_kernel(const int8_t* 
 // A row need not start at 16 bytes: the vectors start at its first aligned element, and the up to three elements before and
 // after them are held by six threads.
 // The kernel is bound by the row's bytes in and out, so every line of the gradient is written once and whole: w p_target is
-// laid out in LDS, half a row at a time (the ids are distinct, a plain scatter; the first half early, behind the row's
-// loads), and subtracted before the store.  Rewriting the kept tokens' entries in global memory afterwards found their lines
-// partly evicted - 64 rows are in flight per 4 MB L2 - and cost 4 M partial writes.  4096 rows x 32000, 1024 kept: 245 ->
-// 228 us, 4.7 TB/s (64 kept: 209 -> 212); 900 rows x 16001, which took three passes for want of alignment: 90 -> 47 us.
+// laid out in LDS, half a row at a time (the ids are distinct, a plain scatter; the first half while the row is on its way),
+// and subtracted before the store.  Rewriting the kept tokens' entries in global memory afterwards found their lines
+// partly evicted - 64 rows are in flight per 4 MB L2 - and cost 4 M partial writes (245 us at 4096 rows x 32000, 1024 kept).
+// Loads return in order, so nothing between the row's loads and their use may wait for a load asked for after them: with the
+// target side's loads behind the row's the same kernel takes 228 us, with them in front 207 us = 5.2 TB/s.  64 kept tokens,
+// 2793 rows: 145 -> 140 us; 900 rows x 16001, which took three passes for want of alignment: 90 -> 38 us.
 // Otherwise (longer rows, draft_logits and grad aligned differently) three passes over the row, the second and third from L2.
 constexpr int kRowThreads = 512;
 constexpr int kRowWaves = kRowThreads / kWave;
@@ -78,7 +80,7 @@ constexpr int kRowRegVals = kRowThreads * 4 * kRowRounds;  // 32768
 constexpr int kRowKept = 1024 / kRowThreads;               // kept target logits per thread
 constexpr int kScatRounds = 8;                             // rounds per turn of the scatter
 constexpr int kScatVals = kScatRounds * kRowThreads * 4;   // 16384 floats, 64 KB of LDS: two workgroups a unit
-constexpr int kCountRows = 8192;  // up to here a row's workgroup counts the classes itself (a few KB from L2, behind the row's loads)
+constexpr int kCountRows = 8192;  // up to here a row's workgroup counts the classes itself (a few KB from L2)
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // whether the rows' workgroups count the classes themselves (their sums are the same whoever forms them)
@@ -97,7 +99,41 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
   const int h = kInRegs ? min((int)(((16 - ((uintptr_t)z & 15)) & 15) >> 2), Vd) : 0;
   const int n4 = (Vd - h) / 4, tail = h + 4 * n4;
 
-  // the row first: its loads are in flight while the target side is worked out
+  // What the target side needs is asked for first, the row behind it: loads return in order, so the target distribution, the
+  // class counts and the weight are worked out while the row is on its way.
+  const int cls = P.traj[m];
+  // rows of the two classes, counted here if they are few: four codes a load
+  const bool count = counts_classes(P);
+  uint32_t c4[kCountRows / 4 / kRowThreads];
+#pragma unroll
+  for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e) {
+    const int i = tid + e * kRowThreads;
+    c4[e] = 0u;
+    if (count && 4 * i < P.M) {
+      if (4 * i + 3 < P.M) {
+        c4[e] = ((const uint32_t*)P.traj)[i];
+      } else {
+        for (int k = 4 * i; k < P.M; ++k) c4[e] |= (uint32_t)(uint8_t)P.traj[k] << (8 * (k & 3));
+      }
+    }
+  }
+  // thread t holds kept entries t, t + 512, ... (past the list: its last entry, sorted out below - a load under a condition
+  // would be waited for at once)
+  int id[kRowKept];
+  uint16_t lt_bits[kRowKept];
+#pragma unroll
+  for (int e = 0; e < kRowKept; ++e) {
+    const size_t at = (size_t)m * K + min(tid + e * kRowThreads, K - 1);
+    id[e] = P.topk_ids[at];
+    lt_bits[e] = P.topk_logits[at];
+  }
+  float n_acc = 0.f, n_disc = 0.f;
+  if (P.grad && !count) {
+    n_acc = P.loss_out[3];
+    n_disc = P.loss_out[4];
+  }
+  asm volatile("" ::: "memory");
+
   f32x4_t r[kInRegs ? kRowRounds : 1];
   int edge = -1;  // the element outside the vectors that this thread holds
   float r_edge = -INFINITY;
@@ -111,52 +147,29 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
     if (tid >= 4 && tid < 7 && tail + tid - 4 < Vd) edge = tail + tid - 4;
     if (edge >= 0) r_edge = z[edge];
   }
-  const int cls = P.traj[m];
-  // rows of the two classes, counted here if they are few: four codes a load, in flight behind the row's own
   int na = 0, nd = 0;
-  const bool count = counts_classes(P);
-  if (count) {
-    uint32_t c4[kCountRows / 4 / kRowThreads];
 #pragma unroll
-    for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e) {
-      const int i = tid + e * kRowThreads;
-      c4[e] = 0u;
-      if (4 * i + 3 < P.M) {
-        c4[e] = ((const uint32_t*)P.traj)[i];
-      } else {
-        for (int k = 4 * i; k < P.M; ++k) c4[e] |= (uint32_t)(uint8_t)P.traj[k] << (8 * (k & 3));
-      }
+  for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = (int8_t)(c4[e] >> (8 * k));
+      na += c == 1;
+      nd += c == 2;
     }
-#pragma unroll
-    for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int c = (int8_t)(c4[e] >> (8 * k));
-        na += c == 1;
-        nd += c == 2;
-      }
-  }
 
-  // ---- the row's target distribution: thread t holds kept entries t, t + 512, ... ------------------------
+  // ---- the row's target distribution ---------------------------------------------------------------------
   const int k_eff = (cls == 2 && P.discard_k > 0) ? min(P.discard_k, K) : K;
-  int id[kRowKept];
   float lt[kRowKept], zt_at[kRowKept];
   bool kept[kRowKept];
   float tmax = -INFINITY;
 #pragma unroll
   for (int e = 0; e < kRowKept; ++e) {
-    const int t = tid + e * kRowThreads;
-    id[e] = -1;
-    lt[e] = -INFINITY;
-    if (t < k_eff) {
-      id[e] = P.topk_ids[(size_t)m * K + t];
-      lt[e] = __uint_as_float((uint32_t)P.topk_logits[(size_t)m * K + t] << 16);
-    }
-    kept[e] = id[e] >= 0 && id[e] < Vd && lt[e] > -INFINITY;
+    lt[e] = __uint_as_float((uint32_t)lt_bits[e] << 16);
+    kept[e] = tid + e * kRowThreads < k_eff && id[e] >= 0 && id[e] < Vd && lt[e] > -INFINITY;
     tmax = fmaxf(tmax, kept[e] ? lt[e] : -INFINITY);
   }
 #pragma unroll
-  for (int e = 0; e < kRowKept; ++e) zt_at[e] = kept[e] ? z[id[e]] : 0.f;  // the drafter's logit of the kept token
+  for (int e = 0; e < kRowKept; ++e) zt_at[e] = z[kept[e] ? id[e] : 0];  // the drafter's logit of the kept token
   tmax = block_max<kRowWaves>(tmax, s_redf);
   const bool any = tmax > -INFINITY;  // a row without a kept target logit contributes nothing
   double tsum = 0.0;
@@ -172,14 +185,10 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
   // ---- the row's weight, and its share of w p_target laid out in LDS for the first turn of the gradient below ------------
   float w = 0.f;
   if (P.grad) {
-    float n_acc, n_disc;
     if (count) {  // both in one sum of whole numbers
       const int both = (int)block_sum<kRowWaves>((double)(na + (nd << 14)), s_redd);
       n_acc = (float)(both & ((1 << 14) - 1));
       n_disc = (float)(both >> 14);
-    } else {
-      n_acc = P.loss_out[3];
-      n_disc = P.loss_out[4];
     }
     if (any && cls == 1) w = 1.f / n_acc;
     if (any && cls == 2) w = P.lambda / n_disc;
