@@ -61,7 +61,7 @@ hipError_t launch_attn_plan(const int32_t* seq_lens, int B, int Hkv, int32_t* PB
 constexpr int kNarrowPar = 4;  // tiles of a run that the narrow kernel's wavefronts take at a time
 constexpr int kWidePar = 2;    // ... the wide kernel's two tile-parity groups
 
-// kFp8KV: kp_ / vp_ hold E4M3 codes and k_scale / v_scale [Hkv] their per-head scales ; they too go straight into LDS and are
+// kFp8KV: kp_ / vp_ hold E4M3 codes and k_scale / v_scale [Hkv] their per-head scales; they too go straight into LDS and are
 // widened between the LDS read and the matrix instruction (see attn_tile.hpp).  Staged through registers and widened into
 // LDS the sweep of 32 requests of 1K-4K tokens took 53 us (the loads in flight, the accumulators and the conversions did not
 // fit into 256 registers: every tile waited for spill traffic behind its loads); with codes in LDS 37 us, 4.2 TB/s.
