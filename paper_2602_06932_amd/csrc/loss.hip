@@ -30,14 +30,19 @@ __device__ __forceinline__ float block_max(float v, float* s_red) {
   return r;
 }
 
-template <int kWaves = kLossWaves>
-__device__ __forceinline__ double block_sum(double v, double* s_red) {
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  return v;
+}
+template <int kWaves = kLossWaves, typename T>
+__device__ __forceinline__ T block_sum(T v, T* s_red) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   __syncthreads();
   if (lane == 0) s_red[wv] = v;
   __syncthreads();
-  double r = 0.0;
+  T r = 0;
 #pragma unroll
   for (int i = 0; i < kWaves; ++i) r += s_red[i];  // fixed order
   return r;
@@ -328,19 +333,20 @@ __global__ __launch_bounds__(kLossThreads) void loss_reduce_kernel(const float* 
                                                                     const int8_t* __restrict__ traj, int M, float lambda,
                                                                     float* __restrict__ loss_out) {
   __shared__ double s_red[kLossWaves];
-  double sa = 0.0, sd = 0.0, both = 0.0;  // both counts in one sum of whole numbers
-  constexpr double kStep = 4294967296.0;
+  __shared__ unsigned long long s_cnt[kLossWaves];
+  double sa = 0.0, sd = 0.0;
+  unsigned long long both = 0;  // accepted rows below, discarded rows from bit 32 on (M < 2^31: neither reaches the other)
   for (int m = threadIdx.x; m < M; m += kLossThreads) {
     const int c = traj[m];
     const double x = (double)row_kl[m];
-    if (c == 1) { sa += x; both += 1.0; }
-    if (c == 2) { sd += x; both += kStep; }
+    if (c == 1) { sa += x; both += 1ull; }
+    if (c == 2) { sd += x; both += 1ull << 32; }
   }
   sa = block_sum(sa, s_red);
   sd = block_sum(sd, s_red);
-  both = block_sum(both, s_red);
+  both = block_sum(both, s_cnt);
   if (threadIdx.x == 0) {
-    const double nd = floor(both / kStep), na = both - nd * kStep;
+    const double na = (double)(both & 0xffffffffull), nd = (double)(both >> 32);
     loss_out[3] = (float)na;
     loss_out[4] = (float)nd;
     const double ma = na > 0 ? sa / na : 0.0, md = nd > 0 ? sd / nd : 0.0;

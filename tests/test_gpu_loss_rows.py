@@ -35,3 +35,38 @@ def test_rows_of_any_alignment_and_length(gpu_lib, rows, vd, k):
     assert (np.abs(kl.cpu().numpy() - ref["row_kl"]) <= 2e-5 + 1e-5 * np.abs(ref["row_kl"])).all()
     assert loss[3].item() == ref["n_accept"] and loss[4].item() == ref["n_discard"]
     assert abs(loss[0].item() - ref["loss"]) <= 2e-5 * max(1.0, abs(ref["loss"]))
+
+
+def _many_rows(gpu_lib, rows, accepted, unused, want_grad):
+    """`rows` rows, eight prototypes over and over: `accepted` of them accepted, `unused` unused, the rest discarded."""
+    av = gpu_lib
+    z, ids, bits, _ = gen.loss_inputs(3, 8, 8, top_k=4)
+    reps = -(-rows // 8)
+    traj = torch.full((rows,), 2, dtype=torch.int8, device="cuda")
+    traj[accepted] = 1
+    traj[unused] = 0
+    dev = [torch.from_numpy(a).cuda().repeat(reps, 1)[:rows] for a in (z, ids, bits.view(np.int16))]
+    kl, loss = torch.empty(rows, device="cuda"), torch.empty(5, device="cuda")
+    grad = torch.full((rows, 8), float("nan"), device="cuda") if want_grad else None
+    d = av.aurora_loss_desc(rows=rows, draft_vocab=8, top_k=4, discard_top_k=0, lambda_discard=0.5)
+    print(f"[case] rows={rows} grad={want_grad}", flush=True)
+    av.aurora_draft_loss(d, *dev, traj, kl, loss, grad)
+    torch.cuda.synchronize()
+    # the oracle on the prototypes, each in either class (no discard filter: a row's KL does not depend on its class)
+    per_row = oracle.draft_loss(z, ids, bits, np.ones(8, np.int8), 0.5)["row_kl"]
+    n_a, n_d = len(accepted), rows - len(accepted) - len(unused)
+    count = np.bincount(np.arange(rows) % 8, minlength=8).astype(np.float64)
+    gone = np.bincount(np.array(accepted + unused, np.int64) % 8, minlength=8)
+    mean_a = float(np.mean([per_row[i % 8] for i in accepted]))
+    mean_d = float((per_row * (count - gone)).sum() / n_d)
+    assert loss[3].item() == np.float32(n_a) and loss[4].item() == np.float32(n_d)
+    for got, want in ((loss[0], mean_a + 0.5 * mean_d), (loss[1], mean_a), (loss[2], mean_d)):
+        assert abs(got.item() - want) <= 2e-5 + 1e-5 * abs(want)
+    return per_row, traj, kl, grad, n_a, n_d
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,n_accept,want_grad", [(2_200_000, 1, False), (2_200_000, 1, True), (4_300_000, 5, False)])
+def test_class_counts_of_millions_of_rows(gpu_lib, rows, n_accept, want_grad):
+    """Both class counts are exact whatever the number of discarded rows (their sum is a whole number of up to 62 bits)."""
+    _many_rows(gpu_lib, rows, [7 + 411_111 * i for i in range(n_accept)], [5, rows - 1], want_grad)
