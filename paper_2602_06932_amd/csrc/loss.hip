@@ -85,6 +85,7 @@ constexpr int kRowRegVals = kRowThreads * 4 * kRowRounds;  // 32768
 constexpr int kRowKept = 1024 / kRowThreads;               // kept target logits per thread
 constexpr int kScatRounds = 8;                             // rounds per turn of the scatter
 constexpr int kScatVals = kScatRounds * kRowThreads * 4;   // 16384 floats, 64 KB of LDS: two workgroups a unit
+constexpr int kGridRows = 1 << 22;  // rows along the grid's first dimension: fewer than 2^32 threads; the rest along the second
 constexpr int kCountRows = 8192;  // up to here a row's workgroup counts the classes itself (a few KB from L2)
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
@@ -97,7 +98,10 @@ template <bool kInRegs>
 __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel(LossLaunch P) {
   __shared__ float s_redf[kRowWaves];
   __shared__ double s_redd[kRowWaves];
-  const int m = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
+  const long long row = (long long)blockIdx.y * kGridRows + blockIdx.x;
+  if (row >= P.M) return;  // the whole workgroup
+  const int m = (int)row;
   const int Vd = P.Vd, K = P.K;
   const float* z = P.draft_logits + (size_t)m * Vd;
   // elements before the first 16-byte boundary, vectors, and the first element after them (in registers only)
@@ -368,10 +372,11 @@ hipError_t launch_draft_loss(const LossLaunch& P, hipStream_t st) {
   if (P.M > 0) {
     // rows and gradient rows have to start at the same place within 16 bytes
     const bool in_regs = P.Vd >= 8 && P.Vd <= kRowRegVals && (!P.grad || (((uintptr_t)P.grad ^ (uintptr_t)P.draft_logits) & 15) == 0);
+    const dim3 grid(P.M < kGridRows ? P.M : kGridRows, (P.M - 1) / kGridRows + 1);
     if (in_regs)
-      hipLaunchKernelGGL(loss_rows_kernel<true>, dim3(P.M), dim3(kRowThreads), 0, st, P);
+      hipLaunchKernelGGL(loss_rows_kernel<true>, grid, dim3(kRowThreads), 0, st, P);
     else
-      hipLaunchKernelGGL(loss_rows_kernel<false>, dim3(P.M), dim3(kRowThreads), 0, st, P);
+      hipLaunchKernelGGL(loss_rows_kernel<false>, grid, dim3(kRowThreads), 0, st, P);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -70,3 +70,20 @@ def _many_rows(gpu_lib, rows, accepted, unused, want_grad):
 def test_class_counts_of_millions_of_rows(gpu_lib, rows, n_accept, want_grad):
     """Both class counts are exact whatever the number of discarded rows (their sum is a whole number of up to 62 bits)."""
     _many_rows(gpu_lib, rows, [7 + 411_111 * i for i in range(n_accept)], [5, rows - 1], want_grad)
+
+
+@pytest.mark.gpu
+def test_more_rows_than_one_grid_dimension_holds(gpu_lib):
+    """A grid dimension takes fewer than 2^32 threads: above 2^23 rows of 512 threads the rows run on in a second one."""
+    rows = (1 << 23) + 1037
+    per_row, traj, kl, grad, n_a, n_d = _many_rows(gpu_lib, rows, [11, (1 << 22) + 3, rows - 2], [5, rows - 1], True)
+    at = torch.arange(rows, device="cuda") % 8
+    want = torch.tensor(per_row, device="cuda")[at]
+    assert ((kl.double() - want).abs() <= 2e-5 + 1e-5 * want.abs()).all()
+    assert torch.isfinite(grad).all() and (grad[5] == 0).all() and (grad[rows - 1] == 0).all()
+    # equal rows of a class have equal gradients, bit for bit
+    first = torch.full((8,), -1, device="cuda")
+    for i in range(8, 16):
+        first[i % 8] = i if traj[i] == 2 else i + 8
+    same = (grad == grad[first[at]]).all(1) | (traj != 2)
+    assert same.all()
