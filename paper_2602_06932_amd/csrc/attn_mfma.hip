@@ -286,6 +286,7 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
         const int dd = 32 * (db & 1) + 8 * g + 4 * lh;  // column within the 64-wide half
         f32x4_t o = {o_acc[db][4 * g] * f_own, o_acc[db][4 * g + 1] * f_own, o_acc[db][4 * g + 2] * f_own,
                      o_acc[db][4 * g + 3] * f_own};
+        if (m_run == -INFINITY) o = f32x4_t{0.f, 0.f, 0.f, 0.f};  // nothing visible: 0 x infinity must not get in
         // rotate the 16-byte slot by the row so that the 32 rows of a column group spread over banks
         *(f32x4_t*)(obuf + li * 64 + ((dd / 4 + li) & 15) * 4) = o;
       }
@@ -566,8 +567,13 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x16_t& src = grp == 0 ? st.o[db] : st.o[2 + db];
-          const f32x4_t own = {src[4 * g], src[4 * g + 1], src[4 * g + 2], src[4 * g + 3]};
-          const f32x4_t o = own * (f_own * vs) + take[(db * 4 + g) * kWave] * (f_oth * vs);
+          // (a group in whose tiles the row saw nothing counts for nothing, also where its sums are 0 x infinity)
+          const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+          f32x4_t own = {src[4 * g], src[4 * g + 1], src[4 * g + 2], src[4 * g + 3]};
+          f32x4_t oth = take[(db * 4 + g) * kWave];
+          if (m_own == -INFINITY) own = z;
+          if (m_oth == -INFINITY) oth = z;
+          const f32x4_t o = own * (f_own * vs) + oth * (f_oth * vs);
           *(f32x4_t*)(part_o + prow * kAtD + 32 * (2 * grp + db) + 8 * g + 4 * lh) = o;
         }
       if (grp == 0 && lh == 0) {
@@ -641,8 +647,9 @@ __global__ __launch_bounds__(32 * kCombineGroups) void attn_mfma_combine(const f
       den *= fo;
 #pragma unroll
       for (int i = 0; i < kU; ++i) {
-        const float fn = __expf(ms[i] - nm);  // a partial with nothing visible: exp(-inf) = 0, and its sums are zeros
-        num += os[i] * fn;
+        // a partial with nothing visible is left out: its factor is exp(-inf) = 0, but its sums may be 0 x infinity
+        const float fn = __expf(ms[i] - nm);
+        if (ms[i] > -INFINITY) num += os[i] * fn;
         den += ls[i] * fn;
       }
       M = nm;

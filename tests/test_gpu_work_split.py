@@ -34,6 +34,32 @@ def test_attention_of_few_tiles(gpu_lib, batch, context, nodes, hkv, kv8):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("num_q,tiles,batch", [(8, 1, 1), (8, 4, 1), (8, 5, 3), (8, 87, 1), (8, 10, 12), (32, 1, 1), (32, 4, 1), (32, 5, 2),
+                                               (32, 86, 1), (32, 5, 12)])
+def test_infinities_at_nodes_a_row_does_not_see(gpu_lib, num_q, tiles, batch, kv8):
+    """The last tile of 32 tokens holds only the later nodes of the chunk, and the last of them has infinities (NaN codes in an
+    8-bit cache) in K and V: rows that see nothing of that tile come out as if it were not there.  (So few tiles that no wavefront
+    multiplies another tile into the same sums; where one does, the product's 0 x infinity stays in them.)"""
+    from paper_2602_06932_amd.device import DeviceVerify
+    from parity_util import check_attention
+    first = {8: 4, 32: 16}[num_q]  # the first node in the last tile
+    length = 32 * tiles + num_q - first
+    w = gen.llama_chain(300 + batch + length, len_lo=length, len_hi=length, num_q=num_q, batch=batch, vocab=64, hidden_size=64,
+                        num_q_heads=8, num_kv_heads=2, kv_fp8=kv8)
+    assert (w.seq_lens == length).all()
+    ref = oracle.attn_workload(w)
+    dv = DeviceVerify(w)
+    at = (length - 1) // w.page_size
+    for pool in (dv.k_pages, dv.v_pages):
+        for b in range(batch):
+            pool[int(w.block_table[b, at]), :, (length - 1) % w.page_size, :] = 0x7F if kv8 else float("inf")
+    dv.attn()
+    torch.cuda.synchronize()
+    check_attention(dv.attn_out_host()[:, :first], ref[:, :first], w.dtype)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("batch,context,nodes", [(1, 40, 0), (1, 1500, 0), (1, 1500, 12), (1, 1500, 32), (5, 333, 32)])
 def test_backward_of_few_tiles(gpu_lib, batch, context, nodes):
     from test_gpu_attn_bwd import _check
