@@ -4,8 +4,8 @@
 //
 // The KV sweep is cut into 32-token tiles of one (request, KV head) pair; the tiles of the whole batch,
 // numbered request-major, are dealt out in equal contiguous runs to a fixed number of resident
-// workgroups (two per compute unit), whatever the mix of sequence lengths.  A workgroup's run meets
-// one or a few pairs; for each it produces one partial (m, l, O) - a "segment" - that a small merge
+// workgroups (two per compute unit), whatever the mix of sequence lengths - over few tokens (build_split in
+// attn_tile.hpp) a workgroup takes a few tiles of one pair.  A workgroup's run meets one or a few pairs; for each it produces one partial (m, l, O) - a "segment" - that a small merge
 // kernel folds.  The G*Nq query rows that share a KV head form the 32-wide N side of
 // v_mfma_f32_32x32x16_bf16, so a KV byte is read once for the whole GQA group.  Inside a segment the
 // four wavefronts are independent: wavefront w owns every 4th tile, with private LDS buffers, a
@@ -23,6 +23,8 @@
 // O += P V(t), so HBM requests stay in flight through the softmax and MFMA phases.
 #include "launch.hpp"
 #include "attn_tile.hpp"
+
+#include <algorithm>
 
 namespace aurora {
 
@@ -58,6 +60,11 @@ hipError_t launch_attn_plan(const int32_t* seq_lens, int B, int Hkv, int32_t* PB
   return hipGetLastError();
 }
 
+// The split for the merge kernel: the prefix of tiles as it is, the prefix of runs as complements (negative numbers).
+__device__ __forceinline__ void publish_split(int32_t* __restrict__ PB, const int* s_pb, int B, bool by_run, int threads) {
+  for (int i = threadIdx.x; i <= B; i += threads) PB[i] = by_run ? ~s_pb[i] : s_pb[i];
+}
+
 constexpr int kNarrowPar = 4;  // tiles of a run that the narrow kernel's wavefronts take at a time
 constexpr int kWidePar = 2;    // ... the wide kernel's two tile-parity groups
 
@@ -83,22 +90,20 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
   __shared__ float s_l[4][32];
 
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
-  __shared__ int s_wsum[4];
+  __shared__ int2 s_wsum[4];
   __shared__ int s_par[kMaxNq];  // the request's tree: the ancestor walk is a chain of dependent reads
+  bool by_run = false;
   if (kLocalPlan) {
-    // every workgroup builds the prefix itself; workgroup (0,0) also publishes it for the merge kernel
-    build_prefix(seq_lens, B, Hkv, s_pb, s_wsum);
-    if (blockIdx.x == 0 && blockIdx.y == 0)
-      for (int i = threadIdx.x; i <= B; i += kAtThreads) PB[i] = s_pb[i];
+    // every workgroup builds the split itself; workgroup (0,0) also publishes it for the merge kernel
+    by_run = build_split<kAtThreads, kNarrowPar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
+    if (blockIdx.x == 0 && blockIdx.y == 0) publish_split(PB, s_pb, B, by_run, kAtThreads);
   }
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
   const int rt = blockIdx.y, row_tiles = gridDim.y;
-  const int U = pbv(B);
-  const int wgs = active_wgs(U, gridDim.x, kNarrowPar);
-  if ((int)blockIdx.x >= wgs) return;
-  int u = unit_begin(U, wgs, blockIdx.x);
-  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
+  const int U = pbv(B);  // units: runs, or tiles
+  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
+  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv;
@@ -137,11 +142,13 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
     const int L = seq_lens[b];
     const int n_b = (L + kAtTile - 1) / kAtTile;
     const int rel = u - pbv(b);
-    const int hk = __builtin_amdgcn_readfirstlane(rel / n_b);
-    const int t0 = rel - hk * n_b;
-    const int t1 = min(n_b, t0 + (u_end - u));
+    const int per_pair = by_run ? (n_b + kNarrowPar - 1) / kNarrowPar : n_b;
+    const int hk = __builtin_amdgcn_readfirstlane(rel / per_pair);
+    const int at = rel - hk * per_pair;
+    const int t0 = by_run ? at * kNarrowPar : at;
+    const int t1 = min(n_b, t0 + (by_run ? kNarrowPar : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;  // segments are a monotone path in (workgroup, pair): unique
-    u += t1 - t0;
+    u += by_run ? 1 : t1 - t0;
 
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
@@ -348,47 +355,19 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
   char* qall = wlds;
   char* ring = wlds + kWideQBytes;
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
-  __shared__ int s_wsum[kWideThreads / kWave];
+  __shared__ int2 s_wsum[kWideThreads / kWave];
   __shared__ int s_par[kMaxNq];
   __shared__ float s_ml[2][4][2][32];  // (m, l) of the rows of each parity group's query tiles
+  bool by_run = false;
   if (kLocalPlan) {
-    // as build_prefix, for 512 threads (threads 256.. own requests beyond 1024: none)
-    {
-      const int t4 = threadIdx.x * 4;
-      int un[4], loc = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        un[i] = t4 + i < B ? ((seq_lens[t4 + i] + kAtTile - 1) / kAtTile) * Hkv : 0;
-        loc += un[i];
-      }
-      int incl = loc;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(incl, o, kWave);
-        if ((int)(threadIdx.x & 63) >= o) incl += y;
-      }
-      if ((threadIdx.x & 63) == 63) s_wsum[threadIdx.x >> 6] = incl;
-      __syncthreads();
-      int run = incl - loc;
-      for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) run += s_wsum[w];
-      if (threadIdx.x == 0) s_pb[0] = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        run += un[i];
-        if (t4 + i < B) s_pb[t4 + i + 1] = run;
-      }
-      __syncthreads();
-    }
-    if (blockIdx.x == 0 && blockIdx.y == 0)
-      for (int i = threadIdx.x; i <= B; i += kWideThreads) PB[i] = s_pb[i];
+    by_run = build_split<kWideThreads, kWidePar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
+    if (blockIdx.x == 0 && blockIdx.y == 0) publish_split(PB, s_pb, B, by_run, kWideThreads);
   }
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
-  const int U = pbv(B);
-  const int wgs = active_wgs(U, gridDim.x, kWidePar);
-  if ((int)blockIdx.x >= wgs) return;
-  int u = unit_begin(U, wgs, blockIdx.x);
-  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
+  const int U = pbv(B);  // units: runs, or tiles
+  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
+  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv;
@@ -421,11 +400,13 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
     const int L = seq_lens[b];
     const int n_b = (L + kAtTile - 1) / kAtTile;
     const int rel = u - pbv(b);
-    const int hk = __builtin_amdgcn_readfirstlane(rel / n_b);
-    const int t0 = rel - hk * n_b;
-    const int t1 = min(n_b, t0 + (u_end - u));
+    const int per_pair = by_run ? (n_b + kWidePar - 1) / kWidePar : n_b;
+    const int hk = __builtin_amdgcn_readfirstlane(rel / per_pair);
+    const int at = rel - hk * per_pair;
+    const int t0 = by_run ? at * kWidePar : at;
+    const int t1 = min(n_b, t0 + (by_run ? kWidePar : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;
-    u += t1 - t0;
+    u += by_run ? 1 : t1 - t0;
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
@@ -589,8 +570,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
 // (request, KV head) pair sit in slots w + pair for the workgroups w whose unit range meets the pair's.
 // Thirty-two threads (four output columns each) fold a run of a row's partials, a few at a time: the merge is a short
 // chain of dependent loads, so what counts is how many loads are in flight.  A row is given to kSplit such groups of
-// threads, whose results meet in LDS; a workgroup is eight groups.  One request of 2777 tokens (22 partials a row; 64 before
-// active_wgs): 27 us one row per group, four partials at a time -> 4.1 us with kSplit = 8.
+// threads, whose results meet in LDS; a workgroup is eight groups.  One request of 2777 tokens: 27 us with 64
+// partials a row, one row per group and four partials at a time -> 4.1 us with 22 partials, one per run, and kSplit = 8.
 constexpr int kCombineGroups = 8;
 template <int kSplit>
 __global__ __launch_bounds__(32 * kCombineGroups) void attn_mfma_combine(const float* __restrict__ part_o,
@@ -598,7 +579,7 @@ __global__ __launch_bounds__(32 * kCombineGroups) void attn_mfma_combine(const f
                                                                          const int32_t* __restrict__ seq_lens,
                                                                          const int32_t* __restrict__ PB,
                                                                          bf16_t* __restrict__ out, int B, int Nq, int Hq,
-                                                                         int Hkv, int wgs_launched, int row_tiles,
+                                                                         int Hkv, int wgs, int row_tiles,
                                                                          int par, float* __restrict__ lse_out) {
   const int grp = threadIdx.x >> 5, sub = grp % kSplit;
   const int b = blockIdx.x / Nq, n = blockIdx.x - b * Nq;
@@ -615,13 +596,16 @@ __global__ __launch_bounds__(32 * kCombineGroups) void attn_mfma_combine(const f
     const int mrow = n * G + hq - hk * G;
     const int rt = mrow >> 5, li = mrow & 31;
     const int n_b = (seq_lens[b] + kAtTile - 1) / kAtTile;
-    const int U = PB[B];
-    const int u0 = PB[b] + hk * n_b, u1 = u0 + n_b;
-    const int wgs = active_wgs(U, wgs_launched, par);
-    // (a sequence of length 0 has no unit and no partial: w1 < w0, nothing is merged and the row comes out as zeros)
-    const int w0 = n_b > 0 ? unit_owner(U, wgs, u0) : 0, w1 = n_b > 0 ? unit_owner(U, wgs, u1 - 1) : -1;
+    const int U = PB[B], first = PB[b];
+    int w0 = 0, np = 0;  // (a sequence of length 0 has no partial: nothing is merged and the row comes out as zeros)
+    if (U < 0) {         // runs, one per workgroup
+      np = (n_b + par - 1) / par;
+      w0 = ~first + hk * np;
+    } else if (n_b > 0) {
+      w0 = unit_owner(U, wgs, first + hk * n_b);
+      np = unit_owner(U, wgs, first + hk * n_b + n_b - 1) - w0 + 1;
+    }
     const int pair = b * Hkv + hk;
-    const int np = w1 - w0 + 1;
     const int per = (np + kSplit - 1) / kSplit;
     const int p_end = min(np, (sub + 1) * per);
     const size_t prow0 = ((size_t)(w0 + pair) * row_tiles + rt) * 32 + li;
@@ -744,10 +728,12 @@ hipError_t launch_attn_mfma(const AttnLaunch& a, hipStream_t st) {
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // Partials of a row if the requests are about equally long.  From a dozen on, splitting a row over all groups of a
-  // workgroup shortens the chain (4.1 against 13 us at 22 partials); below it the eight times as many workgroups cost more
-  // than the one or two rounds of loads they save (4096 rows of nine partials: 13.0 split, 6.9 whole).
-  const int per_row = wgs / (a.B * a.Hkv) + 1;
+  // Partials of a row if the requests are about equally long, and at most one per run of the longest that fits the block table.
+  // From a dozen on, splitting a row over all groups of a workgroup shortens the chain (4.1 against 13 us at 22 partials);
+  // below it the eight times as many workgroups cost more than the one or two rounds of loads they save (4096 rows of nine
+  // partials: 13.0 split, 6.9 whole).
+  const int64_t most = ((int64_t)a.max_pages * a.page + kAtTile - 1) / kAtTile / (row_tiles == 1 ? kNarrowPar : kWidePar) + 2;
+  const int per_row = (int)std::min<int64_t>(wgs / (a.B * a.Hkv) + 1, most);
   if (per_row >= 12) launch_combine<8>(a, st, wgs, row_tiles);
   else launch_combine<1>(a, st, wgs, row_tiles);
   return hipGetLastError();

@@ -37,7 +37,7 @@ __device__ __forceinline__ void load_to_lds_16(const void* gptr, const void* lds
     asm volatile("" ::: "memory");                                                                 \
   } while (0)
 
-// Workgroups of a sweep that get units: all `wgs` launched ones, or so few that a run still gives each of the
+// Workgroups of a backward sweep that get units: all `wgs` launched ones, or so few that a run still gives each of the
 // `par` wavefront groups that share a run a tile.  Shorter runs would leave wavefronts idle without ending any sooner, and
 // every run adds a partial per query row to the merge.  The sweep and the merge kernel evaluate this alike.
 __device__ __forceinline__ int active_wgs(int U, int wgs, int par) {
@@ -332,6 +332,56 @@ __device__ __forceinline__ void build_prefix(const int32_t* __restrict__ seq_len
     if (t4 + i < B) s_pb[t4 + i + 1] = run;
   }
   __syncthreads();
+}
+
+// The split of a forward sweep over few tokens, built by the whole workgroup (kThreads threads, B <= 1024).  If the pairs'
+// tiles, cut into runs of kPar (one for each wavefront group that works at a time; a pair's last run may be shorter), are
+// no more runs than there are workgroups, a workgroup takes one run: s_pb[0 .. B] is the prefix of runs per request and
+// the function returns true.  Otherwise s_pb is the prefix of tiles, which are dealt out evenly (unit_begin).
+// Runs of one pair each: a run that crosses from pair to pair pays a segment's fixed cost (query rows, first tiles, merge of the
+// wavefronts: 3 to 4 us) for each in turn.  Shorter runs than kPar would leave wavefronts idle without ending any sooner, and
+// every run adds a partial per query row to the merge.  32 query heads over 8 KV heads, five rows, us for sweep and merge with
+// [tiles dealt out evenly to all workgroups; to as many as get kPar tiles each; one run each]: 1 request of 16 tokens 10.8, 21.8,
+// 10.4; 8 of 64 tokens 11.8, 15.5, 11.4; 7 of 20 to 400 tokens 17.2, 22.8, 12.1; 4 of 1000 tokens 19.5, 14.7, 14.4.
+template <int kThreads, int kPar>
+__device__ __forceinline__ bool build_split(const int32_t* __restrict__ seq_lens, int B, int Hkv, int workgroups, int* s_pb,
+                                            int2* s_wsum) {
+  const int t4 = threadIdx.x * 4, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int tiles[4], runs[4], nt = 0, nr = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int n = t4 + i < B ? (seq_lens[t4 + i] + kAtTile - 1) / kAtTile : 0;
+    tiles[i] = n * Hkv;
+    runs[i] = (n + kPar - 1) / kPar * Hkv;
+    nt += tiles[i];
+    nr += runs[i];
+  }
+  int it = nt, ir = nr;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int yt = __shfl_up(it, o, kWave), yr = __shfl_up(ir, o, kWave);
+    if (lane >= o) { it += yt; ir += yr; }
+  }
+  if (lane == 63) s_wsum[wave] = make_int2(it, ir);
+  __syncthreads();
+  int at_tile = it - nt, at_run = ir - nr, all_runs = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / kWave; ++w) {
+    const int2 x = s_wsum[w];
+    all_runs += x.y;
+    at_tile += w < wave ? x.x : 0;
+    at_run += w < wave ? x.y : 0;
+  }
+  const bool by_run = all_runs <= workgroups;
+  int at = by_run ? at_run : at_tile;
+  if (threadIdx.x == 0) s_pb[0] = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    at += by_run ? runs[i] : tiles[i];
+    if (t4 + i < B) s_pb[t4 + i + 1] = at;
+  }
+  __syncthreads();
+  return by_run;
 }
 
 constexpr int kLocalPlanMax = 1024;  // up to this many requests every workgroup builds the prefix itself

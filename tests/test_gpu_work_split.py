@@ -1,6 +1,6 @@
-"""How the work is split, where a split changes: attention batches of so few tiles that only some workgroups get any and a row's
-partials are merged by several groups of threads (and the first sizes past either), their backward, and tree walks whose slices
-are held in registers or not.  Against the float64 oracle, at the tolerances of parity_util."""
+"""How the work is split, where a split changes: attention batches of so few tiles that every workgroup takes one run of one
+pair and a row's partials are merged by several groups of threads (and the first sizes past either), their backward, and tree
+walks whose slices are held in registers or not.  Against the float64 oracle, at the tolerances of parity_util."""
 import numpy as np
 import pytest
 
@@ -21,7 +21,10 @@ def _workload(batch, context, nodes, kv8, hq=8, hkv=2):
 @pytest.mark.parametrize("kv8", [False, True])
 @pytest.mark.parametrize("batch,context,nodes,hkv", [(1, 5, 0, 2), (1, 33, 0, 2), (1, 700, 0, 1), (1, 2777, 0, 2), (3, 1500, 7, 2),
                                                      (12, 300, 0, 2), (24, 200, 0, 2), (1, 40, 24, 1), (1, 2777, 32, 2),
-                                                     (9, 500, 32, 2), (2, 900, 61, 2)])
+                                                     (9, 500, 32, 2), (2, 900, 61, 2),
+                                                     # as many runs as workgroups, and one request more
+                                                     (256, 40, 0, 2), (257, 40, 0, 2), (128, 60, 24, 2), (129, 60, 24, 2),
+                                                     (40, 400, 0, 2), (16, 300, 24, 1)])
 def test_attention_of_few_tiles(gpu_lib, batch, context, nodes, hkv, kv8):
     from paper_2602_06932_amd.device import DeviceVerify
     from parity_util import check_attention
