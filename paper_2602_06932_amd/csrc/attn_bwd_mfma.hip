@@ -149,21 +149,19 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
   char* doV = bm_lds + kRT * kAtTileBytes;    // their upstream gradients
   char* waves = bm_lds + 2 * kRT * kAtTileBytes;
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
-  __shared__ int s_wsum[4];
+  __shared__ int2 s_wsum[kBmThreads / kWave];
   __shared__ int s_par[kMaxNq];  // the request's tree: the ancestor walk is a chain of dependent reads
   __shared__ float s_delta[32 * kRT];  // delta_i = <dO_i, O_i> of the pair's query rows, formed while they are staged
+  bool by_run = false;
   if (kLocalPlan) {
-    build_prefix(seq_lens, B, Hkv, s_pb, s_wsum);
-    if (blockIdx.x == 0)
-      for (int i = threadIdx.x; i <= B; i += kBmThreads) PB[i] = s_pb[i];
+    by_run = build_split<kBmThreads, kBmPar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
+    if (blockIdx.x == 0) publish_split(PB, s_pb, B, by_run, kBmThreads);
   }
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
-  const int U = pbv(B);
-  const int wgs = active_wgs(U, gridDim.x, kBmPar);
-  if ((int)blockIdx.x >= wgs) return;
-  int u = unit_begin(U, wgs, blockIdx.x);
-  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
+  const int U = pbv(B);  // units: runs, or tiles
+  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
+  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv, R = G * Nq;
@@ -191,11 +189,13 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
     const int L = seq_lens[b];
     const int n_b = (L + kAtTile - 1) / kAtTile;
     const int rel = u - pbv(b);
-    const int hk = __builtin_amdgcn_readfirstlane(rel / n_b);
-    const int t0 = rel - hk * n_b;
-    const int t1 = min(n_b, t0 + (u_end - u));
+    const int per_pair = by_run ? (n_b + kBmPar - 1) / kBmPar : n_b;
+    const int hk = __builtin_amdgcn_readfirstlane(rel / per_pair);
+    const int at = rel - hk * per_pair;
+    const int t0 = by_run ? at * kBmPar : at;
+    const int t1 = min(n_b, t0 + (by_run ? kBmPar : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;
-    u += t1 - t0;
+    u += by_run ? 1 : t1 - t0;
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
@@ -210,15 +210,6 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
 #pragma unroll
       for (int j = 0; j < 8; ++j) issue_rows<true>(pool, buf, j, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
     };
-    // this wavefront's first tile is on its way while the query rows are staged
-    int tt = wv;
-    int pa = 0, pb = 0;
-    if (tt < ntile) {
-      tile_pages(tt, pa, pb);
-      issue_tile(kp, kbuf, tt, pa, pb);
-      issue_tile(vp, vbuf, tt, pa, pb);
-    }
-
     // the pair's query rows and their upstream gradients: group row m = n * G + g <-> (node n, head hk * G + g);
     // 8 threads per row, 32 bytes each, 32 rows per turn
 #pragma unroll
@@ -273,6 +264,13 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
         for (int r = 0; r < 16; ++r) dq_acc[rt][db][r] = 0.f;
 
     __syncthreads();  // query rows staged
+    int tt = wv;
+    int pa = 0, pb = 0;
+    if (tt < ntile) {
+      tile_pages(tt, pa, pb);
+      issue_tile(kp, kbuf, tt, pa, pb);
+      issue_tile(vp, vbuf, tt, pa, pb);
+    }
 #pragma unroll
     for (int rt = 0; rt < kRT; ++rt) {
       const int m = 32 * rt + li;
@@ -432,21 +430,19 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
   char* kv = bm_lds + 8 * kAtTileBytes;     // three K / V tile pairs
   char* xt = kv + 3 * kBsKvBytes;           // per group: four transposed (P, dS) tiles
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
-  __shared__ int s_wsum[8];
+  __shared__ int2 s_wsum[kB8Threads / kWave];
   __shared__ int s_par[kMaxNq];    // the request's tree: the ancestor walk is a chain of dependent reads
   __shared__ float s_delta[128];  // delta_i = <dO_i, O_i> of the pair's query rows, formed while they are staged
+  bool by_run = false;
   if (kLocalPlan) {
-    build_prefix(seq_lens, B, Hkv, s_pb, s_wsum);
-    if (blockIdx.x == 0)
-      for (int i = threadIdx.x; i <= B; i += kB8Threads) PB[i] = s_pb[i];
+    by_run = build_split<kB8Threads, kB8Par>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
+    if (blockIdx.x == 0) publish_split(PB, s_pb, B, by_run, kB8Threads);
   }
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
 
-  const int U = pbv(B);
-  const int wgs = active_wgs(U, gridDim.x, kB8Par);
-  if ((int)blockIdx.x >= wgs) return;
-  int u = unit_begin(U, wgs, blockIdx.x);
-  const int u_end = unit_begin(U, wgs, blockIdx.x + 1);
+  const int U = pbv(B);  // units: runs, or tiles
+  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
+  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
   if (u >= u_end) return;
 
   const int G = Hq / Hkv, R = G * Nq;
@@ -473,11 +469,13 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
     const int L = seq_lens[b];
     const int n_b = (L + kAtTile - 1) / kAtTile;
     const int rel = u - pbv(b);
-    const int hk = __builtin_amdgcn_readfirstlane(rel / n_b);
-    const int t0 = rel - hk * n_b;
-    const int t1 = min(n_b, t0 + (u_end - u));
+    const int per_pair = by_run ? (n_b + kB8Par - 1) / kB8Par : n_b;
+    const int hk = __builtin_amdgcn_readfirstlane(rel / per_pair);
+    const int at = rel - hk * per_pair;
+    const int t0 = by_run ? at * kB8Par : at;
+    const int t1 = min(n_b, t0 + (by_run ? kB8Par : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;
-    u += t1 - t0;
+    u += by_run ? 1 : t1 - t0;
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
@@ -492,11 +490,6 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       issue_rows<true>(kp, kb, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
       issue_rows<true>(vp, kb + kAtTileBytes, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
     };
-    // the first two tiles are on their way while the query rows are staged (the buffers are idle: the run before ended in a
-    // barrier)
-    issue_eighth(0);
-    issue_eighth(1);
-
     // the pair's query rows and upstream gradients: 8 threads per row, 32 bytes each, 64 rows per turn
 #pragma unroll
     for (int turn = 0; turn < 2; ++turn) {
@@ -541,6 +534,8 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       for (int r = 0; r < 16; ++r) dq_acc[db][r] = 0.f;
 
     __syncthreads();  // query rows staged; the previous run is done with every buffer
+    issue_eighth(0);
+    issue_eighth(1);
     if (m_row < R) {
       dlt = s_delta[m_row];
       anc = ancestor_mask(parents ? s_par : nullptr, m_row / G, Nq);
@@ -624,7 +619,7 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
 __global__ __launch_bounds__(256) void attn_bwd_dq_combine(const float* __restrict__ part_dq,
                                                            const int32_t* __restrict__ seq_lens,
                                                            const int32_t* __restrict__ PB, float* __restrict__ dq, int B,
-                                                           int Nq, int Hq, int Hkv, int wgs_launched, int row_tiles, float scale) {
+                                                           int Nq, int Hq, int Hkv, int wgs, int row_tiles, float scale) {
   const int b = blockIdx.x / Nq, n = blockIdx.x - b * Nq;
   const int hq = blockIdx.y * 8 + (threadIdx.x >> 5);
   if (hq >= Hq) return;
@@ -632,21 +627,20 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_combine(const float* __restri
   const int G = Hq / Hkv, hk = hq / G;
   const int mrow = n * G + hq - hk * G;
   const int n_b = (seq_lens[b] + kAtTile - 1) / kAtTile;
-  const int U = PB[B], u0 = PB[b] + hk * n_b;
-  const int wgs = active_wgs(U, wgs_launched, row_tiles == 4 ? kB8Par : kBmPar);
-  const int w0 = n_b > 0 ? unit_owner(U, wgs, u0) : 0, w1 = n_b > 0 ? unit_owner(U, wgs, u0 + n_b - 1) : -1;
+  int w0, np;
+  pair_owners(PB, B, b, hk, n_b, wgs, row_tiles == 4 ? kB8Par : kBmPar, w0, np);
   const int pair = b * Hkv + hk;
   const int d4 = threadIdx.x & 31;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   constexpr int kU = 4;  // partials in flight; added in run order
-  for (int p0 = w0; p0 <= w1; p0 += kU) {
+  for (int p0 = 0; p0 < np; p0 += kU) {
     f32x4_t x[kU];
 #pragma unroll
     for (int i = 0; i < kU; ++i)
-      if (p0 + i <= w1) x[i] = *(const f32x4_t*)(part_dq + ((size_t)(p0 + i + pair) * 32 * row_tiles + mrow) * kAtD + 4 * d4);
+      if (p0 + i < np) x[i] = *(const f32x4_t*)(part_dq + ((size_t)(w0 + p0 + i + pair) * 32 * row_tiles + mrow) * kAtD + 4 * d4);
 #pragma unroll
     for (int i = 0; i < kU; ++i)
-      if (p0 + i <= w1) acc += x[i];
+      if (p0 + i < np) acc += x[i];
   }
   *(f32x4_t*)(dq + row * kAtD + 4 * d4) = acc * scale;
 }

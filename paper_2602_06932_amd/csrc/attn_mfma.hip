@@ -60,11 +60,6 @@ hipError_t launch_attn_plan(const int32_t* seq_lens, int B, int Hkv, int32_t* PB
   return hipGetLastError();
 }
 
-// The split for the merge kernel: the prefix of tiles as it is, the prefix of runs as complements (negative numbers).
-__device__ __forceinline__ void publish_split(int32_t* __restrict__ PB, const int* s_pb, int B, bool by_run, int threads) {
-  for (int i = threadIdx.x; i <= B; i += threads) PB[i] = by_run ? ~s_pb[i] : s_pb[i];
-}
-
 constexpr int kNarrowPar = 4;  // tiles of a run that the narrow kernel's wavefronts take at a time
 constexpr int kWidePar = 2;    // ... the wide kernel's two tile-parity groups
 
@@ -596,15 +591,8 @@ __global__ __launch_bounds__(32 * kCombineGroups) void attn_mfma_combine(const f
     const int mrow = n * G + hq - hk * G;
     const int rt = mrow >> 5, li = mrow & 31;
     const int n_b = (seq_lens[b] + kAtTile - 1) / kAtTile;
-    const int U = PB[B], first = PB[b];
-    int w0 = 0, np = 0;  // (a sequence of length 0 has no partial: nothing is merged and the row comes out as zeros)
-    if (U < 0) {         // runs, one per workgroup
-      np = (n_b + par - 1) / par;
-      w0 = ~first + hk * np;
-    } else if (n_b > 0) {
-      w0 = unit_owner(U, wgs, first + hk * n_b);
-      np = unit_owner(U, wgs, first + hk * n_b + n_b - 1) - w0 + 1;
-    }
+    int w0, np;
+    pair_owners(PB, B, b, hk, n_b, wgs, par, w0, np);
     const int pair = b * Hkv + hk;
     const int per = (np + kSplit - 1) / kSplit;
     const int p_end = min(np, (sub + 1) * per);

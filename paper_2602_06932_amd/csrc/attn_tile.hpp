@@ -37,16 +37,8 @@ __device__ __forceinline__ void load_to_lds_16(const void* gptr, const void* lds
     asm volatile("" ::: "memory");                                                                 \
   } while (0)
 
-// Workgroups of a backward sweep that get units: all `wgs` launched ones, or so few that a run still gives each of the
-// `par` wavefront groups that share a run a tile.  Shorter runs would leave wavefronts idle without ending any sooner, and
-// every run adds a partial per query row to the merge.  The sweep and the merge kernel evaluate this alike.
-__device__ __forceinline__ int active_wgs(int U, int wgs, int par) {
-  const int w = (U + par - 1) / par;
-  return w < wgs ? (w > 0 ? w : 1) : wgs;
-}
-
 // The sweeps deal the U units to the workgroups as evenly as they divide: contiguous runs of U / wgs units, one
-// more for the first U % wgs workgroups - every active workgroup has work and no compute unit holds more than its share.
+// more for the first U % wgs workgroups - every workgroup has work (if there is enough) and no compute unit holds more than its share.
 __device__ __forceinline__ int unit_begin(int U, int wgs, int w) {
   const int q = U / wgs, r = U % wgs;
   return w * q + (w < r ? w : r);
@@ -305,36 +297,7 @@ __device__ __forceinline__ void tile_pv8(const char* vbuf, const bf16x8_t pb2[2]
     }
 }
 
-// prefix of tiles per request (see attn_plan_kernel) built by the whole workgroup into s_pb[0..B], B <= 1024
-__device__ __forceinline__ void build_prefix(const int32_t* __restrict__ seq_lens, int B, int Hkv, int* s_pb,
-                                             int* s_wsum) {
-  const int t4 = threadIdx.x * 4;
-  int un[4], loc = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    un[i] = t4 + i < B ? ((seq_lens[t4 + i] + kAtTile - 1) / kAtTile) * Hkv : 0;
-    loc += un[i];
-  }
-  int incl = loc;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(incl, o, kWave);
-    if ((int)(threadIdx.x & 63) >= o) incl += y;
-  }
-  if ((threadIdx.x & 63) == 63) s_wsum[threadIdx.x >> 6] = incl;
-  __syncthreads();
-  int run = incl - loc;
-  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) run += s_wsum[w];
-  if (threadIdx.x == 0) s_pb[0] = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    run += un[i];
-    if (t4 + i < B) s_pb[t4 + i + 1] = run;
-  }
-  __syncthreads();
-}
-
-// The split of a forward sweep over few tokens, built by the whole workgroup (kThreads threads, B <= 1024).  If the pairs'
+// The split of a sweep over few tokens, built by the whole workgroup (kThreads threads, B <= 1024).  If the pairs'
 // tiles, cut into runs of kPar (one for each wavefront group that works at a time; a pair's last run may be shorter), are
 // no more runs than there are workgroups, a workgroup takes one run: s_pb[0 .. B] is the prefix of runs per request and
 // the function returns true.  Otherwise s_pb is the prefix of tiles, which are dealt out evenly (unit_begin).
@@ -382,6 +345,27 @@ __device__ __forceinline__ bool build_split(const int32_t* __restrict__ seq_lens
   }
   __syncthreads();
   return by_run;
+}
+
+// The split for the merge kernel: the prefix of tiles as it is, the prefix of runs as complements (negative numbers).
+__device__ __forceinline__ void publish_split(int32_t* __restrict__ PB, const int* s_pb, int B, bool by_run, int threads) {
+  for (int i = threadIdx.x; i <= B; i += threads) PB[i] = by_run ? ~s_pb[i] : s_pb[i];
+}
+
+// The workgroups whose partials of the pair (b, hk), n_b tiles long, a merge kernel adds up: w0 .. w0 + np - 1 of the published
+// split.  (A sequence of length 0 has no partial: np = 0.)
+__device__ __forceinline__ void pair_owners(const int32_t* __restrict__ PB, int B, int b, int hk, int n_b, int wgs, int par,
+                                            int& w0, int& np) {
+  const int U = PB[B], first = PB[b];
+  w0 = 0;
+  np = 0;
+  if (U < 0) {  // runs, one per workgroup
+    np = (n_b + par - 1) / par;
+    w0 = ~first + hk * np;
+  } else if (n_b > 0) {
+    w0 = unit_owner(U, wgs, first + hk * n_b);
+    np = unit_owner(U, wgs, first + hk * n_b + n_b - 1) - w0 + 1;
+  }
 }
 
 constexpr int kLocalPlanMax = 1024;  // up to this many requests every workgroup builds the prefix itself

@@ -63,7 +63,9 @@ def test_infinities_at_nodes_a_row_does_not_see(gpu_lib, num_q, tiles, batch, kv
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("batch,context,nodes", [(1, 40, 0), (1, 1500, 0), (1, 1500, 12), (1, 1500, 32), (5, 333, 32)])
+@pytest.mark.parametrize("batch,context,nodes", [(1, 40, 0), (1, 1500, 0), (1, 1500, 12), (1, 1500, 32), (5, 333, 32),
+                                                 # as many runs as workgroups, one request more, short pairs in fours
+                                                 (128, 60, 0), (129, 60, 0), (129, 60, 12), (300, 60, 5), (128, 60, 32), (129, 60, 32)])
 def test_backward_of_few_tiles(gpu_lib, batch, context, nodes):
     from test_gpu_attn_bwd import _check
     _check(_workload(batch, context, nodes, False), 11)
