@@ -151,7 +151,10 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
   __shared__ int2 s_wsum[kBmThreads / kWave];
   __shared__ int s_par[kMaxNq];  // the request's tree: the ancestor walk is a chain of dependent reads
-  __shared__ float s_delta[32 * kRT];  // delta_i = <dO_i, O_i> of the pair's query rows, formed while they are staged
+  // of the pair's query rows: delta_i = <dO_i, O_i>, formed while they are staged; logsumexp (log2 units); the set of tree nodes
+  // they see (rows past the group see nothing).  Read per tile and row tile: eight registers a lane would be spilled otherwise.
+  __shared__ float s_delta[32 * kRT], s_lse2[32 * kRT];
+  __shared__ unsigned long long s_anc[32 * kRT];
   bool by_run = false;
   if (kLocalPlan) {
     by_run = build_split<kBmThreads, kBmPar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
@@ -237,22 +240,7 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
       dpart += __shfl_xor(dpart, 4, kWave);
       if ((tid & 7) == 0) s_delta[32 * rt + row] = dpart;
     }
-    // this lane's query row of every row tile: logsumexp (log2 units), delta and the set of tree nodes it sees;
-    // rows past the group see nothing
-    float lse2[kRT], dlt[kRT];
-    unsigned long long anc[kRT];
-#pragma unroll
-    for (int rt = 0; rt < kRT; ++rt) {
-      const int m = 32 * rt + li;
-      lse2[rt] = INFINITY;
-      dlt[rt] = 0.f;
-      anc[rt] = 0;
-      if (m < R) {
-        const int node = m / G;
-        const size_t row = ((size_t)b * Nq + node) * Hq + hk * G + m % G;
-        lse2[rt] = lse[row] * kLog2e;
-      }
-    }
+    if (tid < 32 * kRT) s_lse2[tid] = tid < R ? lse[((size_t)b * Nq + tid / G) * Hq + hk * G + tid % G] * kLog2e : INFINITY;
     if (parents && tid < Nq) s_par[tid] = parents[(size_t)b * Nq + tid];
 
     f32x16_t dq_acc[kRT][4];
@@ -271,14 +259,8 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
       issue_tile(kp, kbuf, tt, pa, pb);
       issue_tile(vp, vbuf, tt, pa, pb);
     }
-#pragma unroll
-    for (int rt = 0; rt < kRT; ++rt) {
-      const int m = 32 * rt + li;
-      if (m < R) {
-        dlt[rt] = s_delta[m];
-        anc[rt] = ancestor_mask(parents ? s_par : nullptr, m / G, Nq);
-      }
-    }
+    if (tid < 32 * kRT) s_anc[tid] = tid < R ? ancestor_mask(parents ? s_par : nullptr, tid / G, Nq) : 0ull;
+    __syncthreads();
     for (; tt < ntile; tt += 4) {
       const bool more = tt + 4 < ntile;
       int npa = 0, npb = 0;
@@ -299,7 +281,7 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
           if (more) issue_tile(vp, vbuf, tt + 4, npa, npb);  // V is not read again
         }
         float p[16], ds[16];
-        tile_p_ds(s_acc, dp_acc, p, ds, scale_log2, lse2[rt], dlt[rt], anc[rt], j0, prefix, L, lh);
+        tile_p_ds(s_acc, dp_acc, p, ds, scale_log2, s_lse2[32 * rt + li], s_delta[32 * rt + li], s_anc[32 * rt + li], j0, prefix, L, lh);
         bf16x8_t p_b[2], ds_b[2];
         pack_and_transpose(p, p_b, pt, li, lh);
         pack_and_transpose(ds, ds_b, dst, li, lh);
