@@ -65,9 +65,9 @@ __global__ __launch_bounds__(kLossThreads) void loss_count_kernel(const int8_t* 
   }
 }
 
-// One workgroup of eight wavefronts per row.  kInRegs: a row of at most kRowRegVals values stays in registers (up to 16 x 4
-// per thread): it is read once, each exponential is taken once, and the gradient is that exponential times w / sum.  At 128
-// registers a thread two rows share a compute unit, so one row's loads and stores overlap another's reductions.
+// One workgroup per row.  kRounds > 0: a row of at most 4 kThreads kRounds values stays in registers: it is read once, each
+// exponential is taken once, and the gradient is that exponential times w / sum.  At 128 registers a thread (512 threads, 16
+// rounds) two rows share a compute unit, so one row's loads and stores overlap another's reductions.
 // A row need not start at 16 bytes: the vectors start at its first aligned element, and the up to three elements before and
 // after them are held by six threads.
 // The kernel is bound by the row's bytes in and out, so every line of the gradient is written once and whole: w p_target is
@@ -77,25 +77,35 @@ __global__ __launch_bounds__(kLossThreads) void loss_count_kernel(const int8_t* 
 // Loads return in order, so nothing between the row's loads and their use may wait for a load asked for after them: with the
 // target side's loads behind the row's the same kernel takes 228 us, with them in front 207 us = 5.2 TB/s.  64 kept tokens,
 // 2793 rows: 145 -> 140 us; 900 rows x 16001, which took three passes for want of alignment: 90 -> 38 us.
-// Otherwise (longer rows, draft_logits and grad aligned differently) three passes over the row, the second and third from L2.
-constexpr int kRowThreads = 512;
-constexpr int kRowWaves = kRowThreads / kWave;
-constexpr int kRowRounds = 16;
-constexpr int kRowRegVals = kRowThreads * 4 * kRowRounds;  // 32768
-constexpr int kRowKept = 1024 / kRowThreads;               // kept target logits per thread
-constexpr int kScatRounds = 8;                             // rounds per turn of the scatter
-constexpr int kScatVals = kScatRounds * kRowThreads * 4;   // 16384 floats, 64 KB of LDS: two workgroups a unit
+// Short rows are bound by the chain of reductions, so what counts is how many rows a compute unit holds, so up to
+// 8192 values take four rounds - of 256 threads (68 registers, 16 KB of LDS: seven rows a unit) or of 512 (64 registers, 32 KB:
+// four).  Against three rows of 256 threads and 32 rounds, and two of 512 and 16, grad included: 65536 rows x 40: 950 and 1291
+// -> 328 us; 16384 x 512: 245 and 333 -> 93; 8192 x 4096, 1024 kept: 178 and 194 -> 80; 8192 x 8192: 210 and 202 -> 135.
+// kRounds = 0 (rows longer than 32768 or shorter than 8, draft_logits and grad aligned differently): three passes over the row,
+// the second and third from L2.
+constexpr int kMaxKept = 1024;
+constexpr int kScatRounds = 8;  // rounds per turn of the scatter, at most: 64 KB of LDS for 512 threads, two workgroups a unit
 constexpr int kGridRows = 1 << 22;  // rows along the grid's first dimension: fewer than 2^32 threads; the rest along the second
-constexpr int kCountRows = 8192;  // up to here a row's workgroup counts the classes itself (a few KB from L2)
+// Rows are given to 256 threads up to here, four rounds in registers; then to 512, four rounds up to twice as much and sixteen
+// beyond.
+constexpr int kShortVals = 4096, kMidVals = 8192, kLongVals = 32768;
+// Up to here a row's workgroup counts the classes itself (a few KB from L2 in place of a launch; short rows: as much as the rest
+// of the row, so sooner not)
+__host__ __device__ constexpr int count_rows(int threads) { return threads == 256 ? 2048 : 8192; }
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // whether the rows' workgroups count the classes themselves (their sums are the same whoever forms them)
 __host__ __device__ inline bool counts_classes(const LossLaunch& P) {
-  return P.grad && P.M <= kCountRows && ((uintptr_t)P.traj & 3) == 0;
+  return P.grad && P.M <= count_rows(P.Vd <= kShortVals ? 256 : 512) && ((uintptr_t)P.traj & 3) == 0;
 }
 
-template <bool kInRegs>
-__global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel(LossLaunch P) {
+template <int kRowThreads, int kRounds>
+__global__ __launch_bounds__(kRowThreads, kRounds == 0 ? 1 : kRounds > 4 ? 4 : kRowThreads == 256 ? 6 : 8) void loss_rows_kernel(LossLaunch P) {
+  constexpr bool kInRegs = kRounds > 0;
+  constexpr int kRowRounds = kInRegs ? kRounds : 1, kScat = kRowRounds < kScatRounds ? kRowRounds : kScatRounds;
+  constexpr int kScatVals = kScat * kRowThreads * 4;
+  constexpr int kRowWaves = kRowThreads / kWave, kRowKept = kMaxKept / kRowThreads;
+  constexpr int kCountWords = count_rows(kRowThreads) / 4 / kRowThreads;
   __shared__ float s_redf[kRowWaves];
   __shared__ double s_redd[kRowWaves];
   const int tid = threadIdx.x;
@@ -113,9 +123,9 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
   const int cls = P.traj[m];
   // rows of the two classes, counted here if they are few: four codes a load
   const bool count = counts_classes(P);
-  uint32_t c4[kCountRows / 4 / kRowThreads];
+  uint32_t c4[kCountWords];
 #pragma unroll
-  for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e) {
+  for (int e = 0; e < kCountWords; ++e) {
     const int i = tid + e * kRowThreads;
     c4[e] = 0u;
     if (count && 4 * i < P.M) {
@@ -126,7 +136,7 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
       }
     }
   }
-  // thread t holds kept entries t, t + 512, ... (past the list: its last entry, sorted out below - a load under a condition
+  // thread t holds kept entries t, t + kRowThreads, ... (past the list: its last entry, sorted out below - a load under a condition
   // would be waited for at once)
   int id[kRowKept];
   uint16_t lt_bits[kRowKept];
@@ -158,7 +168,7 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
   }
   int na = 0, nd = 0;
 #pragma unroll
-  for (int e = 0; e < kCountRows / 4 / kRowThreads; ++e)
+  for (int e = 0; e < kCountWords; ++e)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int c = (int8_t)(c4[e] >> (8 * k));
@@ -214,7 +224,7 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
     if (P.grad) {
       const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < kScatRounds; ++j) *(f32x4_t*)(s_pt + 4 * (tid + j * kRowThreads)) = zero;
+      for (int j = 0; j < kScat; ++j) *(f32x4_t*)(s_pt + 4 * (tid + j * kRowThreads)) = zero;
       if (tid < 8) s_edge[tid] = 0.f;
       __syncthreads();
 #pragma unroll
@@ -290,7 +300,7 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
     const float scale = w * (float)(1.0 / zsum);
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j0 = 0; j0 < kRowRounds; j0 += kScatRounds) {
+    for (int j0 = 0; j0 < kRowRounds; j0 += kScat) {
       if (j0 * kRowThreads >= n4) break;  // uniform
       if (j0 > 0) {
         __syncthreads();  // the turn before has been read and cleared
@@ -298,11 +308,11 @@ __global__ __launch_bounds__(kRowThreads, kInRegs ? 4 : 1) void loss_rows_kernel
         __syncthreads();
       }
 #pragma unroll
-      for (int j = 0; j < kScatRounds; ++j) {
+      for (int j = 0; j < kScat; ++j) {
         const int i = tid + (j0 + j) * kRowThreads;
         f32x4_t* at = (f32x4_t*)(s_pt + 4 * (tid + j * kRowThreads));
         const f32x4_t o = r[j0 + j] * scale - *at;
-        if (j0 + kScatRounds < kRowRounds) *at = zero;  // for the next turn; nobody else reads it
+        if (j0 + kScat < kRowRounds) *at = zero;  // for the next turn; nobody else reads it
         if (i < n4) *((f32x4_t*)(g + h) + i) = o;
         __builtin_amdgcn_sched_barrier(0);  // one round at a time: nothing but r[] may take registers here
       }
@@ -360,7 +370,7 @@ __global__ __launch_bounds__(kLossThreads) void loss_reduce_kernel(const float* 
   }
 }
 
-int loss_max_k() { return kRowKept * kRowThreads; }
+int loss_max_k() { return kMaxKept; }
 
 hipError_t launch_draft_loss(const LossLaunch& P, hipStream_t st) {
   hipError_t e;
@@ -371,12 +381,17 @@ hipError_t launch_draft_loss(const LossLaunch& P, hipStream_t st) {
   }
   if (P.M > 0) {
     // rows and gradient rows have to start at the same place within 16 bytes
-    const bool in_regs = P.Vd >= 8 && P.Vd <= kRowRegVals && (!P.grad || (((uintptr_t)P.grad ^ (uintptr_t)P.draft_logits) & 15) == 0);
+    const bool in_regs = P.Vd >= 8 && P.Vd <= kLongVals && (!P.grad || (((uintptr_t)P.grad ^ (uintptr_t)P.draft_logits) & 15) == 0);
     const dim3 grid(P.M < kGridRows ? P.M : kGridRows, (P.M - 1) / kGridRows + 1);
-    if (in_regs)
-      hipLaunchKernelGGL(loss_rows_kernel<true>, grid, dim3(kRowThreads), 0, st, P);
-    else
-      hipLaunchKernelGGL(loss_rows_kernel<false>, grid, dim3(kRowThreads), 0, st, P);
+#define AURORA_LOSS_ROWS(T, R) hipLaunchKernelGGL((loss_rows_kernel<T, R>), grid, dim3(T), 0, st, P)
+    if (P.Vd <= kShortVals) {
+      if (in_regs) AURORA_LOSS_ROWS(256, 4); else AURORA_LOSS_ROWS(256, 0);
+    } else {
+      if (!in_regs) AURORA_LOSS_ROWS(512, 0);
+      else if (P.Vd <= kMidVals) AURORA_LOSS_ROWS(512, 4);
+      else AURORA_LOSS_ROWS(512, 16);
+    }
+#undef AURORA_LOSS_ROWS
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -1,5 +1,5 @@
 """Drafter loss where its row kernel can go wrong: rows that do not start at 16 bytes (elements before and after the vectors),
-vocabularies at the edges of the register path, kept tokens on every side of the LDS turns, and class counts formed by the
+base pointers that are aligned differently, vocabularies at the edges of the register paths, kept tokens on every side of the LDS turns, and class counts formed by the
 rows' workgroups or by a kernel of their own - against the float64 oracle."""
 import numpy as np
 import pytest
@@ -12,8 +12,31 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,vd,k", [(5, 8, 4), (6, 9, 9), (7, 11, 3), (9, 16385, 1000), (5, 16387, 1024), (4, 32767, 1024),
-                                       (3, 32768, 700), (3, 32769, 64), (8193, 40, 8), (8192, 41, 8), (4099, 33, 33)])
+                                       (3, 32768, 700), (3, 32769, 64), (8193, 40, 8), (8192, 41, 8), (4099, 33, 33),
+                                       (5, 4095, 1024), (5, 4096, 1024), (6, 4097, 1024), (5, 8191, 64), (4, 8192, 1024),
+                                       (5, 8193, 500), (2048, 37, 5), (2049, 37, 5), (8193, 4200, 4), (4, 1, 1), (9, 7, 7)])
 def test_rows_of_any_alignment_and_length(gpu_lib, rows, vd, k):
+    _check_rows(gpu_lib, rows, vd, k)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("z_off,grad_off,traj_off", [(1, 1, 0), (2, 2, 1), (3, 3, 0), (0, 1, 0), (3, 0, 2), (0, 0, 3)])
+@pytest.mark.parametrize("rows,vd,k", [(6, 1000, 64), (5, 4100, 1024), (4, 20000, 700)])
+def test_base_pointers_of_any_alignment(gpu_lib, rows, vd, k, z_off, grad_off, traj_off):
+    """draft_logits and grad off a 16-byte boundary by the same number of floats (registers) or by different ones (three
+    passes), and trajectory codes off a 4-byte boundary (counted by a kernel of its own)."""
+    _check_rows(gpu_lib, rows, vd, k, z_off, grad_off, traj_off)
+
+
+def _shifted(t, off):
+    """The tensor's values `off` elements into a larger buffer."""
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+    out = buf[off:off + t.numel()].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+def _check_rows(gpu_lib, rows, vd, k, z_off=0, grad_off=0, traj_off=0):
     av = gpu_lib
     z, ids, bits, traj = gen.loss_inputs(7 + vd, rows, vd, top_k=k)
     keep = min(k, vd)
@@ -24,9 +47,9 @@ def test_rows_of_any_alignment_and_length(gpu_lib, rows, vd, k):
             ids[m, :keep] = (want + rest)[:keep]
     ref = oracle.draft_loss(z, ids, bits, traj, 0.5, None)
     d = av.aurora_loss_desc(rows=rows, draft_vocab=vd, top_k=k, discard_top_k=0, lambda_discard=0.5)
-    dev = [torch.from_numpy(a).cuda() for a in (z, ids, bits.view(np.int16), traj)]
+    dev = [_shifted(torch.from_numpy(a), off) for a, off in ((z, z_off), (ids, 0), (bits.view(np.int16), 0), (traj, traj_off))]
     kl, loss = torch.empty(rows, device="cuda"), torch.empty(5, device="cuda")
-    grad = torch.full((rows, vd), float("nan"), device="cuda")
+    grad = _shifted(torch.full((rows, vd), float("nan")), grad_off)
     av.aurora_draft_loss(d, *dev, kl, loss, grad)
     torch.cuda.synchronize()
     w = max(1.0 / max(1, ref["n_accept"]), 0.5 / max(1, ref["n_discard"]))
