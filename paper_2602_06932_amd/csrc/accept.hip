@@ -125,11 +125,11 @@ struct AcceptParams {
   int32_t* st_rej;    // [B] 1: draw from max(0, p - q); 0: draw from p
   double* gsum;       // [B, ngroups]
   int32_t* lastpos;   // [B, slices] largest token with positive weight per slice, or -1
-  // tree path with several workgroups per request: [B, Nq, tree_slices] sums of the slices of every sweep, kNotYet at launch
+  // tree path with several workgroups per request: [B, 2, 2, tree_slices] halves of the slices' sums, zeros at launch
   unsigned long long* exch;
   const float* temps;  // [B] one temperature per request (0 = that request is verified greedily), or NULL
   int wor;             // tree walk: siblings were drawn without replacement
-  int spin_limit;      // tree walk with several workgroups: polls of the arrival counter before giving up
+  int spin_limit;      // tree walk with several workgroups: polls of the others' sums before giving up
 };
 
 // the temperature of request b: its own, or the call's
@@ -498,24 +498,23 @@ __global__ __launch_bounds__(kSmallThreads) void accept_chain_pick(AcceptParams 
 // counts is the time from one exchange to the next.  A sweep at the node of the previous one finds its logits and draft
 // probabilities in registers; a rejection needs only the slice's total (group sums are formed for the draw alone); the walk's
 // state lives in registers of every wavefront - the tree is a lane per node, the next child a ballot - so a step has two
-// workgroup barriers; and a slice sum is its own flag: its word is kNotYet until it is written, so one store and one load
-// cross the dies.  16 trees of 32 nodes over 128 256 ids: 90 us with group sums exchanged behind an arrival counter
+// workgroup barriers; and a slice sum is its own flag: it travels as two words, each half of the sum beside the number of the
+// sweep, so one store and one load cross the dies and nothing is ordered against anything else.  The words of two sweeps in
+// turn are enough: a workgroup that stores for sweep k + 2 has seen everybody's words of k + 1, which are stored once those of k
+// have been read.  16 trees of 32 nodes over 128 256 ids: 90 us with group sums exchanged behind an arrival counter
 // (release, acquire, then the loads; the rows re-read for every sweep) -> 39 us.
 // The launcher keeps S * B within the number of compute units, so all workgroups of a request are resident together;
 // the wait is bounded all the same.
 // ============================================================================================
 constexpr int kTreeMaxSlices = 16;
 constexpr int kSpinLimit = 1 << 15;  // default number of polls (tens of milliseconds) before a workgroup stops waiting
-constexpr unsigned long long kNotYet = ~0ull;  // no sum has this pattern (it is a NaN; a NaN sum is stored as another one)
 
-// What a workgroup reads from another is one 64-bit word per slice and sweep, written and read with device-scope atomic
-// accesses that go past the die-local caches; nothing else is handed over, so no fence is needed.
-__device__ __forceinline__ void store_sum(unsigned long long* p, double v) {
-  unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-  if (u == kNotYet) u = 0x7ff8000000000000ull;
+// What a workgroup reads from another are 64-bit words, written and read with device-scope atomic accesses that go past the
+// die-local caches.
+__device__ __forceinline__ void store_word(unsigned long long* p, unsigned long long u) {
   __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ unsigned long long load_sum(const unsigned long long* p) {
+__device__ __forceinline__ unsigned long long load_word(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ int lane_value(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
@@ -802,18 +801,26 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
       }
       done = true;
       if (!solo) {
-        unsigned long long* ex = P.exch + ((size_t)b * Nq + sweeps) * S;
+        unsigned long long* ex = P.exch + (size_t)(2 * b + (sweeps & 1)) * 2 * S;
         if (wv == 0) {
+          // lanes 0 .. S - 1 carry the lower halves of the slices' sums, lanes 16 .. 16 + S - 1 the upper ones
           const double own = slice_sum();
-          if (lane == 0) store_sum(&ex[slice], own);
-          unsigned long long u = lane < S && lane != slice ? kNotYet : 0ull;
+          const unsigned long long bits = __builtin_bit_cast(unsigned long long, own);
+          const unsigned tag = (unsigned)sweeps + 1;
+          const int of = lane & (kTreeMaxSlices - 1), half = lane / kTreeMaxSlices;
+          const bool word = half < 2 && of < S;
+          if (word && of == slice)
+            store_word(&ex[half * S + of], ((unsigned long long)tag << 32) | (half ? bits >> 32 : bits & 0xffffffffull));
+          unsigned long long u = 0;
+          const bool wanted = word && of != slice;
           for (int polls = 0;;) {
-            if (u == kNotYet) u = load_sum(&ex[lane]);
-            if (!__any(u == kNotYet)) break;
+            if (wanted && (unsigned)(u >> 32) != tag) u = load_word(&ex[half * S + of]);
+            if (!__any(wanted && (unsigned)(u >> 32) != tag)) break;
             if (++polls > P.spin_limit) { s_fail = 1; break; }
             __builtin_amdgcn_s_sleep(1);
           }
-          if (lane < S) s_tot[lane] = lane == slice ? own : __builtin_bit_cast(double, u);
+          const unsigned part = of != slice ? (unsigned)u : half ? (unsigned)(bits >> 32) : (unsigned)bits;
+          if (word) __builtin_memcpy((char*)s_tot + 8 * of + 4 * half, &part, 4);
         }
         __syncthreads();
         if (s_fail) {
@@ -966,21 +973,23 @@ void accept_chain_geometry(int batch, int vocab, int* slices, int* gmul, int* ng
 static int g_tree_spin_limit = kSpinLimit;
 void set_tree_spin_limit(int polls) { g_tree_spin_limit = polls < 0 ? kSpinLimit : polls; }
 
-__global__ void fill_not_yet_kernel(unsigned long long* p, int n) {
+__global__ void zero_words_kernel(unsigned long long* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = kNotYet;
+  if (i < n) p[i] = 0ull;
 }
 
 int accept_tree_max_slices() { return kTreeMaxSlices; }
 
 // Workgroups per request for a sampling tree walk: as many as leave every workgroup at least 16 groups
-// to sweep, at most kTreeMaxSlices, S * B within the number of compute units (all of them resident
-// at once), and one sum per slice and sweep (at most Nq sweeps) within the exchange buffer, 2 ngroups
-// doubles per request; 1 when that leaves fewer than two.
-static int tree_slices_for(int B, int Nq, int ngroups, int cus) {
+// to sweep, at most kTreeMaxSlices, and S * B within the number of compute units (all of them resident
+// at once); 1 when that leaves fewer than two.  (Their words, 4 S per request, fit into the 2 ngroups doubles.)
+// One workgroup that holds the whole vocabulary in registers is ahead of two that exchange their sums: 16 trees of 16 nodes over
+// 12 000 ids 25.8 against 28.0 us, of 64 nodes 35.9 against 37.0 - but not without replacement, where a group takes longer: 16
+// trees of 64 nodes over 8000 ids 53.0 against 49.7.
+static int tree_slices_for(int B, int ngroups, bool wor, int cus) {
+  if (!wor && ngroups <= held_groups(wor) * kAccWaves) return 1;
   int s = ngroups / 16;
   if (s > kTreeMaxSlices) s = kTreeMaxSlices;
-  if (s > 2 * ngroups / Nq) s = 2 * ngroups / Nq;
   if (B > 0 && s > cus / B) s = cus / B;
   return s >= 2 ? s : 1;
 }
@@ -1008,11 +1017,11 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
     if (sampling) {
       int cus = 0;
       if (hipError_t e = device_cu_count(&cus); e != hipSuccess) return e;
-      S = tree_slices_for(a.B, a.Nq, ngroups, cus);
+      S = tree_slices_for(a.B, ngroups, a.wor != 0, cus);
     }
     if (S > 1) {
-      const int words = a.B * a.Nq * S;
-      hipLaunchKernelGGL(fill_not_yet_kernel, dim3((words + 255) / 256), dim3(256), 0, st, P.exch, words);
+      const int words = a.B * 4 * S;
+      hipLaunchKernelGGL(zero_words_kernel, dim3((words + 255) / 256), dim3(256), 0, st, P.exch, words);
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     const bool held = (ngroups + S - 1) / S <= held_groups(P.wor != 0) * kAccWaves;

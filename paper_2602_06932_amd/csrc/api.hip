@@ -116,7 +116,7 @@ AcceptPlan plan_accept(const aurora_accept_desc* d) {
   p.st_row_off = p.st_lse_off + align_up(B * sizeof(double));
   p.st_rej_off = p.st_row_off + align_up(B * sizeof(int32_t));
   p.gsum_off = p.st_rej_off + align_up(B * sizeof(int32_t));
-  // a chain's group sums; the tree walk exchanges its slice sums here (up to 2 ngroups words per request)
+  // a chain's group sums; the tree walk exchanges its slice sums here (at most ngroups / 4 words per request)
   p.lastpos_off = p.gsum_off + align_up(2 * B * p.ngroups * sizeof(double));
   const size_t lp_slices = (size_t)std::max(p.slices, 2 * accept_tree_max_slices());
   // (the size is part of the interface - callers keep it - and includes B words that nothing uses any more)

@@ -520,15 +520,18 @@ def test_tree_walk_with_several_workgroups_per_request(gpu_lib, batch, num_q, vo
             assert np.array_equal(first[k], again[k], equal_nan=True), k
 
 
-def test_split_tree_walk_finishes_alone_when_its_wait_runs_out(gpu_lib):
+@pytest.mark.parametrize("batch,num_q,vocab,wor", [(6, 16, 20011, False), (6, 16, 20011, True),   # slices held in registers
+                                                   (50, 8, 70000, False), (50, 8, 70000, True),   # five slices of 55 groups: re-read
+                                                   (3, 64, 20011, True)])                         # many sweeps per walk
+def test_split_tree_walk_finishes_alone_when_its_wait_runs_out(gpu_lib, batch, num_q, vocab, wor):
     """The bounded wait of the several-workgroup tree walk, forced from the host: with a spin limit of zero a workgroup
-    that finds the others not yet arrived stops waiting at once; the request's first workgroup then finishes the walk
-    by itself.  Every kernel exits and every request comes out exactly as with the default limit (and as the oracle
+    that finds the others not yet arrived stops waiting at once and finishes the walk by itself, slice by slice; several
+    may do so.  Every kernel exits and every request comes out exactly as with the default limit (and as the oracle
     has it), whatever the limit - nothing is left for the caller to repair."""
     import paper_2602_06932_amd as av
     from paper_2602_06932_amd.device import DeviceVerify
-    w = gen.llama_tree(57, batch=6, num_q=16, vocab=20011, hidden_size=128, context=48, num_q_heads=4, num_kv_heads=2,
-                       draft_noise=2.0)
+    w = gen.llama_tree(57, batch=batch, num_q=num_q, vocab=vocab, hidden_size=128, context=48 + num_q, num_q_heads=4,
+                       num_kv_heads=2, draft_noise=2.0, siblings_without_replacement=wor)
     dv = DeviceVerify(w)
     dv.verify()
     torch.cuda.synchronize()
@@ -556,7 +559,7 @@ def test_split_tree_walk_finishes_alone_when_its_wait_runs_out(gpu_lib):
 
 
 def test_tree_verify_step_replays_from_a_captured_graph(gpu_lib):
-    """The several-workgroup tree walk clears its arrival counters with a kernel of the same call, so it
+    """The several-workgroup tree walk clears the words its sums travel in with a kernel of the same call, so it
     replays from a graph like the rest."""
     from paper_2602_06932_amd.device import DeviceVerify
     w = gen.llama_tree(52, batch=6, num_q=16, vocab=20011, hidden_size=128, context=48, num_q_heads=4, num_kv_heads=2)
@@ -586,7 +589,7 @@ def test_tree_verify_step_replays_from_a_captured_graph(gpu_lib):
 # ---- KV cache held as E4M3 codes with one scale per KV head ------------------------------------------------
 @pytest.mark.parametrize("seed,batch,lens", [(61, 6, (40, 700)), (62, 3, (5, 33)), (63, 9, (100, 2100))])
 def test_fp8_kv_chain(gpu_lib, seed, batch, lens):
-    """Chains over an 8-bit cache: the 32-row matrix-core kernel widens the codes in registers."""
+    """Chains over an 8-bit cache: the 32-row matrix-core kernel widens the codes between LDS and the matrix instruction."""
     w = gen.llama_chain(seed, batch=batch, len_lo=lens[0], len_hi=lens[1], vocab=2000, hidden_size=128, kv_fp8=True)
     assert w.k_pages.dtype == np.uint8
     _full_check(gpu_lib, w)

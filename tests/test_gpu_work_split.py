@@ -72,10 +72,14 @@ def test_backward_of_few_tiles(gpu_lib, batch, context, nodes):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("batch,num_q,vocab,wor", [(130, 6, 9000, False), (130, 6, 9000, True),  # one slice of more groups than are held
-                                                   (50, 8, 70000, False),                       # five slices of 55 groups: the last held one is 48
+@pytest.mark.parametrize("batch,num_q,vocab,wor", [(130, 6, 9000, False), (130, 6, 9000, True),   # 36 groups: held, not held
+                                                   (130, 6, 12288, False), (130, 6, 12289, False), # one slice of 48 groups: held; 49
+                                                   (130, 6, 13000, False),                      # one workgroup, not held
+                                                   (50, 8, 70000, False),                       # five slices of 55 groups: not held
                                                    (64, 8, 49152, False),                       # four slices of 48 groups: held
-                                                   (3, 64, 20011, False)])                      # slices bounded by the exchange buffer
+                                                   (12, 16, 8192, True), (12, 16, 8193, True),  # 32 groups: the first split in two
+                                                   (12, 16, 12288, False), (12, 16, 12289, False),  # 48: one workgroup; 49: split
+                                                   (3, 64, 20011, False), (3, 64, 20011, True)])  # as many sweeps as there can be
 def test_tree_walk_slices(gpu_lib, batch, num_q, vocab, wor):
     from test_gpu_parity import _full_check
     w = gen.llama_tree(400 + batch, batch=batch, num_q=num_q, vocab=vocab, hidden_size=64, context=70, num_q_heads=2,
