@@ -24,6 +24,8 @@
 #include "common.hpp"
 #include "launch.hpp"
 
+#include <algorithm>
+
 namespace aurora {
 
 constexpr int kAccThreads = 1024;
@@ -129,6 +131,7 @@ struct AcceptParams {
   unsigned long long* exch;
   const float* temps;  // [B] one temperature per request (0 = that request is verified greedily), or NULL
   int wor;             // tree walk: siblings were drawn without replacement
+  int solo_slices;     // tree walk with one workgroup: slices it sweeps the vocabulary in
   int spin_limit;      // tree walk with several workgroups: polls of the others' sums before giving up
 };
 
@@ -538,6 +541,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
   __shared__ int s_arg[kMaxNq];
   __shared__ double s_gsum[kMaxGroups];
   __shared__ double s_wtot[kAccWaves], s_tot[kTreeMaxSlices];
+  __shared__ double s_share[kTreeMaxSlices][kAccWaves];  // the wavefronts' shares of the slices' totals
   __shared__ int s_fail, s_pick, s_lastpos;
   __shared__ double s_pick_prefix;
   __shared__ int s_par[kMaxNq], s_tok[kMaxNq];
@@ -551,7 +555,9 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
   __shared__ int s_rejw[kAccWaves][kMaxNq], s_qlenw[kAccWaves][kMaxNq];
 
   const int b = blockIdx.y;
-  const int S = (int)gridDim.x, slice = blockIdx.x;  // S > 1 only for sampling walks
+  // slices of the vocabulary: one per workgroup, or those that the request's only workgroup sweeps one after the other
+  const bool alone = gridDim.x == 1;
+  const int S = alone ? P.solo_slices : (int)gridDim.x, slice = blockIdx.x;
   const bool writer = slice == 0;                     // the workgroup that stores the walk's outputs
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -643,7 +649,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
   const bool vec_ok = rows_vec_ok(P);
   const int per_slice = (ngroups + S - 1) / S;
   auto slice_lo = [&](int s) AURORA_INLINE { return min(ngroups, s * per_slice); };
-  bool solo = S == 1;  // this workgroup sweeps every slice itself
+  bool solo = alone;  // this workgroup sweeps every slice itself
   const QLevels ql = {rej, qlen, qfac};
 
   int cur = 0, depth = 0, last_child = 0, nres = 0, sweeps = 0;
@@ -743,12 +749,12 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
     double acc = 0.0;
     for_groups(sl, level, skip_last, [&](int, const double* x) AURORA_INLINE { acc += (x[0] + x[1]) + (x[2] + x[3]); });
     acc = wave_sum(acc);
-    if (lane == 0) s_wtot[wv] = acc;
+    if (lane == 0) s_share[sl][wv] = acc;
   };
-  auto slice_sum = [&]() AURORA_INLINE {
+  auto slice_sum = [&](int sl) AURORA_INLINE {
     double t = 0.0;
 #pragma unroll
-    for (int i = 0; i < kAccWaves; ++i) t += s_wtot[i];
+    for (int i = 0; i < kAccWaves; ++i) t += s_share[sl][i];
     return t;
   };
   for (;;) {
@@ -791,20 +797,17 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
     const bool raw = c >= 0;
     for (bool done = false; !done;) {
       const int s0 = solo ? 0 : slice, s1 = solo ? S : slice + 1;
-      for (int sl = s0; sl < s1; ++sl) {
-        park_share(sl, level, raw);
-        __syncthreads();
-        if (solo) {
-          if (tid == 0) s_tot[sl] = slice_sum();
-          __syncthreads();
-        }
-      }
+      for (int sl = s0; sl < s1; ++sl) park_share(sl, level, raw);
+      __syncthreads();
       done = true;
-      if (!solo) {
+      if (solo) {
+        if (tid < S) s_tot[tid] = slice_sum(tid);
+        __syncthreads();
+      } else {
         unsigned long long* ex = P.exch + (size_t)(2 * b + (sweeps & 1)) * 2 * S;
         if (wv == 0) {
           // lanes 0 .. S - 1 carry the lower halves of the slices' sums, lanes 16 .. 16 + S - 1 the upper ones
-          const double own = slice_sum();
+          const double own = slice_sum(slice);
           const unsigned long long bits = __builtin_bit_cast(unsigned long long, own);
           const unsigned tag = (unsigned)sweeps + 1;
           const int of = lane & (kTreeMaxSlices - 1), half = lane / kTreeMaxSlices;
@@ -830,7 +833,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
           // result.  Others that wait for it run into their own bound and do likewise; what several then write is the same.
           solo = true;
           done = false;
-          __syncthreads();  // s_wtot and s_tot are about to be rewritten
+          __syncthreads();  // s_share and s_tot are about to be rewritten
         }
       }
     }
@@ -1025,6 +1028,10 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     const bool held = (ngroups + S - 1) / S <= held_groups(P.wor != 0) * kAccWaves;
+    // One workgroup that does not hold the vocabulary still keeps a total per slice, so that the draw re-reads one slice and
+    // not the whole row: 64 groups, one round of loads for its wavefronts.  150 trees of four nodes over 151 936 ids: 257 us with
+    // one slice, 188 with ten (222 with every group's sum kept from the last sweep); 256 of eight over 32 000: 84 and 77.
+    P.solo_slices = held ? 1 : std::min(kTreeMaxSlices, (ngroups + 4 * kAccWaves - 1) / (4 * kAccWaves));
 #define AURORA_TREE(HELD, WOR) hipLaunchKernelGGL((accept_tree_kernel<HELD, WOR>), dim3(S, a.B), dim3(kAccThreads), 0, st, P)
     if (held) {
       if (P.wor) AURORA_TREE(true, true); else AURORA_TREE(true, false);

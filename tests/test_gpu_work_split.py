@@ -75,6 +75,7 @@ def test_backward_of_few_tiles(gpu_lib, batch, context, nodes):
 @pytest.mark.parametrize("batch,num_q,vocab,wor", [(130, 6, 9000, False), (130, 6, 9000, True),   # 36 groups: held, not held
                                                    (130, 6, 12288, False), (130, 6, 12289, False), # one slice of 48 groups: held; 49
                                                    (130, 6, 13000, False),                      # one workgroup, not held
+                                                   (130, 6, 40000, False), (130, 4, 70000, True),  # ... in several slices
                                                    (50, 8, 70000, False),                       # five slices of 55 groups: not held
                                                    (64, 8, 49152, False),                       # four slices of 48 groups: held
                                                    (12, 16, 8192, True), (12, 16, 8193, True),  # 32 groups: the first split in two
