@@ -39,6 +39,11 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// the value of a key (a zero without its sign, NaN for the key of NaN)
+__device__ __forceinline__ float key_value(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
+}
+
 __device__ __forceinline__ uint64_t entry_word(float x, int id) {
   return ((uint64_t)order_key(x) << 32) | (uint32_t)~id;
 }
@@ -379,11 +384,8 @@ __global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) voi
       if (tid == 0) s_count = 0;
       __syncthreads();
       float cut_f;
-      {
-        const uint32_t u = (cut & 0x80000000u) ? (cut ^ 0x80000000u) : ~cut;
-        cut_f = __uint_as_float(u);
-        if (cut_f != cut_f) cut_f = -INFINITY;
-      }
+      cut_f = key_value(cut);
+      if (cut_f != cut_f) cut_f = -INFINITY;
       // Eight lanes per group, 16 bytes each; nine groups in flight per lane, so that the about 1040 groups of K = 1024 are
       // one round.  A lane marks its entries that reach the cut-off in a mask and then lists the ids of the few marked ones
       // (1.2 a lane): the values are fetched again below, by all threads at once.  Appending each entry where it was found
@@ -438,11 +440,8 @@ __global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) voi
     // The pass compares floats: key(x) >= cut  <=>  x >= cut_f for the float cut_f whose key is `cut` (keys
     // are monotone, and -0.0 >= +0.0 holds just as their keys are equal); only survivors pay for a key.
     float cut_f;
-    {
-      const uint32_t u = (cut & 0x80000000u) ? (cut ^ 0x80000000u) : ~cut;
-      cut_f = __uint_as_float(u);
-      if (cut_f != cut_f) cut_f = -INFINITY;  // a prefix below every finite key: everything passes
-    }
+    cut_f = key_value(cut);
+    if (cut_f != cut_f) cut_f = -INFINITY;  // a prefix below every finite key: everything passes
     if (tid < h) {
       const float x = at(tid);
       if (x >= cut_f) {
@@ -488,10 +487,14 @@ __global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) voi
 
   // ---- a list that fits is ranked in place: bucket by value range, count the larger words inside the bucket ----
   // Words are distinct, so the rank of a word (how many are larger) is its position in the output.  The upper 32
-  // bits of a word are an order-preserving key of the value: a monotone map of the key onto 1024 buckets (linear
-  // between the smallest and the largest key of the list, highest values first) keeps the order between buckets,
-  // and inside a bucket - a few words for logits of an LM head - ranks come from direct comparison.  A bucket
-  // of more than 256 words (heavy ties) sends the list to the radix select and bitonic sort below instead.
+  // bits of a word are an order-preserving key of the value: a monotone map onto 1024 buckets between the smallest and the
+  // largest finite value of the list (highest first; infinities and NaN at the ends) keeps the order between buckets, and inside
+  // a bucket that can hold one of the `want` largest - a few words for logits of an LM head - ranks come from direct
+  // comparison.  The map is linear in the key, or in the value where the keys span 64 binades or more: a list that reaches
+  // zero (short rows, which are listed whole) spends nearly all of the key's range on values around it, and its buckets of half a
+  // binade held hundreds of words (160 rows of 4096 logits, K = 64: 56 us, 8.3 linear in the value; K = 1024: 56, 11.5).  Heavy tails on one side of
+  // zero are better off in the key (16.6 us against 32.8).  A bucket
+  // of more than 128 words (heavy ties) sends the list to the radix select and bitonic sort below instead.
   __syncthreads();
   if (!from_row) {
     constexpr int kPer = kTrCap / kTrThreads;  // list entries per thread
@@ -518,31 +521,41 @@ __global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) voi
         w[e] = i < count ? s_cand[i] : 0ull;
       }
     }
+    constexpr unsigned kNegInf = 0x007fffffu, kPosInf = 0xff800000u;  // keys of the infinities
     unsigned kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
-    for (int e = 0; e < kPer; ++e)
-      if (tid + e * kTrThreads < count) {
-        const unsigned k = (unsigned)(w[e] >> 32);
+    for (int e = 0; e < kPer; ++e) {
+      const unsigned k = (unsigned)(w[e] >> 32);
+      if (tid + e * kTrThreads < count && k - (kNegInf + 1u) < kPosInf - (kNegInf + 1u)) {
         kmin = min(kmin, k);
         kmax = max(kmax, k);
       }
+    }
     key_range(kmin, kmax, kmin, kmax);
+    if (kmin > kmax) kmin = kmax = 0x80000000u;  // nothing finite: infinities fall on either side of zero
     const int shift = shift_for(kmax - kmin, 10);
+    const float vmin = key_value(kmin), span = key_value(kmax) - vmin;
+    const bool by_value = (kmax - kmin) >> 29 != 0 && span < INFINITY;
+    const float scale = by_value ? (float)(kBuckets - 1) / span : 0.f;
     int bucket[kPer], pos[kPer];
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
       const int i = tid + e * kTrThreads;
       bucket[e] = 0; pos[e] = 0;
       if (i < count) {
-        bucket[e] = kBuckets - 1 - (int)(((unsigned)(w[e] >> 32) - kmin) >> shift);  // highest values first
+        const unsigned k = min(max((unsigned)(w[e] >> 32), kmin), kmax);
+        int up;
+        if (by_value) up = min((int)((key_value(k) - vmin) * scale), kBuckets - 1);  // uniform
+        else up = (int)((k - kmin) >> shift);
+        bucket[e] = kBuckets - 1 - up;  // highest values first
         pos[e] = atomicAdd(&s_hist[bucket[e]], 1);
       }
     }
     __syncthreads();
     {
       const int c = s_hist[tid];
-      if (c > 256) s_big = 1u;
       const int before = block_excl_scan(c);
+      if (c > 128 && before < want) s_big = 1u;
       s_hist[tid] = before;
     }
     __syncthreads();
@@ -559,15 +572,15 @@ __global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) voi
         const int i = tid + e * kTrThreads;
         if (i < count) {
           const int lo = s_hist[bucket[e]];
+          if (lo >= want) continue;  // every word of the bucket is behind the last one wanted
           const int hi = bucket[e] == kBuckets - 1 ? count : s_hist[bucket[e] + 1];
           int rank = lo;
           for (int jj = lo; jj < hi; ++jj) rank += s_buck[jj] > w[e];
           if (rank < want) {
             const int id = (int)~(uint32_t)(w[e] & 0xffffffffull);
-            const uint32_t key = (uint32_t)(w[e] >> 32);
-            const uint32_t bits = (key & 0x80000000u) ? (key ^ 0x80000000u) : ~key;  // the value, but for the sign of a zero
+            const float x = key_value((uint32_t)(w[e] >> 32));  // the value, but for the sign of a zero
             ids[rank] = id;
-            vals[rank] = bf16_rne_bits((bits << 1) ? __uint_as_float(bits) : at(id));
+            vals[rank] = bf16_rne_bits(x != 0.f ? x : at(id));
           }
         }
       }

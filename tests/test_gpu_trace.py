@@ -54,6 +54,31 @@ def test_topk_full_size_llama_vocab(gpu_lib):
     _check_topk(gpu_lib, gen.trace_logits(1, 160, 128256, "normal"), 1024)
 
 
+@pytest.mark.parametrize("vocab,k", [(1023, 1), (1500, 64), (3000, 1024), (4096, 1), (4096, 64), (4096, 1024), (4099, 700)])
+def test_topk_lists_that_reach_zero(gpu_lib, vocab, k):
+    """Rows that are listed whole, or nearly: values on both sides of zero in ordinary and extreme proportions, with infinities,
+    few distinct values, values next to the smallest ones - the buckets are linear in the value, in the key, or too full."""
+    rng = np.random.default_rng([vocab, k])
+    n = rng.standard_normal((12, vocab), dtype=np.float32)
+    x = n * np.float32(0.3)
+    x[1, rng.random(vocab) < 0.4] = -np.inf
+    x[1, :3] = np.inf
+    x[2] = np.maximum(n[2], 0.0)                                  # half of it zeros
+    x[3] = n[3] * np.float32(1e-39)                               # subnormal values
+    x[4] = np.sign(n[4]) * np.exp(np.abs(n[4]) * 12, dtype=np.float32)  # heavy tails on both sides
+    x[5] = -np.inf
+    x[5, rng.choice(vocab, 5, replace=False)] = n[5, :5]
+    x[6] = np.where(n[6] > 0, 1.0, -1.0)
+    x[7] = np.where(n[7] > 0, np.inf, -np.inf)
+    x[8] = n[8] * np.float32(3e38 / 6)                            # the span of the values is past the largest float
+    x[8, 0], x[8, 1] = 3e38, -3e38
+    x[9] = n[9]
+    x[9, 2] = 1e30                                                # one value far from the rest
+    x[10] = np.float32(-2.0) - np.abs(n[10])
+    x[11] = np.where(n[11] > 1, n[11], -0.0)
+    _check_topk(gpu_lib, np.ascontiguousarray(x), k)
+
+
 @pytest.mark.parametrize("vocab,draft_vocab,k", [(128256, 32000, 1024), (50001, 4097, 1000), (20000, 3000, 1024),
                                                  (9999, 500, 1024), (151936, 32003, 1024)])
 def test_topk_over_the_draft_vocabulary(gpu_lib, vocab, draft_vocab, k):
