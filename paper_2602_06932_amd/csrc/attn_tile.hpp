@@ -297,6 +297,18 @@ __device__ __forceinline__ void tile_pv8(const char* vbuf, const bf16x8_t pb2[2]
     }
 }
 
+// inclusive scan over the 64 lanes in six data-parallel additions: within each row of sixteen, then row 0 into 1 and row 2 into
+// 3, then the lower half into the upper (every workgroup of a sweep waits for two of these before its first load)
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
 // The split of a sweep over few tokens, built by the whole workgroup (kThreads threads, B <= 1024).  If the pairs'
 // tiles, cut into runs of kPar (one for each wavefront group that works at a time; a pair's last run may be shorter), are
 // no more runs than there are workgroups, a workgroup takes one run: s_pb[0 .. B] is the prefix of runs per request and
@@ -319,12 +331,7 @@ __device__ __forceinline__ bool build_split(const int32_t* __restrict__ seq_lens
     nt += tiles[i];
     nr += runs[i];
   }
-  int it = nt, ir = nr;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int yt = __shfl_up(it, o, kWave), yr = __shfl_up(ir, o, kWave);
-    if (lane >= o) { it += yt; ir += yr; }
-  }
+  const int it = wave_incl_scan(nt), ir = wave_incl_scan(nr);
   if (lane == 63) s_wsum[wave] = make_int2(it, ir);
   __syncthreads();
   int at_tile = it - nt, at_run = ir - nr, all_runs = 0;
