@@ -960,7 +960,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_tree_kernel(AcceptParams P
 
 void accept_chain_geometry(int batch, int vocab, int* slices, int* gmul, int* ngroups) {
   const int ng = (vocab + kGroup - 1) / kGroup;
-  // enough slices that a wavefront sweeps its share in two batches of four groups, within about two
+  // enough slices that a wavefront sweeps its share in one batch of four groups, within about two
   // workgroups per compute unit over the whole batch
   int s = (ng + 31) / 32;
   const int cap = (512 + batch - 1) / (batch > 0 ? batch : 1);

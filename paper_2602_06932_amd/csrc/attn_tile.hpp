@@ -222,7 +222,7 @@ __device__ __forceinline__ void issue_rows(const bf16_t* pool, char* buf, int j,
 }
 
 // ---- KV cache held as E4M3 codes (one byte per element, one scale per KV head) ----------------------------
-// A 32-token tile of codes is 32 rows x 128 B = 4 KB each of K and V.  The narrow kernel brings the codes into LDS as
+// A 32-token tile of codes is 32 rows x 128 B = 4 KB each of K and V.  Both kernels bring the codes into LDS as
 // they are and widens them to bf16 (exactly) between the LDS read and the matrix instruction: half the LDS bytes of a
 // bf16 tile and no registers for tiles on their way.  The scales are applied outside the products: K's folds into the
 // softmax scale, V's multiplies the segment's partial O.
