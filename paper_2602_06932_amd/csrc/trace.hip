@@ -534,22 +534,26 @@ __global__ __launch_bounds__(kTrThreads, 4 * kOcc /* wavefronts per SIMD */) voi
     key_range(kmin, kmax, kmin, kmax);
     if (kmin > kmax) kmin = kmax = 0x80000000u;  // nothing finite: infinities fall on either side of zero
     const int shift = shift_for(kmax - kmin, 10);
-    const float vmin = key_value(kmin), span = key_value(kmax) - vmin;
-    const bool by_value = (kmax - kmin) >> 29 != 0 && span < INFINITY;
-    const float scale = by_value ? (float)(kBuckets - 1) / span : 0.f;
+    // the bucket from the top of a key: in the list's own range, infinities at its ends
     int bucket[kPer], pos[kPer];
+    auto place = [&](auto up_of) {
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int i = tid + e * kTrThreads;
-      bucket[e] = 0; pos[e] = 0;
-      if (i < count) {
-        const unsigned k = min(max((unsigned)(w[e] >> 32), kmin), kmax);
-        int up;
-        if (by_value) up = min((int)((key_value(k) - vmin) * scale), kBuckets - 1);  // uniform
-        else up = (int)((k - kmin) >> shift);
-        bucket[e] = kBuckets - 1 - up;  // highest values first
-        pos[e] = atomicAdd(&s_hist[bucket[e]], 1);
+      for (int e = 0; e < kPer; ++e) {
+        const int i = tid + e * kTrThreads;
+        bucket[e] = 0; pos[e] = 0;
+        if (i < count) {
+          bucket[e] = kBuckets - 1 - up_of(min(max((unsigned)(w[e] >> 32), kmin), kmax));
+          pos[e] = atomicAdd(&s_hist[bucket[e]], 1);
+        }
       }
+    };
+    const bool wide = (kmax - kmin) >> 29 != 0;
+    const float vmin = key_value(kmin), span = wide ? key_value(kmax) - vmin : INFINITY;
+    if (span < INFINITY) {
+      const float scale = (float)(kBuckets - 1) / span;
+      place([&](unsigned k) { return min((int)((key_value(k) - vmin) * scale), kBuckets - 1); });
+    } else {
+      place([&](unsigned k) { return (int)((k - kmin) >> shift); });
     }
     __syncthreads();
     {
