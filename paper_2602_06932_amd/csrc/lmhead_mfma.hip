@@ -392,10 +392,7 @@ static hipError_t launch_nt(const AcceptLaunch& a, hipStream_t st, int m_tiles) 
 
 hipError_t launch_lmhead_mfma(const AcceptLaunch& a, hipStream_t st) {
   const int M = (int)a.plan.rows;
-  // From 384 token rows on the contraction is bound by the matrix cores and the tiled kernel, in which all
-  // wavefronts multiply and whose workgroup columns are sized to the token rows, is the faster one (measured on
-  // 128256 x 4096: 448 rows 0.52 against 0.55 ms, 1280 rows 1.33 against 1.44 ms; 320 rows 0.43 against 0.37 ms).
-  if (M >= kLmBigFromRows && lmhead_mfma_big_supported(a)) return launch_lmhead_mfma_big(a, st);
+  if (lm_many_rows(M) && lmhead_mfma_big_supported(a)) return launch_lmhead_mfma_big(a, st);
   // token rows per workgroup: the fewest 160-row passes over W, each as narrow as the rows allow
   const int passes = (M + 159) / 160;
   const int per = (M + passes - 1) / passes;

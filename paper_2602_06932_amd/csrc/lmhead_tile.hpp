@@ -20,6 +20,43 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
     asm volatile("" ::: "memory");                                                                 \
   } while (0)
 
+// The 64 x kRows logits of a wavefront, turned through `tb` (16-byte slot s of token row n lies at slot s ^ (n & 15)): each store
+// instruction covers four token rows of 256 contiguous bytes.
+template <int kRows>
+__device__ __forceinline__ void lm_store_tile(const char* tb, int vrow0, int V, int mrow0, int M, bool v_whole,
+                                              float* __restrict__ logits, bool vec_ok, int lane) {
+  const int srow = lane >> 4, sslot = lane & 15;
+  if (vec_ok && v_whole && mrow0 + kRows <= M) {
+    // the common case, decided once per wavefront: every row and column of the tile exists - plain vector stores
+    float* dst = logits + (size_t)(mrow0 + srow) * V + (vrow0 + 4 * sslot);
+    const size_t step = (size_t)4 * V;  // four token rows further
+#pragma unroll
+    for (int j = 0; j < kRows / 4; ++j) {
+      const int n = 4 * j + srow;
+      const f32x4_t o = *(const f32x4_t*)(tb + n * 256 + ((sslot ^ (n & 15)) * 16));
+      __builtin_nontemporal_store(o, (f32x4_t*)(dst + j * step));  // written once, read much later: keep it out of the way of W
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < kRows / 4; ++j) {
+    const int n = 4 * j + srow;  // token row of the tile
+    const f32x4_t o = *(const f32x4_t*)(tb + n * 256 + ((sslot ^ (n & 15)) * 16));
+    const int mm = mrow0 + n;
+    const int v = vrow0 + 4 * sslot;
+    if (mm < M) {
+      float* dst = logits + (size_t)mm * V + v;
+      if (vec_ok && v + 3 < V) {
+        __builtin_nontemporal_store(o, (f32x4_t*)dst);  // written once, read much later: keep it out of the way of W
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v + e < V) dst[e] = o[e];
+      }
+    }
+  }
+}
+
 // Accumulator register r of a 32x32 MFMA tile holds row 8(r/4) + 4(lane/32) + r%4, column lane%32.
 // a0 / a1 are the tiles of vocab rows vrow0.. and vrow0+32.. for the 32 tokens mrow0.. (column = token).
 // Entries past the vocabulary are set to -inf in place.  Returns this token's (max, arg-max, sum of
@@ -94,36 +131,109 @@ __device__ __forceinline__ void lm_tile_out(f32x16_t& a0, f32x16_t& a1, int vrow
       f32x4_t o = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
       *(f32x4_t*)(tb + li * 256 + ((slot ^ (li & 15)) * 16)) = o;
     }
-  const int srow = lane >> 4, sslot = lane & 15;
-  if (vec_ok && v_whole && mrow0 + 32 <= M) {
-    // the common case, decided once per wavefront: every row and column of the tile exists - eight plain vector stores
-    float* dst = logits + (size_t)(mrow0 + srow) * V + (vrow0 + 4 * sslot);
-    const size_t step = (size_t)4 * V;  // four token rows further
+  lm_store_tile<32>(tb, vrow0, V, mrow0, M, v_whole, logits, vec_ok, lane);
+}
+
+// Exchanges between the rows of sixteen lanes 0..3: a becomes (a0, b0, a2, b2) and b (a1, b1, a3, b3), so a commutative operation on
+// the two then reduces over the pairs of rows, a's result in the even rows and b's in the odd ones (both a's if b is a copy).
+__device__ __forceinline__ void swap_rows16(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+// a becomes (a's lower half, b's lower half) and b (a's upper half, b's upper half)
+__device__ __forceinline__ void swap_halves32(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap_rows16(float& a, float& b) {
+  unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+  swap_rows16(x, y);
+  a = __uint_as_float(x);
+  b = __uint_as_float(y);
+}
+__device__ __forceinline__ void swap_halves32(float& a, float& b) {
+  unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+  swap_halves32(x, y);
+  a = __uint_as_float(x);
+  b = __uint_as_float(y);
+}
+
+// The same for accumulators of 16 x 16 tiles: acc[c][a] is the tile of vocab rows vrow0 + 16 a .. and tokens mrow0 + 16 c ..,
+// c < kC (one or two token tiles); its register r holds row 4 (lane / 16) + r, column lane % 16.  exp_scale is that of token
+// mrow0 + lane % 32, and so are the outputs (kC == 1: of lanes 0-15 and 32-47 alone): the four lanes of a token meet by
+// exchanges of rows of sixteen, two tokens' worth in each.
+template <int kC>
+__device__ __forceinline__ void lm_tile_out16(f32x4_t (*acc)[4], int vrow0, int V, int mrow0, int M, float exp_scale, char* tb,
+                                              float* __restrict__ logits, bool vec_ok, int lane, float& mx_out,
+                                              float& sum_out, int& arg_out, float& half_max_out) {
+  const int li = lane & 15, lq = lane >> 4;
+  const bool v_whole = vrow0 + 64 <= V;  // wave-uniform: only the vocabulary's last tile has rows to mask
+  if (!v_whole) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int n = 4 * j + srow;
-      const f32x4_t o = *(const f32x4_t*)(tb + n * 256 + ((sslot ^ (n & 15)) * 16));
-      __builtin_nontemporal_store(o, (f32x4_t*)(dst + j * step));  // written once, read much later: keep it out of the way of W
-    }
-    return;
+    for (int c = 0; c < kC; ++c)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (vrow0 + 16 * a + 4 * lq + r >= V) acc[c][a][r] = -INFINITY;
   }
+  float g[2][2];  // [token tile][group of 32 vocab rows]: largest of this lane's entries
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int n = 4 * j + srow;  // token row of the tile
-    const f32x4_t o = *(const f32x4_t*)(tb + n * 256 + ((sslot ^ (n & 15)) * 16));
-    const int mm = mrow0 + n;
-    const int v = vrow0 + 4 * sslot;
-    if (mm < M) {
-      float* dst = logits + (size_t)mm * V + v;
-      if (vec_ok && v + 3 < V) {
-        __builtin_nontemporal_store(o, (f32x4_t*)dst);  // written once, read much later: keep it out of the way of W
-      } else {
+  for (int c = 0; c < kC; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (v + e < V) dst[e] = o[e];
-      }
+    for (int h = 0; h < 2; ++h) {
+      float x = -INFINITY;
+#pragma unroll
+      for (int a = 2 * h; a < 2 * h + 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x = fmaxf(x, acc[c][a][r]);
+      g[c][h] = x;
     }
+  if (kC == 1) { g[1][0] = g[0][0]; g[1][1] = g[0][1]; }
+  swap_rows16(g[0][0], g[1][0]);
+  swap_rows16(g[0][1], g[1][1]);
+  float h0 = fmaxf(g[0][0], g[1][0]), h1 = fmaxf(g[0][1], g[1][1]);
+  swap_halves32(h0, h1);
+  half_max_out = fmaxf(h0, h1);  // token lane % 32, group lane / 32
+  float mx = half_max_out, mo = half_max_out;
+  swap_halves32(mx, mo);
+  mx = fmaxf(mx, mo);
+  float mt[2] = {mx, mx}, es[2] = {exp_scale, exp_scale};  // of the lane's tokens in the two tiles
+  swap_rows16(mt[0], mt[1]);
+  swap_rows16(es[0], es[1]);
+  unsigned arg[2];
+  float sum[2];
+#pragma unroll
+  for (int c = 0; c < kC; ++c) {
+    arg[c] = 0x7fffffffu;
+#pragma unroll
+    for (int a = 3; a >= 0; --a)
+#pragma unroll
+      for (int r = 3; r >= 0; --r) arg[c] = acc[c][a][r] == mt[c] ? (unsigned)(vrow0 + 16 * a + 4 * lq + r) : arg[c];
+    const float safe = mt[c] == -INFINITY ? 0.f : mt[c];
+    sum[c] = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[c] += __builtin_amdgcn_exp2f((acc[c][a][r] - safe) * es[c]);
   }
+  if (kC == 1) { arg[1] = arg[0]; sum[1] = sum[0]; }
+  swap_rows16(arg[0], arg[1]);
+  arg[0] = arg[1] = min(arg[0], arg[1]);
+  swap_halves32(arg[0], arg[1]);
+  swap_rows16(sum[0], sum[1]);
+  sum[0] = sum[1] = sum[0] + sum[1];
+  swap_halves32(sum[0], sum[1]);
+  mx_out = mx;
+  sum_out = sum[0] + sum[1];
+  arg_out = (int)min(arg[0], arg[1]);
+#pragma unroll
+  for (int c = 0; c < kC; ++c)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) *(f32x4_t*)(tb + (16 * c + li) * 256 + (((4 * a + lq) ^ li) * 16)) = acc[c][a];
+  lm_store_tile<16 * kC>(tb, vrow0, V, mrow0, M, v_whole, logits, vec_ok, lane);
 }
 
 // exp2 scale log2(e) / T of token row m: the call's scalar, or - with one temperature per request (temps[b],
