@@ -118,14 +118,7 @@ __device__ __forceinline__ float dot8_bf16(const u32x4_t a, const u32x4_t b, flo
 // row past the group has lse = +inf, so both give p = 0 without a select.
 __device__ __forceinline__ void tile_p_ds(f32x16_t s_acc, const f32x16_t dp_acc, float p[16], float ds[16], float scale_log2,
                                           float lse2, float dlt, unsigned long long anc, int j0, int prefix, int L, int lh) {
-  if (j0 + kAtTile > prefix) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = j0 + 8 * (r >> 2) + 4 * lh + (r & 3);
-      const bool seen = j < prefix || (j < L && ((anc >> (j - prefix)) & 1ull));
-      s_acc[r] = seen ? s_acc[r] : -INFINITY;
-    }
-  }
+  if (j0 + kAtTile > prefix) mask_scores(s_acc, j0, prefix, L, anc, lh);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     p[r] = __builtin_amdgcn_exp2f(fmaf(s_acc[r], scale_log2, -lse2));
@@ -463,11 +456,14 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
     const int ntile = t1 - t0;
     const int32_t* bt = block_table + (size_t)b * max_pages;
     // this wavefront's eighth of a tile pair's loads: one row group (four token rows) of K and one of V
-    auto issue_eighth = [&](int tt) {
+    auto tile_pages = [&](int tt) {  // scalar loads, a step ahead of their use
+      const int j0 = start + min(tt, ntile - 1) * kAtTile;
+      return make_int2(bt[j0 >> page_shift], bt[min(j0 + 16, L - 1) >> page_shift]);
+    };
+    auto issue_eighth = [&](int tt, int2 pages) {
       const int tl = min(tt, ntile - 1);
       const int j0 = start + tl * kAtTile;
-      const int pid_a = bt[j0 >> page_shift];
-      const int pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
+      const int pid_a = pages.x, pid_b = pages.y;
       char* kb = kv + (tt % 3) * kBsKvBytes;
       issue_rows<true>(kp, kb, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
       issue_rows<true>(vp, kb + kAtTileBytes, wv8, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
@@ -516,8 +512,10 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       for (int r = 0; r < 16; ++r) dq_acc[db][r] = 0.f;
 
     __syncthreads();  // query rows staged; the previous run is done with every buffer
-    issue_eighth(0);
-    issue_eighth(1);
+    int2 pg_stored = make_int2(0, 0), pg_now = tile_pages(0), pg_next = tile_pages(1);  // of tiles s - 1, s, s + 1
+    issue_eighth(0, pg_now);
+    issue_eighth(1, pg_next);
+    int2 pg_asked = tile_pages(2);  // s + 2
     if (m_row < R) {
       dlt = s_delta[m_row];
       anc = ancestor_mask(parents ? s_par : nullptr, m_row / G, Nq);
@@ -527,7 +525,8 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       __builtin_amdgcn_s_waitcnt((7 << 4) | (3 << 14) | 15);      // lgkmcnt(0): LDS reads and writes of the last step
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      issue_eighth(s + 2);  // into the buffer tile s - 1 used
+      issue_eighth(s + 2, pg_asked);  // into the buffer tile s - 1 used
+      const int2 pg_after = tile_pages(s + 3);
       if ((s & 1) == grp) {
         if (s < ntile) {
           const char* kb = kv + (s % 3) * kBsKvBytes;
@@ -545,8 +544,7 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
       } else if (s >= 1) {
         // columns 32 wv .. 32 wv + 31 of dV = P^T dO and dK = dS^T Q of tile s - 1, contraction over all four row tiles
         const int j0 = start + (s - 1) * kAtTile;
-        const int pa = bt[j0 >> page_shift];
-        const int pb = bt[min(j0 + 16, L - 1) >> page_shift];
+        const int pa = pg_stored.x, pb = pg_stored.y;
         f32x16_t dv_acc, dk_acc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dv_acc[r] = 0.f; dk_acc[r] = 0.f; }
@@ -569,6 +567,10 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
           }
         }
       }
+      pg_stored = pg_now;
+      pg_now = pg_next;
+      pg_next = pg_asked;
+      pg_asked = pg_after;
     }
     // ---- the two groups' dq of a row tile are summed through LDS; group 0 writes the run's partial -----------
     WAIT_VMCNT(0);  // the clamped requests of the last steps have landed: the tile buffers can be reused

@@ -427,16 +427,23 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
 
     // this wavefront's eighth of a step: load instruction `wave` of K and of V, for both tiles of the step
     // (a tile past the end of the sequence re-reads the last one; it is never multiplied)
+    // page ids of the step's two tiles: scalar loads, a step ahead of their use
+    int pid[2][2];
+    auto j0_of = [&](int sidx, int g) { return min(start + (2 * sidx + g) * kAtTile, last_tile_start); };
+    auto fetch_pages = [&](int sidx) {
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        pid[g][0] = bt[j0_of(sidx, g) >> page_shift];
+        pid[g][1] = bt[min(j0_of(sidx, g) + 16, L - 1) >> page_shift];
+      }
+    };
     auto issue_step = [&](int sidx) {
       char* stage = ring + (sidx % kWideStages) * kWideStageBytes;
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        const int j0 = min(start + (2 * sidx + g) * kAtTile, last_tile_start);
-        const int pid_a = bt[j0 >> page_shift];
-        const int pid_b = bt[min(j0 + 16, L - 1) >> page_shift];
         char* kb = stage + g * (2 * kAtTileBytes);
-        issue_rows<false>(kp, kb, wave, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
-        issue_rows<true>(vp, kb + kAtTileBytes, wave, j0, L, page_shift, Hkv, hk, pid_a, pid_b, lane);
+        issue_rows<false>(kp, kb, wave, j0_of(sidx, g), L, page_shift, Hkv, hk, pid[g][0], pid[g][1], lane);
+        issue_rows<true>(vp, kb + kAtTileBytes, wave, j0_of(sidx, g), L, page_shift, Hkv, hk, pid[g][0], pid[g][1], lane);
       }
     };
 
@@ -455,16 +462,6 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
       __syncthreads();
       if constexpr (kFp8KV) load_q_frags8(qf, qtile, li, lh); else load_q_frags(qf, qtile, li, lh);
       anc = ancestor_mask(parents ? s_par : nullptr, node, Nq);
-    };
-    auto compute_step = [&](int sidx) {
-      const int tt = 2 * sidx + grp;
-      if (rt_ok && tt < ntile) {
-        const char* kb = ring + (sidx % kWideStages) * kWideStageBytes + grp * (2 * kAtTileBytes);
-        const f32x16_t s_acc = tile_scores_qreg(kb, qf, li, lh);
-        bf16x8_t pb2[2];
-        tile_softmax(s_acc, st, pb2, scale_log2, start + tt * kAtTile, prefix, L, anc, lh);
-        tile_pv(kb + kAtTileBytes, pb2, st, lane);
-      }
     };
     if constexpr (kFp8KV) {
       // a wavefront's eighth of a step: eight token rows of K and of V of one of the step's two tiles
@@ -502,15 +499,29 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
         asm volatile("" ::: "memory");
       }
     } else {
-      for (int i = 0; i < kWideStages - 1 && i < nstep; ++i) issue_step(i);
+      for (int i = 0; i < kWideStages - 1 && i < nstep; ++i) {
+        fetch_pages(i);
+        issue_step(i);
+      }
+      fetch_pages(kWideStages - 1);
       stage_query();
       for (int sidx = 0; sidx < nstep; ++sidx) {
         // steps sidx+1 .. sidx+kWideStages-2 may stay in flight; near the end of the segment fewer were issued
         if (nstep - 1 - sidx >= kWideStages - 2) WAIT_VMCNT(4 * (kWideStages - 2)); else WAIT_VMCNT(0);
         __builtin_amdgcn_s_barrier();  // step complete from all eight wavefronts; the previous step's stage is free
         asm volatile("" ::: "memory");
-        if (sidx + kWideStages - 1 < nstep) issue_step(sidx + kWideStages - 1);
-        compute_step(sidx);
+        if (sidx + kWideStages - 1 < nstep) {  // (after the scores' products instead: 2 to 4 % slower)
+          issue_step(sidx + kWideStages - 1);
+          fetch_pages(sidx + kWideStages);
+        }
+        const int tt = 2 * sidx + grp;
+        if (rt_ok && tt < ntile) {
+          const char* kb = ring + (sidx % kWideStages) * kWideStageBytes + grp * (2 * kAtTileBytes);
+          const f32x16_t s_acc = tile_scores_qreg(kb, qf, li, lh);
+          bf16x8_t pb2[2];
+          tile_softmax(s_acc, st, pb2, scale_log2, start + tt * kAtTile, prefix, L, anc, lh);
+          tile_pv(kb + kAtTileBytes, pb2, st, lane);
+        }
         asm volatile("" ::: "memory");
       }
     }
