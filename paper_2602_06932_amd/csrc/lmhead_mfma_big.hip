@@ -422,8 +422,9 @@ template <bool kFp8>
 static hipError_t launch_big_dt(const AcceptLaunch& a, hipStream_t st) {
   int m_tiles, nta, ntb, n_a;
   lmhead_mfma_big_geometry((int)a.plan.rows, &m_tiles, &nta, &ntb, &n_a);
-  // (lm_many_rows: one column of 161 to 256 rows, or eleven tiles and more in several)
+  // (lm_many_rows: one column of 129 to 256 rows, or eleven tiles and more in several)
   switch (m_tiles == 1 ? nta : nta * 10 + ntb) {
+    case 5: return launch_big_t<kFp8, 5, 5, true>(a, st, m_tiles, n_a);
     case 6: return launch_big_t<kFp8, 6, 6, true>(a, st, m_tiles, n_a);
     case 7: return launch_big_t<kFp8, 7, 7, true>(a, st, m_tiles, n_a);
     case 8: return launch_big_t<kFp8, 8, 8, true>(a, st, m_tiles, n_a);

@@ -5,7 +5,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-ROWS = [1, 16, 17, 33, 65, 97, 129, 160, 161, 193, 225, 256, 257, 320, 321, 353, 385, 417, 449, 512, 513, 641]
+ROWS = [1, 16, 17, 33, 65, 97, 128, 129, 160, 161, 193, 225, 256, 257, 320, 321, 353, 385, 417, 449, 512, 513, 641]
 
 
 def _check(av, rows, vocab, hidden, fp8, seed):
