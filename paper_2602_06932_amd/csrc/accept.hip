@@ -107,9 +107,9 @@ struct AcceptParams {
   int Nq, V, n_tiles, slices, gmul, ngroups;
   float temperature;
   const float* logits;
-  const float* pmax;
-  const float* psum;
-  const int32_t* parg;
+  float* pmax;
+  float* psum;
+  int32_t* parg;
   const int32_t* tok;
   const float* q;       // draft probabilities, row stride Vq
   const int32_t* t2d;   // target id -> index into a row of q, or -1 (q = 0 there); NULL: q rows are dense over V
@@ -196,6 +196,64 @@ __device__ __forceinline__ void merge_row_stats(const AcceptParams& P, size_t ro
     for (int o = kWave / 2; o > 0; o >>= 1) mt = min(mt, __shfl_xor(mt, o, kWave));
     *out_arg = P.parg[row * nt + (mt < nt ? mt : 0)];
   }
+}
+
+// The same from the logits themselves, where no kernel has formed the tile statistics (generic LM head, small vocabulary), which
+// are left behind as that kernel leaves them: per tile the maximum, its lowest index and the sum of exp((l - max) / T).
+constexpr int kRowStatTiles = 2;
+__device__ __forceinline__ void form_row_stats(const AcceptParams& P, size_t row, double T, int lane, float* out_max,
+                                               double* out_lse, int* out_arg) {
+  const int V = P.V, nt = P.n_tiles;
+  const float* lr = P.logits + row * V;
+  const float inv_t = 1.f / (float)T;
+  const bool vec = (V & 3) == 0;
+  float tile_m = -INFINITY, tile_s = 0.f;  // lane t: those of tile t
+  int tile_arg = 0x7fffffff;
+#pragma unroll 1
+  for (int t = 0; t < nt; ++t) {
+    float x[16];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int v = t * kRowStatTile + c * 256 + lane * 4;
+      if (vec && v < V) {
+        const f32x4_t y = *(const f32x4_t*)(lr + v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * c + e] = y[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * c + e] = v + e < V ? lr[v + e] : -INFINITY;
+      }
+    }
+    float mx = x[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+    mx = wave_max(mx);
+    int at = 0x7fffffff;
+#pragma unroll
+    for (int i = 15; i >= 0; --i) at = x[i] == mx ? t * kRowStatTile + (i >> 2) * 256 + lane * 4 + (i & 3) : at;
+    at = wave_min(at);
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum += x[i] > -INFINITY ? __expf((x[i] - mx) * inv_t) : 0.f;
+    sum = wave_sum(sum);
+    if (lane == t) {
+      tile_m = mx;
+      tile_s = sum;
+      tile_arg = at;
+    }
+  }
+  if (lane < nt) {
+    P.pmax[row * nt + lane] = tile_m;
+    P.psum[row * nt + lane] = tile_s;
+    P.parg[row * nt + lane] = tile_arg;
+  }
+  const float m = wave_max(tile_m);
+  const double md = m > -INFINITY ? (double)m : 0.0, c = 1.4426950408889634 / T;
+  const double s = wave_sum(tile_m > -INFINITY ? (double)tile_s * (double)__builtin_amdgcn_exp2f((float)(((double)tile_m - md) * c)) : 0.0);
+  *out_max = m;
+  *out_lse = (double)m / T + log(s);
+  const int arg = wave_min(tile_m == m ? tile_arg : 0x7fffffff);
+  *out_arg = arg < V ? arg : 0;
 }
 
 // ============================================================================================
@@ -372,6 +430,8 @@ __device__ __forceinline__ void chain_pick(const AcceptParams& P, int b, int row
 // statistics of the request's rows, evaluate the k accept tests in parallel in fp64, find the first
 // failure - then sums the draw weights over its slice of the vocabulary.  Slice 0 writes the
 // per-request outputs and the state the draw kernel needs.
+// kForm: the tile statistics are formed here too.
+template <bool kForm>
 __global__ __launch_bounds__(kSweepThreads) void accept_chain_sweep(AcceptParams P) {
   __shared__ double s_lse[kMaxNq];
   __shared__ int s_ok[kMaxNq], s_arg[kMaxNq];
@@ -395,7 +455,8 @@ __global__ __launch_bounds__(kSweepThreads) void accept_chain_sweep(AcceptParams
   }
   for (int n = wv; n < Nq; n += kSweepThreads / kWave) {
     float mx; double lse; int arg;
-    merge_row_stats(P, row0 + n, T, lane, &mx, &lse, &arg, greedy);
+    if constexpr (kForm) form_row_stats(P, row0 + n, T, lane, &mx, &lse, &arg);
+    else merge_row_stats(P, row0 + n, T, lane, &mx, &lse, &arg, greedy);
     if (lane == 0) { s_lse[n] = lse; s_arg[n] = arg; }
   }
   __syncthreads();
@@ -997,6 +1058,14 @@ static int tree_slices_for(int B, int ngroups, bool wor, int cus) {
   return s >= 2 ? s : 1;
 }
 
+// A request's only workgroup can form its rows' statistics from the logits (16 floats a lane and tile) and save a launch, while
+// the tiles are few: each is a chain of reductions.  2 requests x 5 rows, step, us, with the launch and without: 2003 logits
+// 44.8, 42.7, 4096 45.9, 47.1; 4 x 5 rows, 1024 26.9, 18.0 (with the shared launch in front, generic LM head), 8192 65.8, 73.7.
+bool accept_forms_stats(const AcceptLaunch& a) {
+  return (a.temperature > 0.f || a.temps) && !a.parents && a.plan.slices == 1 && a.plan.stat_tile == kRowStatTile &&
+         a.plan.n_tiles <= kRowStatTiles;
+}
+
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
   AcceptParams P = {};
   P.Nq = a.Nq; P.V = a.V; P.n_tiles = a.plan.n_tiles; P.temperature = a.temperature;
@@ -1041,7 +1110,8 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {
 #undef AURORA_TREE
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(accept_chain_sweep, dim3(P.slices, a.B), dim3(kSweepThreads), 0, st, P);
+  if (a.form_stats) hipLaunchKernelGGL(accept_chain_sweep<true>, dim3(1, a.B), dim3(kSweepThreads), 0, st, P);
+  else hipLaunchKernelGGL(accept_chain_sweep<false>, dim3(P.slices, a.B), dim3(kSweepThreads), 0, st, P);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || P.slices == 1) return e;
   hipLaunchKernelGGL(accept_chain_pick, dim3(a.B), dim3(kSmallThreads), 0, st, P);

@@ -100,7 +100,7 @@ AcceptPlan plan_accept(const aurora_accept_desc* d) {
   AcceptPlan p = {};
   p.rows = (int64_t)d->batch * d->num_q;
   AcceptLaunch probe = accept_launch_from(d);
-  p.stat_tile = lmhead_mfma_supported(probe) ? lmhead_mfma_stat_tile() : 1024;
+  p.stat_tile = lmhead_mfma_supported(probe) ? lmhead_mfma_stat_tile() : kRowStatTile;
   p.n_tiles = (d->vocab + p.stat_tile - 1) / p.stat_tile;
   const size_t rows = (size_t)p.rows;
   p.logits_off = 0;
@@ -126,9 +126,11 @@ AcceptPlan plan_accept(const aurora_accept_desc* d) {
 
 bool misaligned(const void* p) { return ((uintptr_t)p & 255u) != 0; }
 
-int run_attn(const aurora_attn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
-             const int32_t* block_table, const int32_t* seq_lens, const int32_t* parents, void* out,
-             void* workspace, size_t workspace_bytes, hipStream_t st, float* lse_out = nullptr) {
+// Checks the arguments and fills the launch record; a.B == 0 says that there is nothing to do.
+int prepare_attn(const aurora_attn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
+                 const int32_t* block_table, const int32_t* seq_lens, const int32_t* parents, void* out,
+                 void* workspace, size_t workspace_bytes, float* lse_out, AttnLaunch& a) {
+  a = {};
   int rc = check_attn_desc(desc);
   if (rc != AURORA_OK) return rc;
   if (desc->batch == 0) return AURORA_OK;
@@ -136,7 +138,7 @@ int run_attn(const aurora_attn_desc* desc, const void* q, const void* k_pages, c
   if (((uintptr_t)q | (uintptr_t)k_pages | (uintptr_t)v_pages | (uintptr_t)out) & 15) return AURORA_ERR_INVALID_ARG;
   AttnPlan plan = plan_attn(desc);
   if (!workspace || misaligned(workspace) || workspace_bytes < plan.bytes) return AURORA_ERR_WORKSPACE;
-  AttnLaunch a = attn_launch_from(desc);
+  a = attn_launch_from(desc);
   a.q = q; a.k = k_pages; a.v = v_pages; a.block_table = block_table; a.seq_lens = seq_lens; a.parents = parents;
   a.out = out;
   a.lse_out = lse_out;
@@ -144,14 +146,28 @@ int run_attn(const aurora_attn_desc* desc, const void* q, const void* k_pages, c
   a.part_o = (float*)((char*)workspace + plan.part_o_off);
   a.part_ml = (float*)((char*)workspace + plan.part_ml_off);
   a.plan = plan;
-  hipError_t e = plan.mfma ? launch_attn_mfma(a, st) : launch_attn_generic(a, st);
+  return AURORA_OK;
+}
+
+int launch_attn(const AttnLaunch& a, hipStream_t st) {
+  if (a.B == 0) return AURORA_OK;
+  hipError_t e = a.plan.mfma ? launch_attn_mfma(a, st) : launch_attn_generic(a, st);
   return e == hipSuccess ? AURORA_OK : AURORA_ERR_HIP;
 }
 
+int run_attn(const aurora_attn_desc* desc, const void* q, const void* k_pages, const void* v_pages,
+             const int32_t* block_table, const int32_t* seq_lens, const int32_t* parents, void* out,
+             void* workspace, size_t workspace_bytes, hipStream_t st, float* lse_out = nullptr) {
+  AttnLaunch a;
+  int rc = prepare_attn(desc, q, k_pages, v_pages, block_table, seq_lens, parents, out, workspace, workspace_bytes, lse_out, a);
+  return rc == AURORA_OK ? launch_attn(a, st) : rc;
+}
+
+// at: the attention of the same call, not launched yet (goes in front of the LM head, or in one launch with it), or NULL
 int run_accept(const aurora_accept_desc* desc, const void* hidden, const void* lm_head, const int32_t* draft_tokens,
                const float* draft_probs, const float* uniforms, const int32_t* parents, int32_t* accept_len,
                int32_t* next_token, uint8_t* accept_mask, float* p_at_draft, float* row_lse, void* workspace,
-               size_t workspace_bytes, hipStream_t st, bool with_lmhead = true) {
+               size_t workspace_bytes, hipStream_t st, bool with_lmhead = true, const AttnLaunch* at = nullptr) {
   int rc = check_accept_desc(desc);
   if (rc != AURORA_OK) return rc;
   if (desc->batch == 0) return AURORA_OK;
@@ -179,10 +195,15 @@ int run_accept(const aurora_accept_desc* desc, const void* hidden, const void* l
   a.gsum = (double*)(ws + plan.gsum_off);
   a.lastpos = (int32_t*)(ws + plan.lastpos_off);
   a.plan = plan;
-  if (with_lmhead) {
-    hipError_t e = lmhead_mfma_supported(a) ? launch_lmhead_mfma(a, st) : launch_lmhead_generic(a, st);
-    if (e != hipSuccess) return AURORA_ERR_HIP;
-  }
+  const bool generic = with_lmhead && !lmhead_mfma_supported(a);
+  const bool front = at && generic && !at->plan.mfma && verify_front_supported(*at, a);
+  if (at && !front && (rc = launch_attn(*at, st)) != AURORA_OK) return rc;
+  a.form_stats = generic && accept_forms_stats(a);
+  hipError_t e = hipSuccess;
+  if (front) e = launch_verify_front(*at, a, st);
+  else if (with_lmhead) e = generic ? launch_lmhead_generic(a, st) : launch_lmhead_mfma(a, st);
+  if (e == hipSuccess && generic && !a.form_stats) e = launch_row_stats(a, st);
+  if (e != hipSuccess) return AURORA_ERR_HIP;
   return launch_accept(a, st) == hipSuccess ? AURORA_OK : AURORA_ERR_HIP;
 }
 
@@ -204,7 +225,9 @@ int run_lmhead(const aurora_accept_desc* desc, const void* hidden, const void* l
   a.parg = (int32_t*)(ws + plan.parg_off);
   a.hmax = (float*)(ws + plan.hmax_off);
   a.plan = plan;
-  hipError_t e = lmhead_mfma_supported(a) ? launch_lmhead_mfma(a, st) : launch_lmhead_generic(a, st);
+  if (lmhead_mfma_supported(a)) return launch_lmhead_mfma(a, st) == hipSuccess ? AURORA_OK : AURORA_ERR_HIP;
+  hipError_t e = launch_lmhead_generic(a, st);
+  if (e == hipSuccess) e = launch_row_stats(a, st);
   return e == hipSuccess ? AURORA_OK : AURORA_ERR_HIP;
 }
 
@@ -340,12 +363,12 @@ int aurora_verify(const aurora_attn_desc* attn_desc, const aurora_accept_desc* a
       return AURORA_ERR_INVALID_ARG;
     if ((accept_desc->temperature > 0.f || accept_desc->temperatures) && (!draft_probs || !uniforms)) return AURORA_ERR_INVALID_ARG;
   }
-  rc = run_attn(attn_desc, q, k_pages, v_pages, block_table, seq_lens, parents, attn_out, workspace, attn_bytes,
-                (hipStream_t)hip_stream);
+  AttnLaunch at;
+  rc = prepare_attn(attn_desc, q, k_pages, v_pages, block_table, seq_lens, parents, attn_out, workspace, attn_bytes, nullptr, at);
   if (rc != AURORA_OK) return rc;
   return run_accept(accept_desc, hidden, lm_head, draft_tokens, draft_probs, uniforms, parents, accept_len,
                     next_token, accept_mask, p_at_draft, row_lse, (char*)workspace + attn_bytes, acc_bytes,
-                    (hipStream_t)hip_stream);
+                    (hipStream_t)hip_stream, true, &at);
 }
 
 const float* aurora_verify_logits_ptr(const aurora_attn_desc* attn_desc, const aurora_accept_desc* accept_desc,

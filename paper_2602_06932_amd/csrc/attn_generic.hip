@@ -9,31 +9,11 @@
 // that are all in flight together, the page look-up is done once per token and kept for the value pass, reductions take two
 // barriers, and where a request fits one split the workgroup writes the output itself.  4 requests x 5 positions x 8 heads
 // over 256 tokens, fp32: 27 us + 4.8 us for the merge (one 4-byte load at a time, a division per element) -> 9.7 us.
-#include "common.hpp"
+#include "generic_tile.hpp"
 #include "launch.hpp"
 
 namespace aurora {
 
-constexpr int kGenThreads = 256;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-// Sixteen bytes of a stored row, widened to fp32: 4 float32, 8 bfloat16 or 16 E4M3 elements.
-template <typename TKV> struct Vec16 { static constexpr int n = 16 / (int)sizeof(TKV); float x[16 / sizeof(TKV)]; };
-template <typename TKV>
-__device__ __forceinline__ Vec16<TKV> load16(const TKV* p) {
-  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-  const u32x4_t raw = *(const u32x4_t*)p;
-  TKV e[Vec16<TKV>::n];
-  __builtin_memcpy(e, &raw, 16);
-  Vec16<TKV> r;
-#pragma unroll
-  for (int i = 0; i < Vec16<TKV>::n; ++i) r.x[i] = to_f32<TKV>(e[i]);
-  return r;
-}
-
-// TKV = T, or e4m3_t with k_scale / v_scale [Hkv]: the scale of the KV head multiplies the scores and
-// the weighted value sum (both are linear in it).  kD: head_dim.  kWhole: every request fits one split, out (and lse_out,
-// or NULL) are written here.
 template <typename T, typename TKV, int kD, bool kWhole>
 __global__ __launch_bounds__(kGenThreads) void attn_generic_partial(
     const T* __restrict__ q, const TKV* __restrict__ kp, const TKV* __restrict__ vp,
@@ -41,126 +21,9 @@ __global__ __launch_bounds__(kGenThreads) void attn_generic_partial(
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens,
     const int32_t* __restrict__ parents, float* __restrict__ part_o, float* __restrict__ part_ml, T* __restrict__ out,
     float* __restrict__ lse_out, int Nq, int Hq, int Hkv, int page, int max_pages, int split_len, int max_splits, float scale) {
-  constexpr int kWaves = kGenThreads / kWave;
-  __shared__ __attribute__((aligned(16))) float q_s[kD];
-  extern __shared__ __attribute__((aligned(16))) float sc[];  // split_len scores, then as many row numbers in the pools
-  __shared__ float s_max[kWaves], s_sum[kWaves];
-  __shared__ __attribute__((aligned(16))) f32x4_t s_o[kGenThreads];
-  __shared__ unsigned long long anc_s;
-  // (a pool has fewer than 2^32 rows of at least 64 bytes: K and V together would exceed the device's memory)
-  uint32_t* rows = (uint32_t*)(sc + split_len);
-
-  const int split = blockIdx.x, hq = blockIdx.y, bn = blockIdx.z;
-  const int b = bn / Nq, n = bn % Nq;
-  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
-  const int L = seq_lens[b];
-  const int start = split * split_len;
-  const size_t orow = (size_t)bn * Hq + hq;
-  if (start >= L) {
-    if (kWhole) {  // an empty request: zeros, as the merge of no partial gives
-      for (int d = tid; d < kD; d += kGenThreads) out[orow * kD + d] = from_f32<T>(0.f);
-      if (lse_out && tid == 0) lse_out[orow] = -INFINITY;
-    }
-    return;
-  }
-  const int end = min(L, start + split_len);
-  const int prefix = L - Nq;
-  const int hk = hq / (Hq / Hkv);
-  if (k_scale) scale *= k_scale[hk];
-  const float vs = v_scale ? v_scale[hk] : 1.f;
-
-  if (tid == 0) {
-    unsigned long long m = 0;
-    if (parents) {
-      for (int a = n, hops = 0; a >= 0 && hops <= Nq; a = parents[b * Nq + a], ++hops) m |= 1ull << a;
-    } else {
-      m = n == 63 ? ~0ull : ((1ull << (n + 1)) - 1);
-    }
-    anc_s = m;
-  }
-  for (int d = tid; d < kD; d += kGenThreads) q_s[d] = to_f32<T>(q[orow * kD + d]);
-  __syncthreads();
-  const unsigned long long anc = anc_s;
-
-  float lmax = -INFINITY;
-  for (int j = start + tid; j < end; j += kGenThreads) {
-    const bool seen = j < prefix || ((anc >> (j - prefix)) & 1ull);
-    float s = -INFINITY;
-    if (seen) {
-      const int pj = j / page;
-      const int pg = block_table[(size_t)b * max_pages + pj];
-      const uint32_t r = ((uint32_t)pg * Hkv + hk) * (uint32_t)page + (uint32_t)(j - pj * page);
-      rows[j - start] = r;
-      const TKV* kr = kp + (size_t)r * kD;
-      constexpr int kV = Vec16<TKV>::n;
-      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < kD / kV; ++c) {
-        const Vec16<TKV> k = load16(kr + c * kV);
-#pragma unroll
-        for (int e = 0; e < kV; e += 4) {
-          const f32x4_t qv = *(const f32x4_t*)(q_s + c * kV + e);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[i] = fmaf(qv[i], k.x[e + i], acc[i]);
-        }
-      }
-      s = ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale;
-    }
-    sc[j - start] = s;
-    lmax = fmaxf(lmax, s);
-  }
-  lmax = wave_max(lmax);
-  if (lane == 0) s_max[wv] = lmax;
-  __syncthreads();
-  float m = s_max[0];
-#pragma unroll
-  for (int i = 1; i < kWaves; ++i) m = fmaxf(m, s_max[i]);
-  float lsum = 0.f;
-  for (int j = start + tid; j < end; j += kGenThreads) {
-    const float s = sc[j - start];
-    const float p = (s == -INFINITY) ? 0.f : __expf(s - m);
-    sc[j - start] = p;
-    lsum += p;
-  }
-  lsum = wave_sum(lsum);
-  if (lane == 0) s_sum[wv] = lsum;
-  __syncthreads();
-  float l = s_sum[0];
-#pragma unroll
-  for (int i = 1; i < kWaves; ++i) l += s_sum[i];
-
-  // weighted value sum: thread (d4, g) adds columns 4 d4 .. of the positions j == g (mod groups)
-  constexpr int kD4 = kD / 4, kGroups = kGenThreads / kD4;
-  const int d4 = tid % kD4, g = tid / kD4;
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int j = g; j < end - start; j += kGroups) {
-    const float p = sc[j];
-    if (p != 0.f) {
-      const TKV* vr = vp + (size_t)rows[j] * kD + 4 * d4;
-      TKV e[4];
-      __builtin_memcpy(e, __builtin_assume_aligned(vr, 4 * sizeof(TKV)), 4 * sizeof(TKV));
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = fmaf(p, to_f32<TKV>(e[i]), acc[i]);
-    }
-  }
-  s_o[tid] = acc;
-  __syncthreads();
-  if (g != 0) return;
-#pragma unroll
-  for (int gg = 1; gg < kGroups; ++gg) acc += s_o[gg * kD4 + d4];
-  if constexpr (kWhole) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) out[orow * kD + 4 * d4 + i] = from_f32<T>(l > 0.f ? acc[i] * vs / l : 0.f);
-    if (lse_out && tid == 0) lse_out[orow] = l > 0.f ? m + __logf(l) : -INFINITY;
-  } else {
-    const size_t pidx = orow * max_splits + split;
-    *(f32x4_t*)(part_o + pidx * kD + 4 * d4) = acc * vs;
-    if (tid == 0) {
-      part_ml[pidx * 2 + 0] = m;
-      part_ml[pidx * 2 + 1] = l;
-    }
-  }
+  attn_generic_part<T, TKV, kD, kWhole>(blockIdx.x, blockIdx.y, blockIdx.z, q, kp, vp, k_scale, v_scale, block_table, seq_lens,
+                                        parents, part_o, part_ml, out, lse_out, Nq, Hq, Hkv, page, max_pages, split_len,
+                                        max_splits, scale);
 }
 
 // Merge the per-split partials of one (request, node, query head): out = sum_s e^{m_s-M} O_s / sum_s e^{m_s-M} l_s.

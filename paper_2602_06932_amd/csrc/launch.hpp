@@ -40,6 +40,7 @@ struct AcceptLaunch {
   float* hmax;  // [rows, n_tiles * kLmHalfPerTile] maxima of groups of 32 vocabulary entries (matrix-core LM head only)
   double *st_lse, *gsum;
   int32_t *st_row, *st_rej, *lastpos;
+  bool form_stats;  // launch_accept: the logits are there, their tile statistics are not (accept_forms_stats)
   AcceptPlan plan;
 };
 
@@ -63,11 +64,17 @@ constexpr int kLmHalfPerTile = 8;     // groups of 32 vocabulary rows per 256-ro
 inline bool lm_many_rows(int64_t rows) { return rows > 256 ? rows > 320 : rows > 128; }
 bool lmhead_mfma_big_supported(const AcceptLaunch& a);
 hipError_t launch_lmhead_mfma_big(const AcceptLaunch& a, hipStream_t st);
-hipError_t launch_lmhead_generic(const AcceptLaunch& a, hipStream_t st);
+hipError_t launch_lmhead_generic(const AcceptLaunch& a, hipStream_t st);  // logits alone
+constexpr int kRowStatTile = 1024;  // vocabulary entries of a statistics tile where the generic LM head runs
+hipError_t launch_row_stats(const AcceptLaunch& a, hipStream_t st);       // their tile statistics
+// attention and generic LM head (logits alone) of a small float32 call in one launch
+bool verify_front_supported(const AttnLaunch& at, const AcceptLaunch& a);
+hipError_t launch_verify_front(const AttnLaunch& at, const AcceptLaunch& a, hipStream_t st);
 
 // acceptance walk + residual / bonus draw
 void accept_chain_geometry(int batch, int vocab, int* slices, int* gmul, int* ngroups);
 int accept_tree_max_slices();  // workgroups per request the tree walk may use (sizes its exchange buffers)
+bool accept_forms_stats(const AcceptLaunch& a);  // whether launch_accept can do without the tile statistics
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st);
 
 // trace emission: top-K target logits per token row, y_out and rejection trajectory

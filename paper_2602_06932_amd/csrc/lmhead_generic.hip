@@ -1,7 +1,7 @@
 // Generic LM-head projection (fp32 FMA, fp32 or bf16 storage) followed by per-tile softmax
 // statistics.  It is the fp32 path of the library and the fallback for shapes the MFMA kernel
 // does not cover.  logits[m, v] = sum_h hidden[m, h] * W[v, h]  (appendix A.1, eq. 4: l in R^{T x V}).
-#include "common.hpp"
+#include "generic_tile.hpp"
 #include "launch.hpp"
 
 namespace aurora {
@@ -54,72 +54,28 @@ __global__ __launch_bounds__(256) void lmhead_generic(const T* __restrict__ hidd
   }
 }
 
-// The same product for few token rows: 64 x 64 tiles would leave most of the chip idle (16 workgroups on 20 x 1024) and walk
-// the hidden dimension in steps of 16 with two barriers each.  Here a workgroup takes 16 vocabulary rows x 32 token rows and
-// 64 hidden elements per step, the next step's operands being loaded into registers (16 bytes a thread) while the present
-// ones are multiplied out of LDS; a thread owns one vocabulary row and two token rows.  20 x 1024 x 256 in fp32: 25 -> 6 us.
-constexpr int kSM = 32, kSN = 16, kSK = 64, kSPad = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void lmhead_generic_few(const T* __restrict__ hidden, const T* __restrict__ w,
                                                           float* __restrict__ logits, int64_t M, int H, int V) {
-  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-  __shared__ __attribute__((aligned(16))) float As[kSM][kSK + kSPad];
-  __shared__ __attribute__((aligned(16))) float Bs[kSN][kSK + kSPad];
-  const int tid = threadIdx.x;
-  const int v0 = blockIdx.x * kSN;
-  const int64_t m0 = (int64_t)blockIdx.y * kSM;
-  // staging: thread (r, c) brings elements 4c .. of rows r, r + 16 of the token tile and of row r of the vocabulary tile
-  const int r = tid >> 4, c = (tid & 15) * 4;
-  const bool vec = (H & 3) == 0;
-  auto fetch = [&](const T* p, bool ok, int k) -> f32x4_t {
-    f32x4_t x = {0.f, 0.f, 0.f, 0.f};
-    if (ok && vec) {  // rows start at multiples of four elements
-      if (k < H) {
-        T t[4];
-        __builtin_memcpy(t, __builtin_assume_aligned(p + k, 4 * sizeof(T)), 4 * sizeof(T));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = to_f32<T>(t[e]);
-      }
-    } else if (ok) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (k + e < H) x[e] = to_f32<T>(p[k + e]);
-    }
-    return x;
-  };
-  const int64_t ma = m0 + r, mb = m0 + r + 16;
-  const T* pa = hidden + (ma < M ? ma : 0) * H;
-  const T* pb = hidden + (mb < M ? mb : 0) * H;
-  const T* pw = w + (int64_t)(v0 + r < V ? v0 + r : 0) * H;
-  const int n = tid & 15, mm = tid >> 4;  // this thread's vocabulary row; token rows mm and mm + 16
-  f32x4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-  f32x4_t xa = fetch(pa, ma < M, c), xb = fetch(pb, mb < M, c), xw = fetch(pw, v0 + r < V, c);
-  for (int k0 = 0; k0 < H; k0 += kSK) {
-    *(f32x4_t*)&As[r][c] = xa;
-    *(f32x4_t*)&As[r + 16][c] = xb;
-    *(f32x4_t*)&Bs[r][c] = xw;
-    __syncthreads();
-    if (k0 + kSK < H) {
-      xa = fetch(pa, ma < M, k0 + kSK + c);
-      xb = fetch(pb, mb < M, k0 + kSK + c);
-      xw = fetch(pw, v0 + r < V, k0 + kSK + c);
-    }
-#pragma unroll
-    for (int k = 0; k < kSK; k += 4) {
-      const f32x4_t wv = *(const f32x4_t*)&Bs[n][k];
-      const f32x4_t a0 = *(const f32x4_t*)&As[mm][k], a1 = *(const f32x4_t*)&As[mm + 16][k];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc0[e] = fmaf(a0[e], wv[e], acc0[e]);
-        acc1[e] = fmaf(a1[e], wv[e], acc1[e]);
-      }
-    }
-    __syncthreads();
-  }
-  const int v = v0 + n;
-  if (v < V) {
-    if (m0 + mm < M) logits[(m0 + mm) * V + v] = (acc0[0] + acc0[1]) + (acc0[2] + acc0[3]);
-    if (m0 + mm + 16 < M) logits[(m0 + mm + 16) * V + v] = (acc1[0] + acc1[1]) + (acc1[2] + acc1[3]);
+  lmhead_few_tile<T>(blockIdx.x, blockIdx.y, hidden, w, logits, M, H, V);
+}
+
+// Attention and LM head of a small call in one launch (float32, every request one split, few token rows): workgroups
+// [0, lm_x lm_y) take the head's tiles, the others a (request x node, query head) each.  Both are chains of memory round trips
+// that leave most of the chip idle: side by side the longer one counts.  4 x 5 positions x 8 heads over 256 tokens and 20 x 1024
+// logits: 9 + 6 us and a launch -> 10 us.
+template <int kD>
+__global__ __launch_bounds__(kGenThreads) void verify_front_f32(AttnLaunch a, const float* __restrict__ hidden,
+                                                                const float* __restrict__ w, float* __restrict__ logits,
+                                                                int64_t M, int H, int V, int lm_x, int lm_y) {
+  const int wg = blockIdx.x, n_lm = lm_x * lm_y;
+  if (wg < n_lm) {
+    lmhead_few_tile<float>(wg % lm_x, wg / lm_x, hidden, w, logits, M, H, V);
+  } else {
+    const int i = wg - n_lm;
+    attn_generic_part<float, float, kD, true>(0, i % a.Hq, i / a.Hq, (const float*)a.q, (const float*)a.k, (const float*)a.v, nullptr,
+                                              nullptr, a.block_table, a.seq_lens, a.parents, nullptr, nullptr, (float*)a.out,
+                                              nullptr, a.Nq, a.Hq, a.Hkv, a.page, a.max_pages, a.plan.split_len, 1, a.scale);
   }
 }
 
@@ -170,12 +126,38 @@ __global__ __launch_bounds__(256) void row_tile_stats(const float* __restrict__ 
   }
 }
 
+// the small tiles while the large ones would fill less than half of the 256 compute units (a 64 x 64 tile re-reads its
+// operands a quarter as often, which counts once the chip is full)
+static bool few_rows(const AcceptLaunch& a) {
+  return (int64_t)((a.V + kTN - 1) / kTN) * ((a.plan.rows + kTM - 1) / kTM) < 128;
+}
+
+bool verify_front_supported(const AttnLaunch& at, const AcceptLaunch& a) {
+  return !at.bf16 && !at.kv_fp8 && !at.lse_out && at.plan.max_splits == 1 && !a.bf16 && !a.fp8 && few_rows(a);
+}
+
+hipError_t launch_verify_front(const AttnLaunch& at, const AcceptLaunch& a, hipStream_t st) {
+  const int lm_x = (a.V + kSN - 1) / kSN, lm_y = (int)((a.plan.rows + kSM - 1) / kSM);
+  const dim3 grid((unsigned)lm_x * lm_y + (unsigned)at.B * at.Nq * at.Hq);
+  const size_t lds = (size_t)at.plan.split_len * (sizeof(float) + sizeof(uint32_t));
+#define AURORA_FRONT(D)                                                                                                  \
+  hipLaunchKernelGGL(verify_front_f32<D>, grid, dim3(kGenThreads), lds, st, at, (const float*)a.hidden, (const float*)a.lm_head, \
+                     a.logits, a.plan.rows, a.H, a.V, lm_x, lm_y)
+  if (at.D == 64) AURORA_FRONT(64); else AURORA_FRONT(128);
+#undef AURORA_FRONT
+  return hipGetLastError();
+}
+
+hipError_t launch_row_stats(const AcceptLaunch& a, hipStream_t st) {
+  const float inv_t = a.temperature > 0.f ? 1.f / a.temperature : 1.f;
+  hipLaunchKernelGGL(row_tile_stats, dim3(a.plan.n_tiles, (unsigned)a.plan.rows), dim3(256), 0, st, a.logits, a.pmax, a.psum,
+                     a.parg, a.V, a.plan.stat_tile, a.plan.n_tiles, inv_t, a.temps, a.Nq);
+  return hipGetLastError();
+}
+
 hipError_t launch_lmhead_generic(const AcceptLaunch& a, hipStream_t st) {
   const int64_t M = a.plan.rows;
-  // the small tiles while the large ones would fill less than half of the 256 compute units (a 64 x 64 tile re-reads its
-  // operands a quarter as often, which counts once the chip is full)
-  const int64_t large = (int64_t)((a.V + kTN - 1) / kTN) * ((M + kTM - 1) / kTM);
-  if (large < 128) {
+  if (few_rows(a)) {
     dim3 grid((unsigned)((a.V + kSN - 1) / kSN), (unsigned)((M + kSM - 1) / kSM));
     if (a.bf16)
       hipLaunchKernelGGL(lmhead_generic_few<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)a.hidden,
@@ -192,11 +174,6 @@ hipError_t launch_lmhead_generic(const AcceptLaunch& a, hipStream_t st) {
       hipLaunchKernelGGL(lmhead_generic<float>, grid, dim3(256), 0, st, (const float*)a.hidden,
                          (const float*)a.lm_head, a.logits, M, a.H, a.V);
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const float inv_t = a.temperature > 0.f ? 1.f / a.temperature : 1.f;
-  hipLaunchKernelGGL(row_tile_stats, dim3(a.plan.n_tiles, (unsigned)M), dim3(256), 0, st, a.logits, a.pmax, a.psum,
-                     a.parg, a.V, a.plan.stat_tile, a.plan.n_tiles, inv_t, a.temps, a.Nq);
   return hipGetLastError();
 }
 

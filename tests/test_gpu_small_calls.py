@@ -1,0 +1,53 @@
+"""Small calls: a float32 step whose attention and LM head share a launch and whose acceptance forms the rows' statistics from the
+logits, against the same step in its three stages (statistics by a kernel of their own) and against the oracle."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("temps", [False, True])
+@pytest.mark.parametrize("batch,num_q,vocab,hidden,lens", [(1, 1, 1, 8, (1, 9)), (4, 5, 1024, 256, (256, 256)), (3, 7, 1023, 64, (7, 300)), (3, 4, 2048, 64, (9, 99)), (3, 4, 2049, 64, (9, 99)),
+                                                           (8, 2, 2003, 72, (64, 512)), (2, 5, 8192, 96, (30, 60)),
+                                                           # past one slice; past the small LM-head tiles; past one split
+                                                           (2, 5, 8193, 32, (30, 60)), (40, 8, 2048, 64, (20, 40)), (2, 4, 500, 64, (500, 700))])
+def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, lens, temps):
+    from paper_2602_06932_amd.device import DeviceVerify
+    from parity_util import check_accept, check_attention, check_logits
+    kw = {}
+    if temps:
+        kw = dict(draft="noisy_target", temperatures=np.array([0.0, 0.6, 1.0, 0.8] * batch, np.float32)[:batch])
+    seq = np.linspace(lens[0], lens[1], batch).astype(np.int32)
+    w = gen.make_workload(name="small", seed=40 + vocab, seq_lens=np.maximum(seq, num_q).astype(np.int32), recipe="", batch=batch, num_q=num_q,
+                          num_q_heads=8, num_kv_heads=2, head_dim=64, page_size=256, hidden_size=hidden, vocab=vocab,
+                          temperature=1.0, dtype=gen.F32, **{"draft": "independent", **kw})
+    one, parts = DeviceVerify(w), DeviceVerify(w)
+    one.workspace.fill_(255)  # (statistics that are read before they are written would be NaN)
+    parts.workspace.fill_(255)
+    one.verify()
+    parts.attn(), parts.lmhead(), parts.accept_logits()
+    torch.cuda.synchronize()
+    assert np.array_equal(one.attn_out_host(), parts.attn_out_host())
+    ref_o, ref_a = oracle.verify(w, want_cdf=True, want_logits=True)
+    check_attention(one.attn_out_host(), ref_o, w.dtype)
+    check_logits(one.logits_host(), ref_a.logits, w.dtype)
+    check_accept(one.results_host(), ref_a, w)
+    a, b = one.results_host(), parts.results_host()
+    for n in ("accept_len", "next_token", "accept_mask"):
+        assert np.array_equal(a[n], b[n]), n
+    # the two orders of a tile's float32 sums differ by a few of its 2^-24
+    assert np.abs(a["row_lse"] - b["row_lse"]).max() <= 2e-6 * max(1.0, np.abs(b["row_lse"]).max())
+    # the step leaves the statistics behind as the stages do: acceptance alone, on its part of the workspace
+    attn_bytes = gpu_lib.aurora_verify_logits_ptr(one.attn_desc, one.accept_desc, one.workspace) - \
+        gpu_lib.aurora_verify_logits_ptr(None, one.accept_desc, one.workspace)
+    one.accept_len.fill_(-1), one.next_token.fill_(-1)
+    gpu_lib.aurora_verify_accept_logits(one.accept_desc, one.draft_tokens, one.draft_probs, one.uniforms, None, one.accept_len,
+                                        one.next_token, one.accept_mask, one.p_at_draft, one.row_lse, one.workspace[attn_bytes:])
+    torch.cuda.synchronize()
+    c = one.results_host()
+    for n in a:
+        assert np.array_equal(a[n], c[n]) or np.abs(a[n] - c[n]).max() <= 1e-6, n
