@@ -60,11 +60,11 @@ __global__ __launch_bounds__(256) void lmhead_generic_few(const T* __restrict__ 
   lmhead_few_tile<T>(blockIdx.x, blockIdx.y, hidden, w, logits, M, H, V);
 }
 
-// Attention and LM head of a small call in one launch (float32, every request one split, few token rows): workgroups
-// [0, lm_x lm_y) take the head's tiles, the others a (request x node, query head) each.  Both are chains of memory round trips
+// Attention and LM head of a small call in one launch (float32, few token rows): workgroups [0, lm_x lm_y) take the head's
+// tiles, the others a (request x node, query head, split) each; kWhole: one split holds every request.  Both are chains of memory round trips
 // that leave most of the chip idle: side by side the longer one counts.  4 x 5 positions x 8 heads over 256 tokens and 20 x 1024
 // logits: 9 + 6 us and a launch -> 10 us.
-template <int kD>
+template <int kD, bool kWhole>
 __global__ __launch_bounds__(kGenThreads) void verify_front_f32(AttnLaunch a, const float* __restrict__ hidden,
                                                                 const float* __restrict__ w, float* __restrict__ logits,
                                                                 int64_t M, int H, int V, int lm_x, int lm_y) {
@@ -72,10 +72,11 @@ __global__ __launch_bounds__(kGenThreads) void verify_front_f32(AttnLaunch a, co
   if (wg < n_lm) {
     lmhead_few_tile<float>(wg % lm_x, wg / lm_x, hidden, w, logits, M, H, V);
   } else {
-    const int i = wg - n_lm;
-    attn_generic_part<float, float, kD, true>(0, i % a.Hq, i / a.Hq, (const float*)a.q, (const float*)a.k, (const float*)a.v, nullptr,
-                                              nullptr, a.block_table, a.seq_lens, a.parents, nullptr, nullptr, (float*)a.out,
-                                              nullptr, a.Nq, a.Hq, a.Hkv, a.page, a.max_pages, a.plan.split_len, 1, a.scale);
+    const int splits = kWhole ? 1 : a.plan.max_splits, split = (wg - n_lm) % splits, i = (wg - n_lm) / splits;
+    attn_generic_part<float, float, kD, kWhole>(split, i % a.Hq, i / a.Hq, (const float*)a.q, (const float*)a.k, (const float*)a.v,
+                                                nullptr, nullptr, a.block_table, a.seq_lens, a.parents, a.part_o, a.part_ml,
+                                                (float*)a.out, nullptr, a.Nq, a.Hq, a.Hkv, a.page, a.max_pages, a.plan.split_len,
+                                                splits, a.scale);
   }
 }
 
@@ -133,19 +134,27 @@ static bool few_rows(const AcceptLaunch& a) {
 }
 
 bool verify_front_supported(const AttnLaunch& at, const AcceptLaunch& a) {
-  return !at.bf16 && !at.kv_fp8 && !at.lse_out && at.plan.max_splits == 1 && !a.bf16 && !a.fp8 && few_rows(a);
+  // (one grid dimension holds the workgroups of both: fewer than 2^32 threads)
+  return !at.bf16 && !at.kv_fp8 && !at.lse_out && !a.bf16 && !a.fp8 && few_rows(a) &&
+         (int64_t)at.B * at.Nq * at.Hq * at.plan.max_splits < (1 << 23);
 }
 
 hipError_t launch_verify_front(const AttnLaunch& at, const AcceptLaunch& a, hipStream_t st) {
   const int lm_x = (a.V + kSN - 1) / kSN, lm_y = (int)((a.plan.rows + kSM - 1) / kSM);
-  const dim3 grid((unsigned)lm_x * lm_y + (unsigned)at.B * at.Nq * at.Hq);
+  const bool whole = at.plan.max_splits == 1;
+  const dim3 grid((unsigned)lm_x * lm_y + (unsigned)at.B * at.Nq * at.Hq * at.plan.max_splits);
   const size_t lds = (size_t)at.plan.split_len * (sizeof(float) + sizeof(uint32_t));
-#define AURORA_FRONT(D)                                                                                                  \
-  hipLaunchKernelGGL(verify_front_f32<D>, grid, dim3(kGenThreads), lds, st, at, (const float*)a.hidden, (const float*)a.lm_head, \
-                     a.logits, a.plan.rows, a.H, a.V, lm_x, lm_y)
-  if (at.D == 64) AURORA_FRONT(64); else AURORA_FRONT(128);
+#define AURORA_FRONT(D, WHOLE)                                                                                               \
+  hipLaunchKernelGGL((verify_front_f32<D, WHOLE>), grid, dim3(kGenThreads), lds, st, at, (const float*)a.hidden,              \
+                     (const float*)a.lm_head, a.logits, a.plan.rows, a.H, a.V, lm_x, lm_y)
+  if (at.D == 64) {
+    if (whole) AURORA_FRONT(64, true); else AURORA_FRONT(64, false);
+  } else {
+    if (whole) AURORA_FRONT(128, true); else AURORA_FRONT(128, false);
+  }
 #undef AURORA_FRONT
-  return hipGetLastError();
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || whole) return e;
+  return launch_attn_combine(at, st);
 }
 
 hipError_t launch_row_stats(const AcceptLaunch& a, hipStream_t st) {
