@@ -128,6 +128,7 @@ __device__ __forceinline__ void tile_p_ds(f32x16_t s_acc, const f32x16_t dp_acc,
 
 // kLocalPlan: every workgroup builds the tile prefix per request in LDS (up to kLocalPlanMax requests; workgroup 0
 // also writes it to PB for the dq merge); otherwise PB was filled by the planning kernel and is read from memory.
+constexpr int kBmWorkgroups = 256;
 constexpr int kBmPar = 4;  // tiles of a run that the wavefronts take at a time
 
 template <int kRT /* 32-row tiles of query rows per KV head: 1 or 2 */, bool kLocalPlan>
@@ -148,17 +149,10 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
   // they see (rows past the group see nothing).  Read per tile and row tile: eight registers a lane would be spilled otherwise.
   __shared__ float s_delta[32 * kRT], s_lse2[32 * kRT];
   __shared__ unsigned long long s_anc[32 * kRT];
-  bool by_run = false;
-  if (kLocalPlan) {
-    by_run = build_split<kBmThreads, kBmPar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
-    if (blockIdx.x == 0) publish_split(PB, s_pb, B, by_run, kBmThreads);
-  }
+  __shared__ int4 s_first;
+  SplitLens lens;
+  if constexpr (kLocalPlan) lens = load_split_lens(seq_lens, B);
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
-
-  const int U = pbv(B);  // units: runs, or tiles
-  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
-  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
-  if (u >= u_end) return;
 
   const int G = Hq / Hkv, R = G * Nq;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -170,19 +164,22 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
   char* dst = pt + kBmXtBytes;
   const float scale_log2 = scale * kLog2e;
 
-  int b = 0;
-  {
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (pbv(mid) <= u) lo = mid; else hi = mid - 1;
-    }
-    b = lo;
+  Share sh;
+  if constexpr (kLocalPlan) {
+    // every workgroup builds the split itself; the first one also publishes it for the merge kernel
+    sh = build_split<kBmThreads, kBmPar, kBmWorkgroups>(lens, B, Hkv, s_pb, s_wsum, &s_first);
+    if (blockIdx.x == 0) publish_split(PB, s_pb, B, sh.by_run, kBmThreads);
+  } else {
+    sh = load_split<kBmWorkgroups>(PB, seq_lens, B);
   }
+  const bool by_run = sh.by_run;
+  int u = sh.u, b = sh.b, L_next = sh.L;
+  const int u_end = sh.u_end;
+  if (u >= u_end) return;
 
   while (u < u_end) {
-    while (pbv(b + 1) <= u) ++b;
-    const int L = seq_lens[b];
+    while (pbv(b + 1) <= u) ++b;  // read again: two more scalars kept over a segment would be spilled
+    const int L = L_next;
     const int n_b = (L + kAtTile - 1) / kAtTile;
     const int rel = u - pbv(b);
     const int per_pair = by_run ? (n_b + kBmPar - 1) / kBmPar : n_b;
@@ -192,6 +189,11 @@ __global__ __launch_bounds__(kBmThreads, 1) void attn_bwd_mfma_kernel(
     const int t1 = min(n_b, t0 + (by_run ? kBmPar : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;
     u += by_run ? 1 : t1 - t0;
+    if (u < u_end) {  // the next segment's length, under this one
+      int bn = b;
+      while (pbv(bn + 1) <= u) ++bn;
+      L_next = seq_lens[bn];
+    }
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
@@ -408,17 +410,10 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
   __shared__ int2 s_wsum[kB8Threads / kWave];
   __shared__ int s_par[kMaxNq];    // the request's tree: the ancestor walk is a chain of dependent reads
   __shared__ float s_delta[128];  // delta_i = <dO_i, O_i> of the pair's query rows, formed while they are staged
-  bool by_run = false;
-  if (kLocalPlan) {
-    by_run = build_split<kB8Threads, kB8Par>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
-    if (blockIdx.x == 0) publish_split(PB, s_pb, B, by_run, kB8Threads);
-  }
+  __shared__ int4 s_first;
+  SplitLens lens;
+  if constexpr (kLocalPlan) lens = load_split_lens(seq_lens, B);
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
-
-  const int U = pbv(B);  // units: runs, or tiles
-  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
-  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
-  if (u >= u_end) return;
 
   const int G = Hq / Hkv, R = G * Nq;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -429,19 +424,22 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
   const int mask = (1 << page_shift) - 1;
   char* xts = xt + grp * 4 * kBsXtBytes;
 
-  int b = 0;
-  {
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (pbv(mid) <= u) lo = mid; else hi = mid - 1;
-    }
-    b = lo;
+  Share sh;
+  if constexpr (kLocalPlan) {
+    // every workgroup builds the split itself; the first one also publishes it for the merge kernel
+    sh = build_split<kB8Threads, kB8Par, kBmWorkgroups>(lens, B, Hkv, s_pb, s_wsum, &s_first);
+    if (blockIdx.x == 0) publish_split(PB, s_pb, B, sh.by_run, kB8Threads);
+  } else {
+    sh = load_split<kBmWorkgroups>(PB, seq_lens, B);
   }
+  const bool by_run = sh.by_run;
+  int u = sh.u, b = sh.b, L_next = sh.L;
+  const int u_end = sh.u_end;
+  if (u >= u_end) return;
 
   while (u < u_end) {
-    while (pbv(b + 1) <= u) ++b;
-    const int L = seq_lens[b];
+    while (pbv(b + 1) <= u) ++b;  // read again: two more scalars kept over a segment would be spilled
+    const int L = L_next;
     const int n_b = (L + kAtTile - 1) / kAtTile;
     const int rel = u - pbv(b);
     const int per_pair = by_run ? (n_b + kB8Par - 1) / kB8Par : n_b;
@@ -451,6 +449,11 @@ __global__ __launch_bounds__(kB8Threads, 1) void attn_bwd_mfma_shared_kernel(
     const int t1 = min(n_b, t0 + (by_run ? kB8Par : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;
     u += by_run ? 1 : t1 - t0;
+    if (u < u_end) {  // the next segment's length, under this one
+      int bn = b;
+      while (pbv(bn + 1) <= u) ++bn;
+      L_next = seq_lens[bn];
+    }
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
@@ -633,7 +636,7 @@ bool attn_bwd_mfma_supported(const AttnBwdLaunch& a) {
   return a.bf16 && a.D == kAtD && a.page >= 16 && (a.page & (a.page - 1)) == 0 && a.Hq / a.Hkv * a.Nq <= 128;
 }
 
-int attn_bwd_mfma_workgroups() { return 256; }
+int attn_bwd_mfma_workgroups() { return kBmWorkgroups; }
 
 // row tiles of the pair: 1 or 2 (wavefront-private tiles), 4 (shared tiles)
 static int bwd_row_tiles(const AttnBwdLaunch& a) {

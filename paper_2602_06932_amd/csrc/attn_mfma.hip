@@ -87,19 +87,11 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
   __shared__ int s_pb[kLocalPlan ? kLocalPlanMax + 1 : 1];
   __shared__ int2 s_wsum[4];
   __shared__ int s_par[kMaxNq];  // the request's tree: the ancestor walk is a chain of dependent reads
-  bool by_run = false;
-  if (kLocalPlan) {
-    // every workgroup builds the split itself; workgroup (0,0) also publishes it for the merge kernel
-    by_run = build_split<kAtThreads, kNarrowPar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
-    if (blockIdx.x == 0 && blockIdx.y == 0) publish_split(PB, s_pb, B, by_run, kAtThreads);
-  }
+  __shared__ int4 s_first;
+  SplitLens lens;
+  if constexpr (kLocalPlan) lens = load_split_lens(seq_lens, B);
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
-
   const int rt = blockIdx.y, row_tiles = gridDim.y;
-  const int U = pbv(B);  // units: runs, or tiles
-  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
-  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
-  if (u >= u_end) return;
 
   const int G = Hq / Hkv;
   const int R = G * Nq;
@@ -120,23 +112,28 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
   const int qs_node = qs_ok ? qs_m / G : 0;
   const int qs_g = qs_ok ? qs_m % G : 0;
 
-  // request holding unit u: largest b with PB[b] <= u
-  int b = 0;
-  {
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (pbv(mid) <= u) lo = mid; else hi = mid - 1;
-    }
-    b = lo;
+  Share sh;
+  if constexpr (kLocalPlan) {
+    // every workgroup builds the split itself; the first one also publishes it for the merge kernel
+    sh = build_split<kAtThreads, kNarrowPar, kAttnWorkgroups>(lens, B, Hkv, s_pb, s_wsum, &s_first);
+    if (blockIdx.x == 0 && blockIdx.y == 0) publish_split(PB, s_pb, B, sh.by_run, kAtThreads);
+  } else {
+    sh = load_split<kAttnWorkgroups>(PB, seq_lens, B);
   }
+  const bool by_run = sh.by_run;
+  int u = sh.u, b = sh.b, from = sh.from, to = sh.to, L_next = sh.L;
+  const int u_end = sh.u_end;
+  if (u >= u_end) return;
 
   // ---- one segment per (request, KV head) pair this workgroup's unit range touches --------------------
   while (u < u_end) {
-    while (pbv(b + 1) <= u) ++b;
-    const int L = seq_lens[b];
+    while (to <= u) {
+      from = to;
+      to = pbv(++b + 1);
+    }
+    const int L = L_next;
     const int n_b = (L + kAtTile - 1) / kAtTile;
-    const int rel = u - pbv(b);
+    const int rel = u - from;
     const int per_pair = by_run ? (n_b + kNarrowPar - 1) / kNarrowPar : n_b;
     const int hk = __builtin_amdgcn_readfirstlane(rel / per_pair);
     const int at = rel - hk * per_pair;
@@ -144,6 +141,11 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
     const int t1 = min(n_b, t0 + (by_run ? kNarrowPar : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;  // segments are a monotone path in (workgroup, pair): unique
     u += by_run ? 1 : t1 - t0;
+    if (u < u_end) {  // the next segment's length, under this one
+      int bn = b;
+      while (pbv(bn + 1) <= u) ++bn;
+      L_next = seq_lens[bn];
+    }
 
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
@@ -325,6 +327,7 @@ __global__ __launch_bounds__(kAtThreads, 2) void attn_mfma_kernel(
 // one workgroup barrier per step; one workgroup per compute unit.  Work is dealt out exactly as in the
 // narrow kernel; a segment ends with a merge of the two parities through LDS.
 constexpr int kWideThreads = 512;
+constexpr int kWideWorkgroups = 256;  // one per compute unit
 constexpr int kWideStages = 3;
 constexpr int kWideStageBytes = 2 * 2 * kAtTileBytes;                // two tiles, K and V
 constexpr int kWideQBytes = 4 * 32 * kAtRowBytes;                    // four query tiles
@@ -353,17 +356,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
   __shared__ int2 s_wsum[kWideThreads / kWave];
   __shared__ int s_par[kMaxNq];
   __shared__ float s_ml[2][4][2][32];  // (m, l) of the rows of each parity group's query tiles
-  bool by_run = false;
-  if (kLocalPlan) {
-    by_run = build_split<kWideThreads, kWidePar>(seq_lens, B, Hkv, gridDim.x, s_pb, s_wsum);
-    if (blockIdx.x == 0 && blockIdx.y == 0) publish_split(PB, s_pb, B, by_run, kWideThreads);
-  }
+  __shared__ int4 s_first;
+  SplitLens lens;
+  if constexpr (kLocalPlan) lens = load_split_lens(seq_lens, B);
   auto pbv = [&](int i) -> int { return kLocalPlan ? s_pb[i] : PB[i]; };
-
-  const int U = pbv(B);  // units: runs, or tiles
-  int u = by_run ? (int)blockIdx.x : unit_begin(U, gridDim.x, blockIdx.x);
-  const int u_end = by_run ? min(U, u + 1) : unit_begin(U, gridDim.x, blockIdx.x + 1);
-  if (u >= u_end) return;
 
   const int G = Hq / Hkv;
   const int R = G * Nq;
@@ -380,21 +376,27 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
   const int qs_row = (tid & 255) >> 3;  // staging: 8 threads per query row, 32 B each
   const int qs_half = tid >> 8;         // threads 0..255 stage tiles 0 and 1, threads 256..511 tiles 2 and 3
 
-  int b = 0;
-  {
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (pbv(mid) <= u) lo = mid; else hi = mid - 1;
-    }
-    b = lo;
+  Share sh;
+  if constexpr (kLocalPlan) {
+    // every workgroup builds the split itself; the first one also publishes it for the merge kernel
+    sh = build_split<kWideThreads, kWidePar, kWideWorkgroups>(lens, B, Hkv, s_pb, s_wsum, &s_first);
+    if (blockIdx.x == 0 && blockIdx.y == 0) publish_split(PB, s_pb, B, sh.by_run, kWideThreads);
+  } else {
+    sh = load_split<kWideWorkgroups>(PB, seq_lens, B);
   }
+  const bool by_run = sh.by_run;
+  int u = sh.u, b = sh.b, from = sh.from, to = sh.to, L_next = sh.L;
+  const int u_end = sh.u_end;
+  if (u >= u_end) return;
 
   while (u < u_end) {
-    while (pbv(b + 1) <= u) ++b;
-    const int L = seq_lens[b];
+    while (to <= u) {
+      from = to;
+      to = pbv(++b + 1);
+    }
+    const int L = L_next;
     const int n_b = (L + kAtTile - 1) / kAtTile;
-    const int rel = u - pbv(b);
+    const int rel = u - from;
     const int per_pair = by_run ? (n_b + kWidePar - 1) / kWidePar : n_b;
     const int hk = __builtin_amdgcn_readfirstlane(rel / per_pair);
     const int at = rel - hk * per_pair;
@@ -402,6 +404,11 @@ __global__ __launch_bounds__(kWideThreads, 1) void attn_mfma_wide_kernel(
     const int t1 = min(n_b, t0 + (by_run ? kWidePar : u_end - u));
     const int slot = blockIdx.x + b * Hkv + hk;
     u += by_run ? 1 : t1 - t0;
+    if (u < u_end) {  // the next segment's length, under this one
+      int bn = b;
+      while (pbv(bn + 1) <= u) ++bn;
+      L_next = seq_lens[bn];
+    }
     const int start = t0 * kAtTile;
     const int prefix = L - Nq;
     const int ntile = t1 - t0;
@@ -678,8 +685,6 @@ static void launch_combine(const AttnLaunch& a, hipStream_t st, int wgs, int row
 bool attn_mfma_supported(const AttnLaunch& a) {
   return a.bf16 && a.D == kAtD && a.page >= 16 && (a.page & (a.page - 1)) == 0;
 }
-
-constexpr int kWideWorkgroups = 256;  // one per compute unit
 
 hipError_t launch_attn_mfma(const AttnLaunch& a, hipStream_t st) {
   const int R = a.Hq / a.Hkv * a.Nq;

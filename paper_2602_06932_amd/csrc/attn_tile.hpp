@@ -315,23 +315,42 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
+// A workgroup's share of a sweep: units u .. u_end - 1 (runs if by_run, else tiles), and the request b that holds the first one:
+// L tokens long, units from .. to - 1 of the sweep.
+struct Share { bool by_run; int u, u_end, b, L, from, to; };
+
+// The lengths that a thread of build_split scans: its four requests'.  Asked for before anything else; what does not depend on
+// them goes in between.
+struct SplitLens { int n[4]; };
+__device__ __forceinline__ SplitLens load_split_lens(const int32_t* __restrict__ seq_lens, int B) {
+  const int t4 = threadIdx.x * 4;
+  SplitLens r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r.n[i] = t4 + i < B ? seq_lens[t4 + i] : 0;
+  return r;
+}
+
 // The split of a sweep over few tokens, built by the whole workgroup (kThreads threads, B <= 1024).  If the pairs'
 // tiles, cut into runs of kPar (one for each wavefront group that works at a time; a pair's last run may be shorter), are
-// no more runs than there are workgroups, a workgroup takes one run: s_pb[0 .. B] is the prefix of runs per request and
-// the function returns true.  Otherwise s_pb is the prefix of tiles, which are dealt out evenly (unit_begin).
+// no more runs than there are workgroups (kWgs), a workgroup takes one run: s_pb[0 .. B] is the prefix of runs per request.
+// Otherwise s_pb is the prefix of tiles, which are dealt out evenly (unit_begin).
 // Runs of one pair each: a run that crosses from pair to pair pays a segment's fixed cost (query rows, first tiles, merge of the
 // wavefronts: 3 to 4 us) for each in turn.  Shorter runs than kPar would leave wavefronts idle without ending any sooner, and
 // every run adds a partial per query row to the merge.  32 query heads over 8 KV heads, five rows, us for sweep and merge with
 // [tiles dealt out evenly to all workgroups; to as many as get kPar tiles each; one run each]: 1 request of 16 tokens 10.8, 21.8,
 // 10.4; 8 of 64 tokens 11.8, 15.5, 11.4; 7 of 20 to 400 tokens 17.2, 22.8, 12.1; 4 of 1000 tokens 19.5, 14.7, 14.4.
-template <int kThreads, int kPar>
-__device__ __forceinline__ bool build_split(const int32_t* __restrict__ seq_lens, int B, int Hkv, int workgroups, int* s_pb,
-                                            int2* s_wsum) {
+// The thread whose request holds the workgroup's first unit says so: no search of the prefix, and no second trip for the length.
+// A sweep's start is a chain of short trips (lengths, scan, first segment, query rows and page ids, tiles) in which no tile moves; with
+// that, the query rows' divisions ahead of the scan and a later segment's length fetched under the one before it, us for the call:
+// 16 trees of 16 over 1024 to 2048 tokens 67.8 -> 66.2, 32 requests of five rows over 2048 to 4096 in fp8 40.7 -> 40.1, 64 of 100 to
+// 600 tokens in bf16 32.0 -> 31.3, 8 of 64 to 128 10.6 -> 10.4; one request of 900 tokens 11.9 -> 12.0, the backward within noise.
+template <int kThreads, int kPar, int kWgs>
+__device__ __forceinline__ Share build_split(const SplitLens& len, int B, int Hkv, int* s_pb, int2* s_wsum, int4* s_first) {
   const int t4 = threadIdx.x * 4, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int tiles[4], runs[4], nt = 0, nr = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int n = t4 + i < B ? (seq_lens[t4 + i] + kAtTile - 1) / kAtTile : 0;
+    const int n = (len.n[i] + kAtTile - 1) / kAtTile;
     tiles[i] = n * Hkv;
     runs[i] = (n + kPar - 1) / kPar * Hkv;
     nt += tiles[i];
@@ -340,24 +359,58 @@ __device__ __forceinline__ bool build_split(const int32_t* __restrict__ seq_lens
   const int it = wave_incl_scan(nt), ir = wave_incl_scan(nr);
   if (lane == 63) s_wsum[wave] = make_int2(it, ir);
   __syncthreads();
-  int at_tile = it - nt, at_run = ir - nr, all_runs = 0;
+  int at_tile = it - nt, at_run = ir - nr, all_tiles = 0, all_runs = 0;
 #pragma unroll
   for (int w = 0; w < kThreads / kWave; ++w) {
     const int2 x = s_wsum[w];
+    all_tiles += x.x;
     all_runs += x.y;
     at_tile += w < wave ? x.x : 0;
     at_run += w < wave ? x.y : 0;
   }
-  const bool by_run = all_runs <= workgroups;
-  int at = by_run ? at_run : at_tile;
+  Share r;
+  r.by_run = all_runs <= kWgs;
+  r.u = r.by_run ? (int)blockIdx.x : unit_begin(all_tiles, kWgs, blockIdx.x);
+  r.u_end = r.by_run ? min(all_runs, r.u + 1) : unit_begin(all_tiles, kWgs, blockIdx.x + 1);
+  int at = r.by_run ? at_run : at_tile;
   if (threadIdx.x == 0) s_pb[0] = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    at += by_run ? runs[i] : tiles[i];
+    const int from = at;
+    at += r.by_run ? runs[i] : tiles[i];
     if (t4 + i < B) s_pb[t4 + i + 1] = at;
+    if (r.u >= from && r.u < at) *s_first = make_int4(t4 + i, len.n[i], from, at);
   }
   __syncthreads();
-  return by_run;
+  r.b = r.L = r.from = r.to = 0;
+  if (r.u < r.u_end) {
+    const int4 f = *s_first;
+    r.b = f.x;
+    r.L = f.y;
+    r.from = f.z;
+    r.to = f.w;
+  }
+  return r;
+}
+
+// The same of the prefix of tiles that the planning kernel has left in memory.
+template <int kWgs>
+__device__ __forceinline__ Share load_split(const int32_t* __restrict__ PB, const int32_t* __restrict__ seq_lens, int B) {
+  Share r;
+  const int U = PB[B];
+  r.by_run = false;
+  r.u = unit_begin(U, kWgs, blockIdx.x);
+  r.u_end = unit_begin(U, kWgs, blockIdx.x + 1);
+  int lo = 0, hi = B - 1;  // largest b with PB[b] <= u
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (PB[mid] <= r.u) lo = mid; else hi = mid - 1;
+  }
+  r.b = lo;
+  r.L = seq_lens[lo];
+  r.from = PB[lo];
+  r.to = PB[lo + 1];
+  return r;
 }
 
 // The split for the merge kernel: the prefix of tiles as it is, the prefix of runs as complements (negative numbers).
