@@ -94,6 +94,7 @@ template <int P> struct BgParity { static constexpr int value = P; };
 // One workgroup's tile: vocabulary tile vt, token rows m0 .. m0 + 32 kT.  kOne: one workgroup column holds all token rows.
 template <bool kFp8, int kT, bool kOne>
 __device__ __forceinline__ void bg_tile(const BgArgs& A, char* lds, int vt, int m0) {
+  static_assert(kT >= 4, "a half of two tiles has room for the reads of W");
   constexpr int kTa = (kT + 1) / 2, kTb = kT / 2;  // token tiles of the halves a and b of a stage
   const char* __restrict__ hidden = A.hidden;
   const char* __restrict__ w = A.w;
@@ -239,13 +240,11 @@ __device__ __forceinline__ void bg_tile(const BgArgs& A, char* lds, int vt, int 
       if (u == 0) {
         BG_OPEN(10);  // half b of stage ks is there; its half a and its W have been read
         issue_h(ks + 2, par, 0);
-        if (kTa == 1) issue_w(ks + 3, s0, 0);
       }
-      if (u == 1 && u < kTa) issue_w(ks + 3, s0, 0);
+      if (u == 1) issue_w(ks + 3, s0, 0);
       if (u == kTa) {
         BG_OPEN(10);  // W and half a of stage ks + 1 are there; half b of stage ks has been read
         issue_h(ks + 2, par, 1);
-        if (kTb == 1) issue_w(ks + 3, s0, 1);
       }
       if (u == kTa + 1) issue_w(ks + 3, s0, 1);
       if (u < kTb) {
@@ -262,7 +261,7 @@ __device__ __forceinline__ void bg_tile(const BgArgs& A, char* lds, int vt, int 
       }
 #pragma unroll
       for (int a = 0; a < 4; ++a)
-        if (u == (kTb == 1 ? kTa : kTa + a / 2)) {
+        if (u == kTa + a / 2) {
           read_w(s1, a, wn[a]);
           reads += 2;
         }

@@ -1,12 +1,12 @@
 // Calibration probe: what a dense bf16 contraction can reach on this device, stripped of everything specific to
-// the LM head.  One workgroup per compute unit slot runs the many-row LM-head kernel's inner structure - eight
+// the LM head.  One workgroup per compute unit slot runs an LM-head tile in 32-row products - eight
 // wavefronts, 2 x 4 accumulator tiles of v_mfma_f32_32x32x16_bf16 each, four steps per stage, 64 KB of operands per
 // stage - with its parts switched on one at a time:
 //   mode 0  matrix cores only, operands fixed in registers
 //   mode 1  + the operand reads from LDS (six 16-byte reads per lane and step, the LM head's swizzled layout)
 //   mode 2  + the LDS-direct loads that refill the stage (row slivers of 128 bytes at an 8 KB pitch, L2
-//             resident: no HBM traffic), issued by the multiplying wavefronts as in that kernel: through a buffer
-//             descriptor, two after every step
+//             resident: no HBM traffic), issued by the multiplying wavefronts through a buffer descriptor, two
+//             after every step
 //   mode 3  the loads alone
 //   mode 4  the W sweep alone: every workgroup streams its own 256 rows x 8 KB of `operands` once from HBM through a
 //           three-stage LDS ring in the LM head's tile shape (row slivers of 128 bytes per stage), four loading
@@ -14,7 +14,8 @@
 // Nothing waits for data and the results are discarded: the probe measures rates, and how they depend on the VALUES
 // multiplied (the caller fills `operands`: random LM-head-like values, or zeros).  The time of a matrix-core
 // kernel on this part depends on them - the signature of a power limit - and the numbers this gives are the
-// ceiling the LM-head kernels are priced against beside the published peak.
+// ceiling of that form, which the tile of up to 160 rows uses; the many-row kernel multiplies in the 16x16x32 form, whose rate from
+// registers on the same values is half as high again (2.06 against 1.35-1.39 PFLOP/s).
 #include "launch.hpp"
 #include "lmhead_tile.hpp"
 

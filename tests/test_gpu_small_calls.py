@@ -11,11 +11,11 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("temps", [False, True])
-@pytest.mark.parametrize("batch,num_q,vocab,hidden,lens", [(1, 1, 1, 8, (1, 9)), (4, 5, 1024, 256, (256, 256)), (3, 7, 1023, 64, (7, 300)), (3, 4, 2048, 64, (9, 99)), (3, 4, 2049, 64, (9, 99)),
-                                                           (8, 2, 2003, 72, (64, 512)), (2, 5, 8192, 96, (30, 60)),
+@pytest.mark.parametrize("batch,num_q,vocab,hidden,lens,dim", [(1, 1, 1, 8, (1, 9), 64), (4, 5, 1024, 256, (256, 256), 64), (3, 7, 1023, 64, (7, 300), 64), (3, 4, 2048, 64, (9, 99), 64), (3, 4, 2049, 64, (9, 99), 64),
+                                                           (8, 2, 2003, 72, (64, 512), 64), (2, 5, 8192, 96, (30, 60), 64),
                                                            # past one slice; past the small LM-head tiles; past one split
-                                                           (2, 5, 8193, 32, (30, 60)), (40, 8, 2048, 64, (20, 40)), (2, 4, 500, 64, (500, 700))])
-def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, lens, temps):
+                                                           (2, 5, 8193, 32, (30, 60), 64), (40, 8, 2048, 64, (20, 40), 64), (2, 4, 500, 64, (500, 700), 64), (4, 5, 2001, 64, (7, 300), 128), (2, 4, 500, 64, (500, 700), 128)])
+def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, lens, dim, temps):
     from paper_2602_06932_amd.device import DeviceVerify
     from parity_util import check_accept, check_attention, check_logits
     kw = {}
@@ -23,7 +23,7 @@ def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, le
         kw = dict(draft="noisy_target", temperatures=np.array([0.0, 0.6, 1.0, 0.8] * batch, np.float32)[:batch])
     seq = np.linspace(lens[0], lens[1], batch).astype(np.int32)
     w = gen.make_workload(name="small", seed=40 + vocab, seq_lens=np.maximum(seq, num_q).astype(np.int32), recipe="", batch=batch, num_q=num_q,
-                          num_q_heads=8, num_kv_heads=2, head_dim=64, page_size=256, hidden_size=hidden, vocab=vocab,
+                          num_q_heads=8, num_kv_heads=2, head_dim=dim, page_size=256, hidden_size=hidden, vocab=vocab,
                           temperature=1.0, dtype=gen.F32, **{"draft": "independent", **kw})
     one, parts = DeviceVerify(w), DeviceVerify(w)
     one.workspace.fill_(255)  # (statistics that are read before they are written would be NaN)

@@ -38,6 +38,22 @@ def test_attention_of_few_tiles(gpu_lib, batch, context, nodes, hkv, kv8):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("batch,hq", [(1024, 4), (1030, 4), (1030, 16)])
+def test_attention_of_many_short_requests(gpu_lib, batch, hq, kv8):
+    """The last size whose split the workgroups build themselves, and past it, where it is read from the planning kernel's prefix."""
+    from paper_2602_06932_amd.device import DeviceVerify
+    from parity_util import check_attention
+    w = gen.llama_chain(170, batch=batch, num_q=5, num_q_heads=hq, num_kv_heads=2, len_lo=5, len_hi=70, vocab=64, hidden_size=64,
+                        kv_fp8=kv8)
+    dv = DeviceVerify(w)
+    dv.attn_out.fill_(float("nan"))
+    dv.attn()
+    torch.cuda.synchronize()
+    check_attention(dv.attn_out_host(), oracle.attn_workload(w), w.dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv8", [False, True])
 @pytest.mark.parametrize("num_q,tiles,batch", [(8, 1, 1), (8, 4, 1), (8, 5, 3), (8, 87, 1), (8, 10, 12), (32, 1, 1), (32, 4, 1), (32, 5, 2),
                                                (32, 86, 1), (32, 5, 12)])
 def test_infinities_at_nodes_a_row_does_not_see(gpu_lib, num_q, tiles, batch, kv8):
