@@ -342,7 +342,7 @@ __device__ __forceinline__ SplitLens load_split_lens(const int32_t* __restrict__
 // The thread whose request holds the workgroup's first unit says so: no search of the prefix, and no second trip for the length.
 // A sweep's start is a chain of short trips (lengths, scan, first segment, query rows and page ids, tiles) in which no tile moves; with
 // that, the query rows' divisions ahead of the scan and a later segment's length fetched under the one before it, us for the call:
-// 16 trees of 32 over 4096 tokens 67.8 -> 66.2, 32 requests of five rows over 2048 to 4096 in fp8 40.7 -> 40.1, 64 of 100 to
+// 16 trees of 32 over 4096 tokens 67.8 -> 66.2, 32 requests of five rows over 1024 to 4096 in fp8 40.7 -> 40.1, 64 of 100 to
 // 600 tokens in bf16 32.0 -> 31.3, 8 of 64 to 128 10.6 -> 10.4; one request of 2777 tokens 11.9 -> 12.0, the backward within noise.
 template <int kThreads, int kPar, int kWgs>
 __device__ __forceinline__ Share build_split(const SplitLens& len, int B, int Hkv, int* s_pb, int2* s_wsum, int4* s_first) {
