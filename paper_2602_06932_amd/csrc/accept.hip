@@ -224,17 +224,20 @@ __device__ __forceinline__ void form_row_stats(const AcceptParams& P, size_t row
         for (int e = 0; e < 4; ++e) x[4 * c + e] = v + e < V ? lr[v + e] : -INFINITY;
       }
     }
-    float mx = x[0];
+    float mx = -INFINITY;  // (a NaN is no maximum)
 #pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, x[i]);
     mx = wave_max(mx);
+    // what lies past the vocabulary is told by its index: a NaN has to reach the sum, and with it the row's logsumexp
     int at = 0x7fffffff;
-#pragma unroll
-    for (int i = 15; i >= 0; --i) at = x[i] == mx ? t * kRowStatTile + (i >> 2) * 256 + lane * 4 + (i & 3) : at;
-    at = wave_min(at);
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sum += x[i] > -INFINITY ? __expf((x[i] - mx) * inv_t) : 0.f;
+    for (int i = 15; i >= 0; --i) {
+      const int v = t * kRowStatTile + (i >> 2) * 256 + lane * 4 + (i & 3);
+      at = x[i] > -INFINITY && x[i] == mx ? v : at;
+      sum += v < V ? __expf((x[i] - mx) * inv_t) : 0.f;
+    }
+    at = wave_min(at);
     sum = wave_sum(sum);
     if (lane == t) {
       tile_m = mx;
@@ -252,8 +255,7 @@ __device__ __forceinline__ void form_row_stats(const AcceptParams& P, size_t row
   const double s = wave_sum(tile_m > -INFINITY ? (double)tile_s * (double)__builtin_amdgcn_exp2f((float)(((double)tile_m - md) * c)) : 0.0);
   *out_max = m;
   *out_lse = (double)m / T + log(s);
-  const int arg = wave_min(tile_m == m ? tile_arg : 0x7fffffff);
-  *out_arg = arg < V ? arg : 0;
+  *out_arg = wave_min(tile_m == m ? tile_arg : 0x7fffffff);
 }
 
 // ============================================================================================

@@ -51,3 +51,40 @@ def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, le
     c = one.results_host()
     for n in a:
         assert np.array_equal(a[n], c[n]) or np.abs(a[n] - c[n]).max() <= 1e-6, n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("temps", [False, True])
+@pytest.mark.parametrize("kind", ["nan_entry", "nan_row", "inf_entry"])
+@pytest.mark.parametrize("vocab", [1, 1000, 1024, 2001, 2048])
+def test_logits_that_are_not_finite(gpu_lib, vocab, kind, temps):
+    """A NaN logit reaches the row's logsumexp, and with it the accept tests, wherever the statistics are formed."""
+    from paper_2602_06932_amd.device import DeviceVerify
+    kw = dict(temperatures=np.array([0.0, 0.6, 1.0, 0.8], np.float32)) if temps else {}
+    w = gen.make_workload(name="small", seed=60 + vocab, seq_lens=np.full(4, 20, np.int32), recipe="", batch=4, num_q=5, num_q_heads=4,
+                          num_kv_heads=2, head_dim=64, page_size=16, hidden_size=64, vocab=vocab, temperature=1.0, dtype=gen.F32,
+                          draft="noisy_target", **kw)
+    dv = DeviceVerify(w)
+    if kind == "nan_row":  # every logit of a request's third row
+        dv.hidden.view(4, 5, 64)[1, 2, 7] = float("nan")
+    else:                  # one logit of every row: the vocabulary's last
+        dv.lm_head.view(vocab, 64)[-1, 3] = float(kind[:3])
+    dv.accept()
+    torch.cuda.synchronize()
+    one = {n: x.copy() for n, x in dv.results_host().items()}
+    dv.workspace.fill_(255)
+    for t in (dv.accept_len, dv.next_token, dv.accept_mask):
+        t.fill_(9)
+    dv.lmhead(), dv.accept_logits()
+    torch.cuda.synchronize()
+    two = dv.results_host()
+    for n in ("accept_len", "next_token", "accept_mask"):
+        assert np.array_equal(one[n], two[n]), n
+    for n in ("row_lse", "p_at_draft"):
+        assert np.array_equal(np.isnan(one[n]), np.isnan(two[n])), n
+        same = (one[n] == two[n]) | np.isnan(two[n])
+        assert (same | (np.abs(one[n] - two[n]) <= 2e-6 * np.maximum(1, np.abs(two[n])))).all(), n
+    if kind == "nan_entry" and vocab > 1:  # (a row of nothing else has no maximum: its logsumexp is -inf)
+        assert np.isnan(one["row_lse"]).all()
+        sampled = np.arange(4) > 0 if temps else np.full(4, True)
+        assert (one["accept_len"][sampled] == 0).all()
