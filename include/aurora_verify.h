@@ -214,7 +214,8 @@ int aurora_verify_lmhead(const aurora_accept_desc* desc,
  * Second stage of aurora_verify_accept on its own: the acceptance walk and the residual / bonus draw
  * (section 2.1's rule, as specified at aurora_verify_accept) on the logits and statistics that a
  * preceding aurora_verify_lmhead call with the same descriptor left in `workspace`.
- * aurora_verify_lmhead followed by this call enqueues exactly the kernels of aurora_verify_accept;
+ * aurora_verify_lmhead followed by this call does the work of aurora_verify_accept with bit-identical outputs (where the
+ * generic LM head runs, that call may merge kernels that the two stages keep apart);
  * the split exists so that a caller can put its own events (or other work) between the two stages.
  */
 int aurora_verify_accept_logits(const aurora_accept_desc* desc, const int32_t* draft_tokens,

@@ -198,8 +198,21 @@ __device__ __forceinline__ void merge_row_stats(const AcceptParams& P, size_t ro
   }
 }
 
+// The sum over a row of sixteen lanes, in every one of them, added over distances of 8, 4, 2 and 1 lanes (after each turn by that
+// distance the values repeat with it, so turning the row is exchanging).
+__device__ __forceinline__ float row16_sum(float x) {
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));
+  return x;
+}
+
 // The same from the logits themselves, where no kernel has formed the tile statistics (generic LM head, small vocabulary), which
-// are left behind as that kernel leaves them: per tile the maximum, its lowest index and the sum of exp((l - max) / T).
+// are left behind as row_tile_stats leaves them, bit for bit: per tile the maximum, its lowest index and the sum of
+// exp((l - max) / T) in that kernel's order.  Its thread t adds the entries t, t + 256, .. of a tile, its wavefronts add over
+// distances of 32, 16, .. 1 threads, and their four sums are added in turn.  Here element e of lane l's four vectors is thread
+// 4 l + e: a wavefront there is a row of sixteen lanes here, its distances of 32 to 4 are 8 to 1 lanes, the last two are elements.
 constexpr int kRowStatTiles = 2;
 __device__ __forceinline__ void form_row_stats(const AcceptParams& P, size_t row, double T, int lane, float* out_max,
                                                double* out_lse, int* out_arg) {
@@ -230,15 +243,31 @@ __device__ __forceinline__ void form_row_stats(const AcceptParams& P, size_t row
     mx = wave_max(mx);
     // what lies past the vocabulary is told by its index: a NaN has to reach the sum, and with it the row's logsumexp
     int at = 0x7fffffff;
-    float sum = 0.f;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int v = t * kRowStatTile + (i >> 2) * 256 + lane * 4 + (i & 3);
+      s[i & 3] += v < V ? __expf((x[i] - mx) * inv_t) : 0.f;
+    }
 #pragma unroll
     for (int i = 15; i >= 0; --i) {
       const int v = t * kRowStatTile + (i >> 2) * 256 + lane * 4 + (i & 3);
       at = x[i] > -INFINITY && x[i] == mx ? v : at;
-      sum += v < V ? __expf((x[i] - mx) * inv_t) : 0.f;
     }
-    at = wave_min(at);
-    sum = wave_sum(sum);
+    // the lowest index: of the first of the tile's quarters that holds one, the first lane's
+    unsigned long long hit = 0;
+#pragma unroll
+    for (int c = 3; c >= 0; --c) {
+      const unsigned long long here = __ballot(((at - t * kRowStatTile) >> 8) == c);
+      hit = here ? here : hit;
+    }
+    at = __builtin_amdgcn_readlane(at, hit ? __ffsll((long long)hit) - 1 : 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = row16_sum(s[e]);
+    const unsigned row_s = __float_as_uint((s[0] + s[2]) + (s[1] + s[3]));
+    float sum = __uint_as_float(__builtin_amdgcn_readlane(row_s, 0));
+#pragma unroll
+    for (int r = 1; r < 4; ++r) sum += __uint_as_float(__builtin_amdgcn_readlane(row_s, 16 * r));
     if (lane == t) {
       tile_m = mx;
       tile_s = sum;

@@ -324,8 +324,8 @@ def test_lmhead_many_token_rows(gpu_lib, batch, num_q, vocab, hidden):
 
 @pytest.mark.parametrize("tree", [False, True])
 def test_lmhead_then_accept_logits_equals_accept(gpu_lib, tree):
-    """The two stages of the acceptance half called one after the other enqueue the same kernels as the
-    single call: identical outputs, and parity with the oracle."""
+    """The two stages of the acceptance half called one after the other do the work of the single call: identical outputs, and
+    parity with the oracle."""
     from paper_2602_06932_amd.device import DeviceVerify
     w = gen.llama_chain(19, batch=7, len_lo=20, len_hi=60, vocab=3333, hidden_size=128) if not tree else \
         gen.llama_tree(19, batch=5, num_q=16, vocab=3333, hidden_size=128, context=64, num_q_heads=4, num_kv_heads=2)
@@ -344,6 +344,30 @@ def test_lmhead_then_accept_logits_equals_accept(gpu_lib, tree):
                         uniforms=w.uniforms, parents=w.parents, dtype=w.dtype, temperature=w.temperature,
                         want_cdf=True, want_logits=True)
     check_accept(two, ref, w)
+
+
+@pytest.mark.parametrize("dtype,hidden", [(gen.F32, 96), (gen.BF16, 72)])
+@pytest.mark.parametrize("batch,num_q,vocab", [(7, 5, 1000), (7, 5, 2048), (3, 9, 1024), (2, 17, 1025), (300, 2, 2003), (3, 4, 2049)])
+def test_lmhead_then_accept_logits_equals_accept_without_matrix_cores(gpu_lib, batch, num_q, vocab, dtype, hidden):
+    """The same where the generic LM head runs: the single call may form the rows' statistics in the acceptance sweep, in the
+    order in which the statistics kernel of the two stages does."""
+    from paper_2602_06932_amd.device import DeviceVerify
+    w = gen.make_workload(name="stages", seed=190, seq_lens=np.full(batch, 20, np.int32), batch=batch, num_q=num_q, num_q_heads=4,
+                          num_kv_heads=2, head_dim=64, page_size=16, hidden_size=hidden, vocab=vocab, temperature=0.8, dtype=dtype,
+                          draft="noisy_target", draft_noise=0.3)
+    dv = DeviceVerify(w)
+    dv.workspace.fill_(255)
+    dv.accept()
+    one = {k: v.copy() for k, v in dv.results_host().items()}
+    dv.workspace.fill_(255)
+    for t in (dv.accept_len, dv.next_token):
+        t.fill_(-7)
+    dv.accept_mask.fill_(9)
+    dv.lmhead()
+    dv.accept_logits()
+    two = dv.results_host()
+    for k in one:
+        assert np.array_equal(one[k], two[k]), k
 
 
 @pytest.mark.parametrize("vocab,draft_vocab", [(4000, 1000), (3001, 777)])

@@ -37,10 +37,8 @@ def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, le
     check_logits(one.logits_host(), ref_a.logits, w.dtype)
     check_accept(one.results_host(), ref_a, w)
     a, b = one.results_host(), parts.results_host()
-    for n in ("accept_len", "next_token", "accept_mask"):
+    for n in a:
         assert np.array_equal(a[n], b[n]), n
-    # the two orders of a tile's float32 sums differ by a few of its 2^-24
-    assert np.abs(a["row_lse"] - b["row_lse"]).max() <= 2e-6 * max(1.0, np.abs(b["row_lse"]).max())
     # the step leaves the statistics behind as the stages do: acceptance alone, on its part of the workspace
     attn_bytes = gpu_lib.aurora_verify_logits_ptr(one.attn_desc, one.accept_desc, one.workspace) - \
         gpu_lib.aurora_verify_logits_ptr(None, one.accept_desc, one.workspace)
@@ -50,7 +48,7 @@ def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, le
     torch.cuda.synchronize()
     c = one.results_host()
     for n in a:
-        assert np.array_equal(a[n], c[n]) or np.abs(a[n] - c[n]).max() <= 1e-6, n
+        assert np.array_equal(a[n], c[n]), n
 
 
 @pytest.mark.gpu
@@ -78,12 +76,8 @@ def test_logits_that_are_not_finite(gpu_lib, vocab, kind, temps):
     dv.lmhead(), dv.accept_logits()
     torch.cuda.synchronize()
     two = dv.results_host()
-    for n in ("accept_len", "next_token", "accept_mask"):
-        assert np.array_equal(one[n], two[n]), n
-    for n in ("row_lse", "p_at_draft"):
-        assert np.array_equal(np.isnan(one[n]), np.isnan(two[n])), n
-        same = (one[n] == two[n]) | np.isnan(two[n])
-        assert (same | (np.abs(one[n] - two[n]) <= 2e-6 * np.maximum(1, np.abs(two[n])))).all(), n
+    for n in one:
+        assert np.array_equal(one[n], two[n], equal_nan=True), n
     if kind == "nan_entry" and vocab > 1:  # (a row of nothing else has no maximum: its logsumexp is -inf)
         assert np.isnan(one["row_lse"]).all()
         sampled = np.arange(4) > 0 if temps else np.full(4, True)
