@@ -1092,9 +1092,15 @@ static int tree_slices_for(int B, int ngroups, bool wor, int cus) {
 // A request's only workgroup can form its rows' statistics from the logits (16 floats a lane and tile) and save a launch, while
 // the tiles are few: each is a chain of reductions.  2 requests x 5 rows, step, us, with the launch and without: 2003 logits
 // 44.8, 42.7, 4096 45.9, 47.1; 4 x 5 rows, 1024 26.9, 18.0 (with the shared launch in front, generic LM head), 8192 65.8, 73.7.
+// A wavefront forms the tiles of every eighth row one after the other, where the launch has all of them side by side - until
+// there are enough of them to fill the chip either way, and the launch only reads the logits once more.  LM head and acceptance, us, with the
+// launch and without, by tiles a wavefront: two (16 rows x 1024) 1 request 17.8, 15.8, three (24 x 1024) 1 request 19.5, 19.3,
+// 32 requests 27.8, 26.7; four (32 x 1024) 1 request 21.6, 22.7, (16 x 2048) 8 requests 19.1, 21.2, 64 requests 31.4, 30.8; eight
+// (32 x 2048) 64 requests 45.9, 49.0, 128 requests 63.4, 58.4; sixteen (64 x 2048) 1 request 29.5, 53.2, 128 requests 105, 100.
 bool accept_forms_stats(const AcceptLaunch& a) {
+  const int chain = a.plan.n_tiles * ((a.Nq + kSweepThreads / kWave - 1) / (kSweepThreads / kWave));
   return (a.temperature > 0.f || a.temps) && !a.parents && a.plan.slices == 1 && a.plan.stat_tile == kRowStatTile &&
-         a.plan.n_tiles <= kRowStatTiles;
+         a.plan.n_tiles <= kRowStatTiles && (chain <= 3 || a.B >= 128);
 }
 
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t st) {

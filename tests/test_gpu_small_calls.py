@@ -14,7 +14,11 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("batch,num_q,vocab,hidden,lens,dim", [(1, 1, 1, 8, (1, 9), 64), (4, 5, 1024, 256, (256, 256), 64), (3, 7, 1023, 64, (7, 300), 64), (3, 4, 2048, 64, (9, 99), 64), (3, 4, 2049, 64, (9, 99), 64),
                                                            (8, 2, 2003, 72, (64, 512), 64), (2, 5, 8192, 96, (30, 60), 64),
                                                            # past one slice; past the small LM-head tiles; past one split
-                                                           (2, 5, 8193, 32, (30, 60), 64), (40, 8, 2048, 64, (20, 40), 64), (2, 4, 500, 64, (500, 700), 64), (4, 5, 2001, 64, (7, 300), 128), (2, 4, 500, 64, (500, 700), 128)])
+                                                           (2, 5, 8193, 32, (30, 60), 64), (40, 8, 2048, 64, (20, 40), 64), (2, 4, 500, 64, (500, 700), 64), (4, 5, 2001, 64, (7, 300), 128), (2, 4, 500, 64, (500, 700), 128),
+                                                           # several rows a wavefront: formed in the sweep up to three tiles each, ..
+                                                           (2, 9, 1000, 32, (30, 60), 64), (3, 24, 1024, 32, (30, 60), 64), (130, 17, 1100, 32, (30, 60), 64),
+                                                           # .. or by the launch
+                                                           (2, 25, 1000, 32, (30, 60), 64), (3, 9, 1100, 32, (30, 60), 64), (127, 9, 1100, 32, (30, 60), 64)])
 def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, lens, dim, temps):
     from paper_2602_06932_amd.device import DeviceVerify
     from parity_util import check_accept, check_attention, check_logits
