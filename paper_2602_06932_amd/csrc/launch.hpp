@@ -55,13 +55,7 @@ bool lmhead_mfma_supported(const AcceptLaunch& a);
 int lmhead_mfma_stat_tile();
 hipError_t launch_lmhead_mfma(const AcceptLaunch& a, hipStream_t st);  // picks the small- or large-M kernel
 constexpr int kLmHalfPerTile = 8;     // groups of 32 vocabulary rows per 256-row statistics tile
-// Whether the tiled kernel takes the LM head of so many token rows, rather than passes of at most 160 rows of the W-streaming one.
-// 128256 x 4096, bf16 / fp8, us, W-streaming -> tiled: up to 128 rows W's stream bounds both (64 rows 178 / 99 -> 179 / 100, 96 rows
-// 186 / 107 -> 187 / 106); from five tiles of 32 rows on the tiled one is ahead (129 rows 207 / 119 -> 197 / 113, 160 rows 215 / 119 ->
-// 203 / 117, 192 rows 295 / 169 -> 212 / 120, 256 rows 325 / 188 -> 250 / 142, 352 rows 446 / 245 -> 375 / 217), except
-// where it needs a second workgroup column, which shares W's misses, and two passes of up to 160 rows do not (288 rows 354 / 197 ->
-// 351 / 212, 320 rows 360 / 204 -> 363 / 215).
-inline bool lm_many_rows(int64_t rows) { return rows > 256 ? rows > 320 : rows > 128; }
+constexpr int kLmTiledOnlyRows = 384;  // token rows from which the tiled kernel takes every vocabulary (lmhead_mfma.hip)
 bool lmhead_mfma_big_supported(const AcceptLaunch& a);
 hipError_t launch_lmhead_mfma_big(const AcceptLaunch& a, hipStream_t st);
 hipError_t launch_lmhead_generic(const AcceptLaunch& a, hipStream_t st);  // logits alone

@@ -390,9 +390,31 @@ static hipError_t launch_nt(const AcceptLaunch& a, hipStream_t st, int m_tiles) 
   return a.fp8 ? launch_nt_t<NT, true>(a, st, m_tiles) : launch_nt_t<NT, false>(a, st, m_tiles);
 }
 
+// Whether the tiled kernel takes the LM head, rather than passes of at most 160 token rows of the W-streaming one.  Both run one
+// workgroup of 256 vocabulary entries per compute unit.  us, bf16 / fp8, W-streaming -> tiled; 128256 x 4096 where no size is given:
+// up to 128 rows W's stream bounds both (64 rows 178 / 99 -> 179 / 100, 96 rows 186 / 107 -> 187 / 106); to 160 rows the tiled one
+// is ahead (129 rows 207 / 119 -> 197 / 113, 160 rows 215 / 119 -> 203 / 117; 2003 x 4096 74 / 43 -> 69 / 42), from 257 to 320 rows
+// it needs a second workgroup column as the other does and is behind (288 rows 354 / 197 -> 351 / 212, 320 rows 360 / 204 ->
+// 363 / 215).  In between it takes one column of workgroups less, each of which takes longer (161 to 256 rows 1.25 to 1.45 times, 321 to
+// 383 rows 1.1 to 1.4), so it is ahead exactly where that makes the launch fewer rounds of the chip: 256 rows, 8 vocabulary tiles
+// (2003 x 4096) 63 / 36 -> 92 / 57, 126 tiles (32003 x 4096) 81 / 50 -> 108 / 66, 129 tiles (33024 x 4096) 127 / 72 -> 91 / 52,
+// 257 tiles (65792 x 4096, three rounds or two) 196 / 112 -> 193 / 114, 501 tiles 325 / 188 -> 250 / 142; 352 rows, 64 tiles 61 / 34 ->
+// 66 / 38, 126 tiles 140 / 84 -> 97 / 62, 129 tiles (two rounds each) 126 / 70 -> 147 / 82, 171 tiles 188 / 103 -> 150 / 86, 385 tiles
+// (98560 x 2048, five or four) 188 / 112 -> 177 / 114 - in 8 bits one round in five is not enough.
+static bool tiled_is_ahead(int M, int v_tiles, bool fp8, int cus) {
+  const int passes = (M + 159) / 160, cols = (M + 255) / 256;
+  if (passes == cols) return M > 128 && M <= 160;
+  const int streaming = (v_tiles * passes + cus - 1) / cus, tiled = (v_tiles * cols + cus - 1) / cus;
+  return fp8 ? 5 * tiled < 4 * streaming : tiled < streaming;
+}
+
 hipError_t launch_lmhead_mfma(const AcceptLaunch& a, hipStream_t st) {
   const int M = (int)a.plan.rows;
-  if (lm_many_rows(M) && lmhead_mfma_big_supported(a)) return launch_lmhead_mfma_big(a, st);
+  if (lmhead_mfma_big_supported(a)) {
+    int cus = 0;
+    if (hipError_t e = device_cu_count(&cus); e != hipSuccess) return e;
+    if (M >= kLmTiledOnlyRows || tiled_is_ahead(M, a.plan.n_tiles, a.fp8, cus)) return launch_lmhead_mfma_big(a, st);
+  }
   // token rows per workgroup: the fewest 160-row passes over W, each as narrow as the rows allow
   const int passes = (M + 159) / 160;
   const int per = (M + passes - 1) / passes;

@@ -138,10 +138,10 @@ __device__ __forceinline__ void bg_tile(const BgArgs& A, char* lds, int vt, int 
   // One column: its workgroups start their walk over the hidden dimension at different offsets and wrap around (rows are a
   // multiple of the memory-channel interleave apart: in lockstep all would ask the same channels; 128 rows 263 -> 205 us), and W, read
   // once, does not displace the token rows in L2.  Several columns walk in step: they share W's lines, and the columns of all
-  // vocab tiles of an XCD their token rows (1280 rows staggered 2 % slower, 512 rows 1 %).  Up to 383 rows, where either way is
-  // within 3 % of the other (bf16 in step ahead, fp8 staggered), the walk is staggered too: the sums keep the order that the
-  // W-streaming kernel gives them.
-  const int k0 = kOne || M < 384 ? (int)((vt * 13u) % (unsigned)nk) : 0;
+  // vocab tiles of an XCD their token rows (1280 rows staggered 2 % slower, 512 rows 1 %).  Below the rows where this kernel takes
+  // every vocabulary, where either way is within 3 % of the other (bf16 in step ahead, fp8 staggered), the walk is staggered too:
+  // the W-streaming kernel takes some vocabularies there, and a row's sums keep its order in both.
+  const int k0 = kOne || M < kLmTiledOnlyRows ? (int)((vt * 13u) % (unsigned)nk) : 0;
   auto k_off = [&](int ks) { return ks < nk ? (unsigned)((ks + k0 >= nk ? ks + k0 - nk : ks + k0) * kBgRowBytes) : 0u; };
   auto issue_w = [&](int ks, unsigned slot, int hf) {
     const i32x4_t d = {w_rsrc[0], w_rsrc[1], ks < nk ? w_rsrc[2] : 0, w_rsrc[3]};  // past the end: nothing is read
@@ -367,8 +367,8 @@ __global__ __launch_bounds__(kBgThreads, 1) void lmhead_mfma_big_kernel(BgArgs A
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  The m_tiles token tiles
   // of one vocab tile get ids 8 apart: same XCD, launched together - the W tile comes from HBM once and
-  // from L2 for the others.  Every workgroup walks the hidden dimension in the same order: the
-  // workgroups resident on one XCD then want the same slices of the token tiles at about the same time
+  // from L2 for the others.  Where they walk the hidden dimension in step (bg_tile), the
+  // workgroups resident on one XCD want the same slices of the token tiles at about the same time
   // and its L2 serves all but the first.
   const int wg = blockIdx.x;
   const int vt = (wg / (8 * m_tiles)) * 8 + (wg & 7);
@@ -421,7 +421,7 @@ template <bool kFp8>
 static hipError_t launch_big_dt(const AcceptLaunch& a, hipStream_t st) {
   int m_tiles, nta, ntb, n_a;
   lmhead_mfma_big_geometry((int)a.plan.rows, &m_tiles, &nta, &ntb, &n_a);
-  // (lm_many_rows: one column of 129 to 256 rows, or eleven tiles and more in several)
+  // (what tiled_is_ahead lets through: one column of 129 to 256 rows, or eleven tiles and more in several)
   switch (m_tiles == 1 ? nta : nta * 10 + ntb) {
     case 5: return launch_big_t<kFp8, 5, 5, true>(a, st, m_tiles, n_a);
     case 6: return launch_big_t<kFp8, 6, 6, true>(a, st, m_tiles, n_a);

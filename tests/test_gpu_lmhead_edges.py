@@ -62,3 +62,14 @@ def test_lmhead_at_the_edges(gpu_lib, rows, fp8):
     unit = 128 if fp8 else 64  # hidden elements of a stage
     for i, (vocab, stages) in enumerate([(256, 1), (257, 2), (1000, 3), (63, 4), (2085, 5), (516, 7)]):
         _check(gpu_lib, rows, vocab, unit * stages, fp8, 1000 * rows + i)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("rows", [161, 192, 193, 225, 256, 321, 352, 383])
+def test_tiled_lmhead_of_one_round_less(gpu_lib, rows, fp8):
+    """171 vocabulary tiles: enough that the tiled kernel takes these rows from the W-streaming one, which has the small
+    vocabularies above."""
+    unit = 128 if fp8 else 64
+    for i, (vocab, stages) in enumerate([(43525, 1), (43776, 2), (43522, 3), (43772, 5)]):
+        _check(gpu_lib, rows, vocab, unit * stages, fp8, 2000 * rows + i)
