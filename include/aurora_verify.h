@@ -225,7 +225,8 @@ int aurora_verify_accept_logits(const aurora_accept_desc* desc, const int32_t* d
                                 void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Both halves on the same stream: attention, then acceptance.  The halves share no data
- * (the hidden states entering the LM head are an independent input). */
+ * (the hidden states entering the LM head are an independent input; if they lie in attn_out, the LM head reads what
+ * attention wrote there). */
 int aurora_verify(const aurora_attn_desc* attn_desc, const aurora_accept_desc* accept_desc,
                   const void* q, const void* k_pages, const void* v_pages,
                   const int32_t* block_table, const int32_t* seq_lens, const int32_t* parents,

@@ -18,7 +18,10 @@ torch = pytest.importorskip("torch")
                                                            # several rows a wavefront: formed in the sweep up to three tiles each, ..
                                                            (2, 9, 1000, 32, (30, 60), 64), (3, 24, 1024, 32, (30, 60), 64), (130, 17, 1100, 32, (30, 60), 64),
                                                            # .. or by the launch
-                                                           (2, 25, 1000, 32, (30, 60), 64), (3, 9, 1100, 32, (30, 60), 64), (127, 9, 1100, 32, (30, 60), 64)])
+                                                           (2, 25, 1000, 32, (30, 60), 64), (3, 9, 1100, 32, (30, 60), 64), (127, 9, 1100, 32, (30, 60), 64),
+                                                           # long contexts: in one launch with the head, and in two
+                                                           (1, 1, 500, 64, (40000, 40000), 128), (1, 1, 8000, 64, (40000, 40000), 128),
+                                                           (2, 8, 100, 64, (34000, 34000), 64)])
 def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, lens, dim, temps):
     from paper_2602_06932_amd.device import DeviceVerify
     from parity_util import check_accept, check_attention, check_logits
@@ -86,3 +89,44 @@ def test_logits_that_are_not_finite(gpu_lib, vocab, kind, temps):
         assert np.isnan(one["row_lse"]).all()
         sampled = np.arange(4) > 0 if temps else np.full(4, True)
         assert (one["accept_len"][sampled] == 0).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["hidden", "hidden_part", "lm_head"])
+def test_head_that_reads_what_attention_writes(gpu_lib, where):
+    """Hidden states (or W) that lie in attention's output: the step is attention, then the LM head, as its stages are."""
+    from paper_2602_06932_amd.device import DeviceVerify
+    w = gen.make_workload(name="small", seed=70, seq_lens=np.full(4, 300, np.int32), recipe="", batch=4, num_q=5, num_q_heads=8,
+                          num_kv_heads=2, head_dim=64, page_size=64, hidden_size=512, vocab=20 if where == "lm_head" else 1000,
+                          temperature=1.0, dtype=gen.F32, draft="noisy_target")
+    dv = DeviceVerify(w)
+    room = torch.zeros(3 * 20 * 512, device="cuda")
+    attn_out = room[20 * 512:40 * 512]
+    hidden, lm_head = dv.hidden, dv.lm_head
+    if where == "lm_head":
+        lm_head = attn_out
+    else:  # the same rows, or rows that begin in the output's last quarter
+        hidden = attn_out if where == "hidden" else room[35 * 512:55 * 512]
+
+    def step(*stages):
+        room.zero_()
+        dv.workspace.fill_(255)
+        for t in (dv.accept_len, dv.next_token, dv.accept_mask):
+            t.fill_(9)
+        torch.cuda.synchronize()
+        kv = (dv.q, dv.k_pages, dv.v_pages, dv.block_table, dv.seq_lens, None, attn_out)
+        acc = (hidden, lm_head, dv.draft_tokens, dv.draft_probs, dv.uniforms)
+        res = (dv.accept_len, dv.next_token, dv.accept_mask, dv.p_at_draft, dv.row_lse, dv.workspace)
+        if stages:
+            gpu_lib.aurora_verify_attn(dv.attn_desc, *kv, dv.workspace)
+            torch.cuda.synchronize()
+            gpu_lib.aurora_verify_accept(dv.accept_desc, *acc, None, *res)
+        else:
+            gpu_lib.aurora_verify(dv.attn_desc, dv.accept_desc, *kv, *acc, *res)
+        torch.cuda.synchronize()
+        return {**{n: x.copy() for n, x in dv.results_host().items()}, "out": attn_out.cpu().numpy()}
+
+    one, two = step(), step("attention", "accept")
+    assert np.abs(one["out"]).max() > 0
+    for n in one:
+        assert np.array_equal(one[n], two[n]), n
