@@ -140,19 +140,9 @@ bool verify_front_supported(const AttnLaunch& at, const AcceptLaunch& a) {
     return (uintptr_t)p < out_end && out < (uintptr_t)p + rows * a.H * sizeof(float);
   };
   if (meets_out(a.hidden, (size_t)a.plan.rows) || meets_out(a.lm_head, (size_t)a.V)) return false;
-  if (at.bf16 || at.kv_fp8 || at.lse_out || a.bf16 || a.fp8 || !few_rows(a)) return false;
-  const int64_t wgs = (int64_t)at.B * at.Nq * at.Hq * at.plan.max_splits;
-  // Long contexts, step in us as two launches and as one.  64-wide heads: the compiler keeps a K load less in flight in the shared
-  // kernel, which past some four million (query row, token) pairs is more than the launch: 2 x 8 positions x 8 heads x 30 000 tokens 299.7,
-  // 298.3; 7 x 8 x 8 x 17 000 527, 550; 9 x 10 x 8 x 30 000 1493, 1534 (128-wide: 11 x 6 x 16 x 13 000 2099, 1982).
-  if (at.D == 64 && wgs * at.plan.split_len > (1 << 22)) return false;
-  // Splits of more than 512 tokens that would all be resident by themselves, but not behind the head's tiles: the last of them start
-  // when the head is done, 1 x 1 x 8 x 65 536 tokens of 128 and 8000 logits of 1024 204, 223 (1000 of 256 185, 177: all resident).
-  // Three or five workgroups of a compute unit's registers.
-  const int64_t resident = 256 * (at.D == 64 ? 5 : 3);
-  const int64_t lm = (int64_t)((a.V + kSN - 1) / kSN) * ((a.plan.rows + kSM - 1) / kSM);
-  if (at.plan.split_len > 512 && wgs <= resident && wgs + lm > resident) return false;
-  return wgs < (1 << 23);  // (one grid dimension holds the workgroups of both: fewer than 2^32 threads)
+  // (one grid dimension holds the workgroups of both: fewer than 2^32 threads)
+  return !at.bf16 && !at.kv_fp8 && !at.lse_out && !a.bf16 && !a.fp8 && few_rows(a) &&
+         (int64_t)at.B * at.Nq * at.Hq * at.plan.max_splits < (1 << 23);
 }
 
 hipError_t launch_verify_front(const AttnLaunch& at, const AcceptLaunch& a, hipStream_t st) {
