@@ -140,9 +140,21 @@ bool verify_front_supported(const AttnLaunch& at, const AcceptLaunch& a) {
     return (uintptr_t)p < out_end && out < (uintptr_t)p + rows * a.H * sizeof(float);
   };
   if (meets_out(a.hidden, (size_t)a.plan.rows) || meets_out(a.lm_head, (size_t)a.V)) return false;
-  // (one grid dimension holds the workgroups of both: fewer than 2^32 threads)
-  return !at.bf16 && !at.kv_fp8 && !at.lse_out && !a.bf16 && !a.fp8 && few_rows(a) &&
-         (int64_t)at.B * at.Nq * at.Hq * at.plan.max_splits < (1 << 23);
+  if (at.bf16 || at.kv_fp8 || at.lse_out || a.bf16 || a.fp8 || !few_rows(a)) return false;
+  const int64_t wgs = (int64_t)at.B * at.Nq * at.Hq * at.plan.max_splits;
+  // Long contexts, step in us as two launches and as one.  64-wide heads: the compiler keeps a K load less in flight in the shared
+  // kernel, which past some four million (query row, token) pairs is more than the launch: 2 x 8 positions x 8 heads x 30 000 tokens 299.7,
+  // 298.3; 7 x 8 x 8 x 17 000 527, 550; 9 x 10 x 8 x 30 000 1493, 1534 (128-wide: 11 x 6 x 16 x 13 000 2099, 1982).
+  if (at.D == 64 && wgs * at.plan.split_len > (1 << 22)) return false;
+  // Attention that would all be resident by itself, but is not behind the head's tiles, starts late: with splits of more than 512 tokens
+  // (1 x 1 x 8 x 65 536 tokens of 128 and 8000 logits of 1024 204, 223; 1000 logits of 256, all resident, 185, 177), or where the
+  // head's tiles alone take two rounds (128-wide heads: the shared kernel's registers leave room for three workgroups, the head's own for five) and
+  // are long: 3 x 11 x 8 x 64 tokens and 8000 logits of 512, 1024, 2048, 4096: 45.4, 44.2; 57.8, 60.8; 85.7, 99.7; 143, 177.
+  // More attention than that covers them: 8 x 8 x 8 x 900 and 6500 of 2048 159, 143.
+  const int64_t resident = 256 * (at.D == 64 ? 5 : 3);
+  const int64_t lm = (int64_t)((a.V + kSN - 1) / kSN) * ((a.plan.rows + kSM - 1) / kSM);
+  if (wgs <= resident && wgs + lm > resident && (at.plan.split_len > 512 || (lm > resident && a.H > 1024))) return false;
+  return wgs < (1 << 23);  // (one grid dimension holds the workgroups of both: fewer than 2^32 threads)
 }
 
 hipError_t launch_verify_front(const AttnLaunch& at, const AcceptLaunch& a, hipStream_t st) {

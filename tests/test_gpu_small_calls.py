@@ -18,7 +18,12 @@ torch = pytest.importorskip("torch")
                                                            # several rows a wavefront: formed in the sweep up to three tiles each, ..
                                                            (2, 9, 1000, 32, (30, 60), 64), (3, 24, 1024, 32, (30, 60), 64), (130, 17, 1100, 32, (30, 60), 64),
                                                            # .. or by the launch
-                                                           (2, 25, 1000, 32, (30, 60), 64), (3, 9, 1100, 32, (30, 60), 64), (127, 9, 1100, 32, (30, 60), 64)])
+                                                           (2, 25, 1000, 32, (30, 60), 64), (3, 9, 1100, 32, (30, 60), 64), (127, 9, 1100, 32, (30, 60), 64),
+                                                           # long contexts: in one launch with the head, and in two
+                                                           (1, 1, 500, 64, (40000, 40000), 128), (1, 1, 8000, 64, (40000, 40000), 128),
+                                                           (2, 8, 100, 64, (34000, 34000), 64),
+                                                           # the head's tiles past one round of the shared kernel
+                                                           (3, 11, 8000, 1028, (60, 64), 128)])
 def test_float32_step_equals_its_stages(gpu_lib, batch, num_q, vocab, hidden, lens, dim, temps):
     from paper_2602_06932_amd.device import DeviceVerify
     from parity_util import check_accept, check_attention, check_logits
