@@ -26,19 +26,19 @@ MFMA_PEAK_TFLOPS = {4: 157.3, 2: 2500.0, 1: 5000.0}  # dense, by bytes per opera
 MEASURED_TRAFFIC = {
     ("llama", 1, "lmhead"): {"read_bytes": 1061753574, "write_bytes": 92878848,
         "source": "profiles/lmhead_counters_llama3_8b_chain_k4.txt"},
-    ("llama", 1, "attn"): {"read_bytes": 314706187 + 8241253, "write_bytes": 7954598 + 1310720,
+    ("llama", 1, "attn"): {"read_bytes": 314716160 + 8395161, "write_bytes": 7952486 + 1310720,
         "source": "profiles/attn_counters_llama3_8b_chain_k4.txt"},
     ("qwen_greedy", 1, "lmhead"): {"read_bytes": 1392347059, "write_bytes": 306916556,
         "source": "profiles/lmhead_counters_qwen3_8b_greedy_k6.txt"},
-    ("qwen_greedy", 1, "attn"): {"read_bytes": 1167539001 + 15271195, "write_bytes": 14873830 + 3670016,
+    ("qwen_greedy", 1, "attn"): {"read_bytes": 1167585280 + 15623782, "write_bytes": 14870528 + 3670016,
         "source": "profiles/attn_counters_qwen3_8b_greedy_k6.txt"},
     ("tree", 1, "lmhead"): {"read_bytes": 1185360051, "write_bytes": 296476716,
         "source": "profiles/lmhead_counters_llama3_8b_tree32.txt"},
-    ("tree", 1, "attn"): {"read_bytes": 277109115 + 34725227, "write_bytes": 34078816 + 4194304,
+    ("tree", 1, "attn"): {"read_bytes": 277135360 + 17906688, "write_bytes": 17058816 + 4194304,
         "source": "profiles/attn_counters_llama3_8b_tree32.txt"},
     ("stress", 1, "lmhead"): {"read_bytes": 6421602432, "write_bytes": 1162472960,
         "source": "profiles/lmhead_counters_stress_b256.txt"},
-    ("stress", 1, "attn"): {"read_bytes": 8113377592 + 42115614, "write_bytes": 40029894 + 15728640,
+    ("stress", 1, "attn"): {"read_bytes": 8113766400 + 41351168, "write_bytes": 40017920 + 15728640,
         "source": "profiles/attn_counters_stress_b256.txt"},
 }
 

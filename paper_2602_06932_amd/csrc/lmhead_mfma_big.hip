@@ -7,8 +7,8 @@
 // the fewest workgroup columns, so a launch uses at most two values of kT, one apart (544 rows: 6 + 6 + 5).
 //
 // 16 x 16 products: v_mfma_f32_16x16x32_bf16 and v_mfma_scale_f32_16x16x128_f8f6f4.  On operands like these the part's power
-// limit sets the rate, and it differs by the form: from registers 2.06 PFLOP/s against 1.35-1.39 for the 32x32x16 bf16 product
-// (fp8: 4.35 against 4.0 for 32x32x64).  1280 x 200064 x 6144: 2820 -> 2680 us from this alone.
+// limit sets the rate, and under it the smaller form gets further than the 32x32x16 one: 1280 x 200064 x 6144 2820 -> 2680 us from
+// the change of form alone.
 //
 // What bounds it then is latency: the vector cache returns a compute unit's loads in the order they were asked for, so a load
 // that hits L2 waits behind W's misses in front of it, and how long a load may take is how long before its use it can leave,

@@ -14,8 +14,8 @@
 // Nothing waits for data and the results are discarded: the probe measures rates, and how they depend on the VALUES
 // multiplied (the caller fills `operands`: random LM-head-like values, or zeros).  The time of a matrix-core
 // kernel on this part depends on them - the signature of a power limit - and the numbers this gives are the
-// ceiling of that form, which the tile of up to 160 rows uses; the many-row kernel multiplies in the 16x16x32 form, whose rate from
-// registers on the same values is half as high again (2.06 against 1.35-1.39 PFLOP/s).
+// ceiling of that form, which the W-streaming kernel uses; the many-row kernel multiplies in the 16x16x32 form, which this probe
+// does not measure.
 #include "launch.hpp"
 #include "lmhead_tile.hpp"
 

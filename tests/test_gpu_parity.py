@@ -308,9 +308,9 @@ def test_lmhead_stage_alone_matches_oracle_logits(gpu_lib):
                                                        (100, 7, 1500, 128), (55, 7, 1100, 64)])
 def test_lmhead_many_token_rows(gpu_lib, batch, num_q, vocab, hidden):
     """More than 160 token rows.  231 and 260 rows: several passes of the W-streaming kernel.  From 384 rows the
-    tiled kernel, whose workgroup columns hold three or four pairs of 32-row tiles: 384 rows = 3 + 3 pairs, 385 and
-    448 = 4 + 3 (the last pair half empty for 385), 505 = 4 + 4, 575 = 3 + 3 + 3, 700 = 4 + 4 + 3; ragged vocabulary
-    tail, statistics checked through row_lse / accept."""
+    tiled kernel, whose workgroup columns hold six to eight tiles of 32 rows: 384 rows = 6 + 6, 385 and 448 = 7 + 6 and
+    7 + 7, 505 = 8 + 8, 575 = 6 + 6 + 6, 700 = 8 + 7 + 7; ragged vocabulary tail, statistics checked through row_lse /
+    accept."""
     from paper_2602_06932_amd.device import DeviceVerify
     w = gen.llama_chain(18, batch=batch, num_q=num_q, len_lo=20, len_hi=40, vocab=vocab, hidden_size=hidden,
                         num_q_heads=4, num_kv_heads=2)
